@@ -209,6 +209,23 @@ int pp_back_tof_lm_batch(const float* xstart, const float* xend, const int16_t* 
                          const pp_image_t* geom, const pp_tof_t* tof, float* imgs, int32_t n_img, const float* p,
                          const int32_t* order, void* stream);
 
+/* Bytes of device memory pp_back_lm_ws needs for n events on this grid (tof NULL: non-TOF), 0 where
+ * the call is better served by pp_back, pp_back_tof_lm or their variants (many events per transaxial
+ * line, or a grid the tiles do not suit; invalid arguments also give 0).  Host only. */
+size_t pp_back_lm_workspace_bytes(int64_t n_events, const pp_image_t* geom, const pp_tof_t* tof);
+
+/* The listmode back projections (Sec. 2.2) with a caller workspace (16-byte aligned, at least
+ * pp_back_lm_workspace_bytes(n_events, geom, tof) bytes, else PP_EINVAL_N): the events' planes are
+ * collected per image tile and added up in LDS, so that the events need no order and sparse lines
+ * cost no more than dense ones.  Same results as pp_back (tof_bin NULL, tof unused),
+ * pp_back_tof_lm, pp_back_tof_lm_batch (n_img images and value arrays; n_img <= 1 without TOF) or, with
+ * pair != NULL, their crystal-index forms (xstart the crystal table, xend unused), up to the order and
+ * rounding of the sums (float64 inside a tile).  The workspace is free for other use in stream order. */
+int pp_back_lm_ws(const float* xstart, const float* xend, int32_t n_crystals, const int32_t* pair,
+                  const int16_t* tof_bin, int64_t n_events, const pp_image_t* geom, const pp_tof_t* tof, float* imgs,
+                  int32_t n_img, const float* p, const int32_t* order, void* workspace, size_t workspace_bytes,
+                  void* stream);
+
 /* TOF listmode back projection, adjoint of pp_fwd_tof_lm: img += A^T p. */
 int pp_back_tof_lm(const float* xstart, const float* xend, const int16_t* tof_bin, int64_t n_events,
                    const pp_image_t* geom, const pp_tof_t* tof, float* img, const float* p, const int32_t* order,

@@ -161,6 +161,7 @@ def load():
         "pp_fwd_tof_lm_batch": [P, P, P, I64, G, T, P, I32, P, P, P],
         "pp_fwd_tof_lm_gather": [P, P, P, I64, G, T, P, P, P, P, P, P, P, P],
         "pp_back_tof_lm_batch": [P, P, P, I64, G, T, P, I32, P, P, P],
+        "pp_back_lm_ws": [P, P, I32, P, P, I64, G, T, P, I32, P, P, P, ctypes.c_size_t, P],
         "pp_lm_presort": [P, P, P, I64, G, T, I32, P, P, ctypes.c_size_t, P],
         "pp_lm_presort_noalloc": [P, P, P, I64, G, T, I32, P, P],
         "pp_gather_events": [P, P, P, P, I64, P, P, P, P],
@@ -190,6 +191,8 @@ def load():
         f.restype = INT
     lib.pp_lm_presort_workspace_bytes.argtypes = [I64]
     lib.pp_lm_presort_workspace_bytes.restype = ctypes.c_size_t
+    lib.pp_back_lm_workspace_bytes.argtypes = [I64, G, T]
+    lib.pp_back_lm_workspace_bytes.restype = ctypes.c_size_t
     lib.pp_osem_chunks.argtypes = [I64, I32]
     lib.pp_osem_chunks.restype = I64
     lib.pp_strerror.argtypes = [INT]

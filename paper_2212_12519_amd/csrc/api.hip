@@ -380,6 +380,33 @@ int pp_back_tof_lm(const float* xstart, const float* xend, const int16_t* tof_bi
     return hip_status(launch_back_tof_lm(coords(xstart, xend), tof_bin, n, g, t, img, p, order, as_stream(stream)));
 }
 
+size_t pp_back_lm_workspace_bytes(int64_t n, const pp_image_t* geom, const pp_tof_t* tof) {
+    GeomK g;
+    TofK t;
+    if (make_geom(geom, g) != PP_OK || (tof && make_tof(tof, t) != PP_OK)) return 0;
+    return tile_workspace_bytes(n, g, tof ? &t : nullptr);
+}
+
+int pp_back_lm_ws(const float* xstart, const float* xend, int32_t n_crystals, const int32_t* pair,
+                  const int16_t* tof_bin, int64_t n, const pp_image_t* geom, const pp_tof_t* tof, float* imgs,
+                  int32_t n_img, const float* p, const int32_t* order, void* workspace, size_t workspace_bytes,
+                  void* stream) {
+    GeomK g;
+    TofK t;
+    RaySrc src = coords(xstart, xend);
+    PP_TRY(make_geom(geom, g));
+    if (tof_bin) PP_TRY(make_tof(tof, t));
+    if (n < 0 || n > INT32_MAX || n_img < 0 || n_img > (1 << 20) || (!tof_bin && n_img > 1)) return PP_EINVAL_N;
+    if (pair) PP_TRY(crystals(xstart, n_crystals, pair, n, src));
+    if (n == 0 || n_img == 0) return PP_OK;
+    if (!xstart || (!pair && !xend) || !imgs || !p || !workspace) return PP_EINVAL_PTR;
+    if ((reinterpret_cast<uintptr_t>(workspace) & 15u) != 0) return PP_EINVAL_PTR;
+    const size_t need = tile_workspace_bytes(n, g, tof_bin ? &t : nullptr);
+    if (need == 0 || workspace_bytes < need) return PP_EINVAL_N;
+    return hip_status(launch_back_tiles(src, tof_bin, n, g, tof_bin ? &t : nullptr, imgs, n_img, p, order, workspace,
+                                        device_cus(), as_stream(stream)));
+}
+
 int pp_count_samples(const float* xstart, const float* xend, const int16_t* tof_bin, int64_t n, const pp_image_t* geom,
                      const pp_tof_t* tof, int32_t* counts, void* stream) {
     GeomK g;

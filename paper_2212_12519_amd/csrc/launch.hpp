@@ -42,6 +42,12 @@ hipError_t launch_back_tof_lm(const RaySrc& src, const int16_t* bins, int64_t n,
 hipError_t launch_back_tof_lm_batch(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g,
                                     const TofK& t, float* imgs, int n_img, const float* p, const int32_t* order,
                                     hipStream_t s);
+// tile back projection (tiles.hip): workspace bytes, 0 where the run/sheet kernel is the better one; bins
+// nullptr: non-TOF (one image)
+size_t tile_workspace_bytes(int64_t n, const GeomK& g, const TofK* t);
+hipError_t launch_back_tiles(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK* t,
+                             float* imgs, int n_img, const float* p, const int32_t* order, void* ws, int cus,
+                             hipStream_t s);
 hipError_t launch_poisson_nll(const float* p, float bg, const float* y, int64_t n, float* grad, double* partial,
                               int n_partial, hipStream_t s);
 size_t presort_workspace_bytes(int64_t n);

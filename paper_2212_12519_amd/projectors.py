@@ -14,6 +14,22 @@ from ._lib import (TofParams, _bins, _crystal_events, _dev, _img, _order, _rays,
                    stream_of)
 
 
+def _back_lm_tiles(xs, xe, n_crystals, pair, tof_bin, n, gc, tc, imgs, n_img, p, order):
+    """A listmode back projection by image tiles (pp_back_lm_ws) with a workspace from torch's allocator; False,
+    with nothing launched, where the library prefers its run/sheet kernel or the memory for it is not there."""
+    lib = load()
+    nbytes = lib.pp_back_lm_workspace_bytes(n, gc, tc) if n > 0 and n_img > 0 else 0
+    if nbytes == 0:
+        return False
+    try:
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=imgs.device)
+    except torch.OutOfMemoryError:
+        return False
+    check(lib.pp_back_lm_ws(ptr(xs), ptr(xe), n_crystals, ptr(pair), ptr(tof_bin), n, gc, tc, ptr(imgs), n_img, ptr(p),
+                            ptr(order), ptr(ws), nbytes, stream_of(imgs)))
+    return True
+
+
 def pp_fwd(xstart, xend, geom, img, p, order=None):
     """Non-TOF forward projection into p[n] (overwritten). Sec. 2.1 of the paper.
     order: optional int32 processing order (pp_lm_presort); results stay indexed by ray."""
@@ -37,7 +53,9 @@ def pp_back(xstart, xend, geom, img, p, order=None):
     _order(order, n)
     if p.dtype != torch.float32 or p.numel() != n:
         raise ValueError("p must be float32 [n]")
-    check(load().pp_back(ptr(xstart), ptr(xend), n, g.c(), ptr(img), ptr(p), ptr(order), stream_of(img)))
+    # an order makes it a listmode call; ray lists without one (sinograms) are runs of one line each
+    if order is None or not _back_lm_tiles(xstart, xend, 0, None, None, n, g.c(), None, img, 1, p, order):
+        check(load().pp_back(ptr(xstart), ptr(xend), n, g.c(), ptr(img), ptr(p), ptr(order), stream_of(img)))
     return img
 
 
@@ -132,8 +150,9 @@ def pp_back_tof_lm_batch(xstart, xend, tof_bin, geom, tof, imgs, p, order=None):
     nb = imgs.numel() // g.n_vox
     if p.dtype != torch.float32 or p.numel() != nb * n:
         raise ValueError("p must be float32 [B, n]")
-    check(load().pp_back_tof_lm_batch(ptr(xstart), ptr(xend), ptr(tof_bin), n, g.c(), t.c(n), ptr(imgs), nb, ptr(p),
-                                      ptr(order), stream_of(p)))
+    if not _back_lm_tiles(xstart, xend, 0, None, tof_bin, n, g.c(), t.c(n), imgs, nb, p, order):
+        check(load().pp_back_tof_lm_batch(ptr(xstart), ptr(xend), ptr(tof_bin), n, g.c(), t.c(n), ptr(imgs), nb, ptr(p),
+                                          ptr(order), stream_of(p)))
     return imgs
 
 
@@ -147,8 +166,9 @@ def pp_back_tof_lm(xstart, xend, tof_bin, geom, tof, img, p, order=None):
     _order(order, n)
     if p.dtype != torch.float32 or p.numel() != n:
         raise ValueError("p must be float32 [n]")
-    check(load().pp_back_tof_lm(ptr(xstart), ptr(xend), ptr(tof_bin), n, g.c(), t.c(n), ptr(img), ptr(p),
-                                ptr(order), stream_of(img)))
+    if not _back_lm_tiles(xstart, xend, 0, None, tof_bin, n, g.c(), t.c(n), img, 1, p, order):
+        check(load().pp_back_tof_lm(ptr(xstart), ptr(xend), ptr(tof_bin), n, g.c(), t.c(n), ptr(img), ptr(p),
+                                    ptr(order), stream_of(img)))
     return img
 
 
@@ -413,8 +433,9 @@ def pp_back_crystals(crystal_xyz, pair, geom, img, p, order=None):
     _order(order, n)
     if p.dtype != torch.float32 or p.numel() != n:
         raise ValueError("p must be float32 [n]")
-    check(load().pp_back_crystals(ptr(crystal_xyz), nc, ptr(pair), n, g.c(), ptr(img), ptr(p), ptr(order),
-                                  stream_of(img)))
+    if not _back_lm_tiles(crystal_xyz, None, nc, pair, None, n, g.c(), None, img, 1, p, order):
+        check(load().pp_back_crystals(ptr(crystal_xyz), nc, ptr(pair), n, g.c(), ptr(img), ptr(p), ptr(order),
+                                      stream_of(img)))
     return img
 
 
@@ -441,8 +462,9 @@ def pp_back_tof_lm_crystals(crystal_xyz, pair, tof_bin, geom, tof, img, p, order
     _order(order, n)
     if p.dtype != torch.float32 or p.numel() != n:
         raise ValueError("p must be float32 [n]")
-    check(load().pp_back_tof_lm_crystals(ptr(crystal_xyz), nc, ptr(pair), ptr(tof_bin), n, g.c(), t.c(n), ptr(img),
-                                         ptr(p), ptr(order), stream_of(img)))
+    if not _back_lm_tiles(crystal_xyz, None, nc, pair, tof_bin, n, g.c(), t.c(n), img, 1, p, order):
+        check(load().pp_back_tof_lm_crystals(ptr(crystal_xyz), nc, ptr(pair), ptr(tof_bin), n, g.c(), t.c(n), ptr(img),
+                                             ptr(p), ptr(order), stream_of(img)))
     return img
 
 
