@@ -2,6 +2,7 @@
 // The declarations, conventions and error codes are documented in ppmi.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -38,6 +39,7 @@ int make_geom(const pp_image_t* gi, GeomK& g) {
     for (int a = 0; a < 3; ++a) {
         g.o[a] = gi->origin[a];
         g.h[a] = gi->voxsize[a];
+        g.ih[a] = 1.0 / g.h[a];
         g.n[a] = gi->dim[a];
     }
     g.stride[2] = 1;
@@ -120,7 +122,50 @@ void fit_tof_poly(TofK& t, double sig, double ns, double bw) {
     if (err <= 5e-7 * peak) t.poly = 1;
 }
 
-int make_tof(const pp_tof_t* ti, TofK& t) {
+// The device's tof_edge_weights in the same float32 operations: Phi at g + (m + 1/2) (upper: its negative at
+// g - (m + 1/2)).
+float tof_edge_host(float g, int m, bool upper, const TofEdgeK& e) {
+    const float* c = e.c[m];
+    float x = upper ? -g : g;
+    if (m == e.R - 1) x = std::fmin(x, e.t_max);
+    const float q = x * x;
+    const float A = std::fmaf(std::fmaf(std::fmaf(c[6], q, c[4]), q, c[2]), q, c[0]);
+    const float B = std::fmaf(std::fmaf(std::fmaf(c[7], q, c[5]), q, c[3]), q, c[1]);
+    return std::fmaf(x, B, A);
+}
+
+// Fits the edge polynomials of the sinogram kernels (TofEdgeK), one Gaussian for all rays.  Kept (R > 0) if the
+// float32 evaluation stays within 1.5e-7 of the exact Phi at every edge (checked at 257 offsets per edge): a
+// bin's weight, a difference of two, then is as near as the erf form's (3.4e-7).
+void fit_tof_edges(const TofK& t, double sig, double ns, double bw, TofEdgeK& e) {
+    e.R = 0;
+    if (t.lut || t.sig_ray || t.off_ray) return;
+    const double X = ns * sig / bw, k = bw / (std::sqrt(2.0) * sig);
+    if (!(X > 0.0 && X <= (double)kEdgeMaxR)) return;
+    const int R = std::max((int)std::ceil(X), 1);
+    static_assert(kEdgeDegree == 7, "tof_edge_weights is written for degree 7");
+    auto phi = [&](double x) { return 0.5 * std::erf(k * std::fmin(std::fmax(x, -X), X)); };
+    e.R = R;
+    e.inv_bw = 1.0 / bw;
+    e.B0 = -t.c0 / bw;
+    e.sat = (float)phi(X);
+    e.t_max = (float)(X - (R - 0.5));
+    for (int m = 0; m < R; ++m) {
+        double c[kEdgeDegree + 1];
+        cheb_powers([&](double s) { return 0.5 * std::erf(k * (m + 0.5 + 0.5 * s)); }, kEdgeDegree, c);
+        for (int i = 0; i <= kEdgeDegree; ++i) e.c[m][i] = (float)std::ldexp(c[i], i);  // s = 2 t
+    }
+    double err = 0.0;
+    for (int m = 0; m < R; ++m)
+        for (int i = 0; i <= 256; ++i) {
+            const float g = (float)(i / 256.0 - 0.5);
+            err = std::fmax(err, std::fabs(tof_edge_host(g, m, false, e) - phi(m + 0.5 + (double)g)));
+            err = std::fmax(err, std::fabs(tof_edge_host(g, m, true, e) - phi(m + 0.5 - (double)g)));
+        }
+    if (!(err <= 1.5e-7)) e.R = 0;
+}
+
+int make_tof(const pp_tof_t* ti, TofK& t, TofEdgeK* edges = nullptr) {
     if (!ti) return PP_EINVAL_PTR;
     if (ti->n_bins < 1 || ti->n_bins > 256) return PP_EINVAL_TOF;
     if (!std::isfinite(ti->bin_width) || !(ti->bin_width > 0.0f) || !std::isfinite(ti->center_offset))
@@ -151,6 +196,7 @@ int make_tof(const pp_tof_t* ti, TofK& t) {
         t.lut_inv_dx = (float)(1.0 / dx);
         t.poly = 0;
         t.wpeak = 0.0f;
+        if (edges) edges->R = 0;
         return PP_OK;
     }
     if (!std::isfinite(ti->sigma) || !(ti->sigma > 0.0f) || !std::isfinite(ti->n_sigmas) || !(ti->n_sigmas > 0.0f))
@@ -172,7 +218,12 @@ int make_tof(const pp_tof_t* ti, TofK& t) {
     t.lut = nullptr;
     t.lut_n = 0;
     t.lut_inv_dx = 0.0f;
-    fit_tof_poly(t, sig, ns, bw);
+    if (edges) {  // the sinogram kernels
+        t.poly = 0;
+        fit_tof_edges(t, sig, ns, bw, *edges);
+    } else {
+        fit_tof_poly(t, sig, ns, bw);
+    }
     return PP_OK;
 }
 
@@ -290,20 +341,22 @@ int pp_fwd_tof_sino(const float* xstart, const float* xend, int64_t n, const pp_
                     const float* img, float* p, void* stream) {
     GeomK g;
     TofK t;
+    TofEdgeK te;
     PP_TRY(make_geom(geom, g));
-    PP_TRY(make_tof(tof, t));
+    PP_TRY(make_tof(tof, t, &te));
     PP_TRY(check_n_sino(n));
     if (n == 0) return PP_OK;
     if (!xstart || !xend || !img || !p) return PP_EINVAL_PTR;
-    return hip_status(launch_fwd_tof_sino(coords(xstart, xend), n, g, t, img, p, as_stream(stream)));
+    return hip_status(launch_fwd_tof_sino(coords(xstart, xend), n, g, t, &te, img, p, as_stream(stream)));
 }
 
 int pp_back_tof_sino(const float* xstart, const float* xend, int64_t n, const pp_image_t* geom, const pp_tof_t* tof,
                      float* img, const float* p, void* stream) {
     GeomK g;
     TofK t;
+    TofEdgeK te;
     PP_TRY(make_geom(geom, g));
-    PP_TRY(make_tof(tof, t));
+    PP_TRY(make_tof(tof, t, &te));
     PP_TRY(check_n_sino(n));
     if (n == 0) return PP_OK;
     if (!xstart || !xend || !img || !p) return PP_EINVAL_PTR;

@@ -22,6 +22,7 @@ namespace ppmi {
 struct GeomK {
     double o[3];   // centre of voxel (0,0,0), mm
     double h[3];   // voxel size, mm
+    double ih[3];  // 1 / h
     int n[3];      // voxels per axis
     int stride[3]; // element strides (n1*n2, n2, 1)
 };
@@ -67,6 +68,20 @@ struct GaussK {
     float w[3][2 * kGaussMaxR + 1];
 };
 
+// The TOF bin weights of a sample as differences of Phi, the truncated Gaussian's distribution function less
+// 1/2 (Phi(x) = erf(clip(x) / (sqrt(2) sigma)) / 2, x in bin widths), at the bin edges around it: with g in
+// [-1/2, 1/2) the sample's offset from the centre of the bin it lies in, the edges lie at g +- (m + 1/2),
+// m = 0 .. R - 1 (beyond them Phi is clipped), and Phi(m + 1/2 + t) is a polynomial in t, fitted on the host.
+constexpr int kEdgeMaxR = 5;
+constexpr int kEdgeDegree = 7;
+struct TofEdgeK {
+    int R;         // 0: no fit within the error bound, or more than kEdgeMaxR edges on a side
+    float sat;     // Phi beyond the truncation
+    float t_max;   // the outermost edge's argument is clipped to t_max
+    double B0, inv_bw;  // position in bins, B0 + s inv_bw: the nearest integer is the bin, the remainder g
+    float c[kEdgeMaxR][kEdgeDegree + 1];  // Phi(m + 1/2 + t) = sum_i c[m][i] t^i
+};
+
 // A ray prepared for plane stepping along its principal axis p.
 struct RayK {
     double U0, dU;  // in-plane voxel coordinate along axis u at plane k: U0 + k dU
@@ -85,15 +100,31 @@ __device__ __forceinline__ int clamp_plane(double v, int lo, int hi) {
     return (int)v;
 }
 
+// x / y from y's correctly rounded reciprocal r: the quotient's residual corrects it to the correctly rounded
+// one (Markstein), in three instructions instead of a division's thirty.
+__device__ __forceinline__ double div_by(double x, double y, double r) {
+    const double q = x * r;
+    return fma(fma(-q, y, x), r, q);
+}
+
+// 1 / x to about an ulp (x finite, not subnormal)
+__device__ __forceinline__ double near_rcp(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+
 // Restrict [lo, hi] to the planes k whose coordinate a0 + k da lies in (amin, amax).
-// Conservative by one plane on each side; exact filtering happens per sample.
+// Conservative by one plane on each side (far more than the rounding of the crossings); exact filtering happens
+// per sample.
 __device__ __forceinline__ void clip_affine(double a0, double da, double amin, double amax, int& lo, int& hi) {
     if (da == 0.0) {
         if (!(a0 > amin && a0 < amax)) hi = lo - 1;
         return;
     }
-    double k1 = (amin - a0) / da;
-    double k2 = (amax - a0) / da;
+    const double r = near_rcp(da);
+    double k1 = (amin - a0) * r;
+    double k2 = (amax - a0) * r;
     double kmin = fmin(k1, k2), kmax = fmax(k1, k2);
     int a = clamp_plane(floor(kmin), lo, hi);
     int b = clamp_plane(ceil(kmax), lo, hi);
@@ -126,18 +157,18 @@ __device__ __forceinline__ bool ray_setup(const float* __restrict__ xs, const fl
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         d[a] = (double)e32[a] - (double)s32[a];
-        S[a] = ((double)s32[a] - g.o[a]) / g.h[a];
-        D[a] = d[a] / g.h[a];
+        S[a] = div_by((double)s32[a] - g.o[a], g.h[a], g.ih[a]);
+        D[a] = div_by(d[a], g.h[a], g.ih[a]);
     }
     const double len = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-    const double Sp = S[p], Dp = D[p];
-    r.dU = D[u] / Dp;
-    r.dW = D[w] / Dp;
+    const double Sp = S[p], Dp = D[p], iDp = 1.0 / Dp;
+    r.dU = div_by(D[u], Dp, iDp);
+    r.dW = div_by(D[w], Dp, iDp);
     r.U0 = S[u] - Sp * r.dU;
     r.W0 = S[w] - Sp * r.dW;
-    r.ds = len / Dp;
+    r.ds = div_by(len, Dp, iDp);
     r.s0 = -Sp * r.ds - 0.5 * len;
-    r.ell = (float)(g.h[p] * len / fabs(d[p]));
+    r.ell = (float)fabs(r.ds);  // h_p len / |d_p|
     r.sp = g.stride[p];
     r.su = g.stride[u];
     r.sw = g.stride[w];
@@ -405,6 +436,46 @@ __device__ __forceinline__ float tof_erf(float x, float inv, const TofK& t) {
     return erf_scaled(__builtin_amdgcn_fmed3f(x * inv, -t.u_max, t.u_max));
 }
 
+
+// The weights of the 2 R + 1 bins around the bin a sample lies in, w[R + i] for the i-th bin above it; the inner
+// edges in pairs: Phi(h + g) = A(g^2) + g B(g^2), -Phi(g - h) = A(g^2) - g B(g^2).  About 9 instructions per
+// inner pair of edges and 18 for the outer one, where two erf take about 26 (two half-rate ones each).
+// The coefficients that meet a second scalar operand in one instruction, moved to vector registers once.
+template <int R>
+__device__ __forceinline__ void tof_edge_to_vgprs(TofEdgeK& t) {
+#pragma unroll
+    for (int m = 0; m < R; ++m) asm volatile("" : "+v"(t.c[m][6]), "+v"(t.c[m][7]));
+}
+
+template <int R>
+__device__ __forceinline__ void tof_edge_weights(float g, const TofEdgeK& t, float (&w)[2 * R + 1]) {
+    float pos[R], neg[R];  // Phi at the edges below and, negated, above
+    const float q = g * g;
+#pragma unroll
+    for (int m = 0; m < R - 1; ++m) {
+        const float A = fmaf(fmaf(fmaf(t.c[m][6], q, t.c[m][4]), q, t.c[m][2]), q, t.c[m][0]);
+        const float B = fmaf(fmaf(fmaf(t.c[m][7], q, t.c[m][5]), q, t.c[m][3]), q, t.c[m][1]);
+        pos[m] = fmaf(g, B, A);
+        neg[m] = fmaf(-g, B, A);
+    }
+    auto outer = [&](float x) {
+        x = __builtin_amdgcn_fmed3f(x, -1.0f, t.t_max);  // min: x >= -1/2
+        const float y = x * x;
+        const float A = fmaf(fmaf(fmaf(t.c[R - 1][6], y, t.c[R - 1][4]), y, t.c[R - 1][2]), y, t.c[R - 1][0]);
+        const float B = fmaf(fmaf(fmaf(t.c[R - 1][7], y, t.c[R - 1][5]), y, t.c[R - 1][3]), y, t.c[R - 1][1]);
+        return fmaf(x, B, A);
+    };
+    pos[R - 1] = outer(g);
+    neg[R - 1] = outer(-g);
+    w[R] = pos[0] + neg[0];
+#pragma unroll
+    for (int m = 1; m < R; ++m) {
+        w[R - m] = pos[m] - pos[m - 1];
+        w[R + m] = neg[m] - neg[m - 1];
+    }
+    w[0] = t.sat - pos[R - 1];
+    w[2 * R] = t.sat - neg[R - 1];
+}
 
 // Tabulated kernel (the lookup-table alternative of Sec. 4, which also admits non-Gaussian
 // TOF kernels): linear interpolation of the table at u = (x - lo) / dx, 0 outside it.

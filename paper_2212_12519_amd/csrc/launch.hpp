@@ -10,6 +10,7 @@ namespace ppmi {
 
 struct GeomK;
 struct TofK;
+struct TofEdgeK;
 struct RaySrc;
 
 // Events and projections written in processing order by launch_fwd_tof_lm_gather
@@ -24,7 +25,8 @@ hipError_t launch_fwd(const RaySrc& src, int64_t n, const GeomK& g, const float*
                       const int32_t* order, hipStream_t s);
 hipError_t launch_back(const RaySrc& src, int64_t n, const GeomK& g, float* img, const float* p,
                        const int32_t* order, hipStream_t s);
-hipError_t launch_fwd_tof_sino(const RaySrc& src, int64_t n, const GeomK& g, const TofK& t,
+// te: the fitted edge polynomials, or nullptr (or no fit): the erf form
+hipError_t launch_fwd_tof_sino(const RaySrc& src, int64_t n, const GeomK& g, const TofK& t, const TofEdgeK* te,
                                const float* img, float* p, hipStream_t s);
 hipError_t launch_back_tof_sino(const RaySrc& src, int64_t n, const GeomK& g, const TofK& t,
                                 float* img, const float* p, hipStream_t s);

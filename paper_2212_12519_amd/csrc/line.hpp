@@ -1,0 +1,232 @@
+// Forward projection of ray lists in which many consecutive rays lie on one transaxial line (sinograms
+// with the ring pairs fastest, densely presorted events).
+//
+// The rays of a line (bitwise-equal principal axis p in {0, 1}, U0 and dU) meet the image in the same two
+// columns per plane, so a workgroup interpolates the columns once, sheet[k][j] = (1 - fu) img[k][i0][j] +
+// fu img[k][i0 + 1][j], and keeps this sheet in LDS: a sample is then two neighbouring LDS words instead of
+// four global gathers with their index arithmetic and bounds (the rows carry a zero at either end).
+// Consecutive groups on one line share the sheet.  Rays of short runs, or along axis 2, gather from the
+// image.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "joseph.hpp"
+
+namespace ppmi {
+
+constexpr int kLineMaxBlock = 1024;
+constexpr int kLineHeads = 32;  // a group with more runs than its rays / kLineHeads gathers them all
+
+// Whether the runs of a group of T rays are long enough for the group's waves to share sheets: by the transaxial
+// end points of three of its rays, half a group apart, two neighbours of which lie on one line.  (Much shorter
+// runs would be walked one after the other by a few of the waves.)
+__device__ inline bool line_group(const RaySrc& src, int64_t i0, int64_t n, int T) {
+    const float *s[3], *e[3];
+    bool ok = true;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int64_t i = i0 + q * T / 2 - (q == 2);
+        ok &= src.ends(i < n ? i : n - 1, s[q], e[q]);
+    }
+    if (!ok) return false;
+    float2 a[3], b[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) a[q] = make_float2(s[q][0], s[q][1]), b[q] = make_float2(e[q][0], e[q][1]);
+    auto same = [&](int q) { return a[q].x == a[q + 1].x && a[q].y == a[q + 1].y && b[q].x == b[q + 1].x && b[q].y == b[q + 1].y; };
+    return same(0) || same(1);
+}
+
+// Rows of the sheet: planes 0 .. n_p - 1, nw + 2 entries each (slices -1 .. nw)
+__host__ __device__ inline int line_stride(const GeomK& g) { return g.n[2] + 2; }
+__host__ __device__ inline int line_planes(const GeomK& g) { return g.n[0] > g.n[1] ? g.n[0] : g.n[1]; }
+// Words of a sheet with a guard entry on either side, and of its planes' records (LinePlane)
+__host__ __device__ inline int line_words(const GeomK& g) { return line_planes(g) * line_stride(g) + 2; }
+__host__ __device__ inline int line_plane_words(const GeomK& g) { return 3 * line_planes(g); }
+
+// Trim the (conservative) plane range to the planes whose stencil has its first voxel in [-1, n): W then
+// addresses the sheet's row without further checks.
+__device__ __forceinline__ void line_trim(RayK& r) {
+    auto out = [&](int k) {
+        const int i = (int)floor(fma((double)k, r.dU, r.U0)), j = (int)floor(fma((double)k, r.dW, r.W0));
+        return i < -1 || i >= r.nu || j < -1 || j >= r.nw;
+    };
+    while (r.k_lo <= r.k_hi && out(r.k_lo)) ++r.k_lo;
+    while (r.k_lo <= r.k_hi && out(r.k_hi)) --r.k_hi;
+}
+
+// The sheet of line (p, U0, dU) over all planes (every thread of the workgroup; zeros where a column lies
+// outside the grid).  The planes' column offsets and weights are worked out once; a thread keeps its slice and
+// takes every rows-th plane, four planes' loads in flight together: with one at a time the load's latency, not
+// the rays' samples, was most of the kernel's time.
+struct LinePlane {
+    unsigned a, b;  // byte offsets of the two columns; out of the image's range outside the grid
+    float fu;
+};
+constexpr unsigned kLineOutside = 0xC0000000u;  // beyond every grid whose sheet fits the LDS
+
+__device__ __forceinline__ void line_load(float* sheet, LinePlane* planes, __amdgpu_buffer_rsrc_t ib, const GeomK& g, int p,
+                                 double U0, double dU) {
+    const int np = g.n[p], nu = g.n[1 - p], nw = g.n[2], zs = line_stride(g);
+    const int sp = g.stride[p], su = g.stride[1 - p];
+    const int T = blockDim.x, lanes = min(nw, T), rows = T / lanes;
+    for (int k = threadIdx.x; k < np; k += T) {
+        const double U = fma((double)k, dU, U0), fi = floor(U);
+        const int i0 = (int)fmin(fmax(fi, -2.0), (double)nu);
+        const unsigned at = (unsigned)(k * sp + i0 * su) * 4u;
+        planes[k] = {(unsigned)i0 < (unsigned)nu ? at : kLineOutside,
+                     (unsigned)(i0 + 1) < (unsigned)nu ? at + (unsigned)su * 4u : kLineOutside, (float)(U - fi)};
+    }
+    __syncthreads();
+    const int kr = (int)threadIdx.x / lanes;
+    constexpr int kBatch = 4;
+    if (kr >= rows) return;
+    for (int j = (int)threadIdx.x - kr * lanes; j < nw; j += lanes) {
+        for (int k0 = kr; k0 < np; k0 += kBatch * rows) {
+            float a[kBatch], b[kBatch], fu[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const LinePlane q = planes[min(k0 + u * rows, np - 1)];
+                fu[u] = q.fu;
+                a[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ib, q.a + 4u * j, 0, 0));
+                b[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ib, q.b + 4u * j, 0, 0));
+            }
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int k = k0 + u * rows;
+                if (k < np) sheet[k * zs + j + 1] = fmaf(fu[u], b[u], (1.0f - fu[u]) * a[u]);
+            }
+        }
+    }
+}
+
+// The samples of a ray through the sheet: f(v, k) with the interpolated value v at plane k, and with Four also
+// f4(v) for four planes at once.  Z(k) = W(k) + 1 + k zs is the position in the sheet as one array: its integer
+// part addresses the pair of entries (row and slice at once), its remainder is fw.  (Z keeps 38 bits behind the
+// point; a rounding across an integer at the grid's faces reads the neighbouring row's zero or the guard entry
+// beside the sheet.)
+template <bool Four, class F, class F4>
+__device__ __forceinline__ void line_walk(const float* sheet, int zs, const RayK& r, F f, F4 f4) {
+    const double dZ = r.dW + (double)zs, Z0 = r.W0 + 1.0, d2 = dZ + dZ, d3 = d2 + dZ;
+    auto at = [&](double Z) {
+        const int i = (int)Z;
+        const float a = sheet[i], b = sheet[i + 1];
+        return fmaf((float)__builtin_amdgcn_fract(Z), b - a, a);
+    };
+    int k = r.k_lo;
+    if (Four)
+        for (; k + 3 <= r.k_hi; k += 4) {
+            const double Z = fma((double)k, dZ, Z0);
+            const float v[4] = {at(Z), at(Z + dZ), at(Z + d2), at(Z + d3)};
+            f4(v);
+        }
+    for (; k <= r.k_hi; ++k) f(at(fma((double)k, dZ, Z0)), k);
+}
+
+// The runs of a group of blockDim.x consecutive rays, one per thread (line: p in {0, 1} and U0, dU; p < 0: a
+// ray on no line).  heads[w]: the positions of wave w where a new run begins.  Returns the number of runs.
+// Every thread of the workgroup calls it; it synchronises once before and once after writing.
+__device__ inline int line_runs(int p, double U0, double dU, unsigned long long* heads, double* last) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    int pp = __shfl_up(p, 1, 64);
+    double pU = __shfl_up(U0, 1, 64), pd = __shfl_up(dU, 1, 64);
+    __syncthreads();  // the previous group's readers are done
+    if (lane == 63) {
+        last[3 * wave] = (double)p;
+        last[3 * wave + 1] = U0;
+        last[3 * wave + 2] = dU;
+    }
+    __syncthreads();
+    if (lane == 0 && wave > 0) {
+        pp = (int)last[3 * wave - 3];
+        pU = last[3 * wave - 2];
+        pd = last[3 * wave - 1];
+    }
+    const bool head = threadIdx.x == 0 || p != pp || (p >= 0 && (U0 != pU || dU != pd));
+    const unsigned long long b = __ballot(head);
+    if (lane == 0) heads[wave] = b;
+    __syncthreads();
+    int count = 0;
+    for (int w = 0; w < waves; ++w) count += __popcll(heads[w]);
+    return count;
+}
+
+// First position after `at` where a run begins (blockDim.x if none)
+__device__ __forceinline__ int line_next(const unsigned long long* heads, int at) {
+    const int waves = blockDim.x >> 6;
+    int w = (at + 1) >> 6;
+    if (w >= waves) return blockDim.x;
+    unsigned long long m = heads[w] & (~0ull << ((at + 1) & 63));
+    while (m == 0) {
+        if (++w >= waves) return blockDim.x;
+        m = heads[w];
+    }
+    return w * 64 + __ffsll((long long)m) - 1;
+}
+
+// The workgroup's state in LDS.
+struct LineShared {
+    unsigned long long heads[kLineMaxBlock / 64];
+    double last[3 * (kLineMaxBlock / 64)];
+    double line[2];
+    int p;
+};
+
+// Walks `groups` groups of blockDim.x rays from position `first` on, but those with their bit set in `left`.  setup(i, r) prepares the ray at position i
+// (false: it contributes nothing; r.p, r.U0 and r.dU stay valid if it has a line); walk(r, sheet, on), called by
+// whole waves, projects this thread's ray if on (sheet nullptr: by gathers; a ray without planes is never on);
+// end(i0, count) follows every group.  plane_mem: LDS words for the planes' records, free to use in walk and end.
+template <class Setup, class Walk, class End>
+__device__ __forceinline__ void line_groups(const GeomK& g, __amdgpu_buffer_rsrc_t ib, float* mem, float* plane_mem, int min_run, int64_t first,
+                            int groups, unsigned left, int64_t n, LineShared& sh, Setup setup, Walk walk, End end) {
+    const int T = blockDim.x, tid = threadIdx.x, zs = line_stride(g);
+    float* const sheet = mem + 1;  // [-1] and the entry past the end: guards
+    LinePlane* const planes = reinterpret_cast<LinePlane*>(plane_mem);
+    for (int e = tid; e < line_planes(g) * 2; e += T) sheet[(e >> 1) * zs + (e & 1 ? zs - 1 : 0)] = 0.0f;
+    if (tid < 2) mem[tid * (line_planes(g) * zs + 1)] = 0.0f;
+    int cur_p = -1;  // the sheet's line (block-uniform)
+    double cur_U = 0.0, cur_d = 0.0;
+    for (int grp = 0; grp < groups; ++grp) {
+        const int64_t i0 = first + (int64_t)grp * T;
+        if (i0 >= n) break;  // block-uniform
+        if (left >> grp & 1) continue;
+        RayK r;
+        r.p = -1;
+        r.U0 = r.dU = 0.0;
+        r.k_lo = 0, r.k_hi = -1;
+        const bool ok = setup(i0 + tid, r);
+        if (ok) line_trim(r);
+        else r.k_lo = 0, r.k_hi = -1;
+        const int lp = (r.p == 0 || r.p == 1) ? r.p : -1;
+        const int runs = line_runs(lp, r.U0, r.dU, sh.heads, sh.last);
+        bool done = r.k_lo > r.k_hi;
+        if (runs * kLineHeads <= T) {
+            for (int h = 0; h < T;) {  // block-uniform
+                const int e = line_next(sh.heads, h);
+                if (tid == h) {
+                    sh.p = lp;
+                    sh.line[0] = r.U0;
+                    sh.line[1] = r.dU;
+                }
+                __syncthreads();
+                const int p = sh.p;
+                const double U0 = sh.line[0], dU = sh.line[1];
+                const bool same = p >= 0 && p == cur_p && U0 == cur_U && dU == cur_d;
+                if (p >= 0 && !same && e - h >= min_run) {
+                    line_load(sheet, planes, ib, g, p, U0, dU);
+                    cur_p = p, cur_U = U0, cur_d = dU;
+                }
+                __syncthreads();
+                const bool on = !done && tid >= h && tid < e && p == cur_p && p >= 0 && U0 == cur_U && dU == cur_d;
+                if (__ballot(on)) walk(r, (const float*)sheet, on);
+                done |= on;
+                h = e;
+                if (h < T) __syncthreads();  // before the sheet or the run's line is written again
+            }
+        }
+        if (__ballot(!done)) walk(r, (const float*)nullptr, !done);
+        end(i0, (int)(n - i0 < T ? n - i0 : T));
+    }
+}
+
+}  // namespace ppmi

@@ -5,11 +5,14 @@
 
 #include "joseph.hpp"
 #include "launch.hpp"
+#include "line.hpp"
 #include "sheet.hpp"
 
 namespace ppmi {
 
 constexpr int kBlock = 256;
+constexpr int kLineBlock = 512;  // k_fwd_lines, k_fwd_left
+constexpr int kSinoBlock = 512;  // k_fwd_tof_sino_lines, at most
 
 // ------------------------------------------------------------- non-TOF ----
 
@@ -37,6 +40,72 @@ __global__ void __launch_bounds__(kBlock) k_fwd(RaySrc src,
         acc *= r.ell;
     }
     p[l] = acc;
+}
+
+// The groups of kLineBlock rays that k_fwd_lines leaves (line_group), half a group at a time; a workgroup looks at
+// `batch` halves.
+__global__ void __launch_bounds__(kBlock) k_fwd_left(RaySrc src, int64_t n, GeomK g, const float* __restrict__ img,
+                                                     float* __restrict__ p, int batch) {
+    static_assert(kLineBlock == 2 * kBlock, "halves of a group");
+    __shared__ bool left[kBlock];
+    const int64_t h0 = (int64_t)blockIdx.x * batch;
+    if ((int)threadIdx.x < batch) {
+        const int64_t i = (h0 + threadIdx.x) / 2 * kLineBlock;
+        left[threadIdx.x] = i < n && !line_group(src, i, n, kLineBlock);
+    }
+    __syncthreads();
+    const __amdgpu_buffer_rsrc_t ib = img_buffer(img, g);
+    for (int q = 0; q < batch; ++q) {
+        if (!left[q]) continue;  // block-uniform
+        const int64_t l = (h0 + q) * kBlock + threadIdx.x;
+        if (l >= n) continue;
+        RayK r;
+        float acc = 0.0f;
+        if (ray_setup(src, l, g, r)) {
+            for (int k = r.k_lo; k <= r.k_hi; ++k) acc += stencil_gather(ib, r, stencil_at(r, k));
+            acc *= r.ell;
+        }
+        p[l] = acc;
+    }
+}
+
+// The rays in list order, through line sheets where many rays share a line (line.hpp).
+__global__ void __launch_bounds__(kLineBlock) k_fwd_lines(RaySrc src, int64_t n, GeomK g, const float* __restrict__ img,
+                                                             float* __restrict__ p, int min_run, int groups) {
+    extern __shared__ float sheet[];
+    __shared__ LineShared sh;
+    const __amdgpu_buffer_rsrc_t ib = img_buffer(img, g);
+    const int zs = line_stride(g);
+    // the groups whose runs are too short are left to k_fwd_left
+    __shared__ unsigned left;
+    if (threadIdx.x == 0) left = 0;
+    __syncthreads();
+    const int64_t first = (int64_t)blockIdx.x * groups * blockDim.x;
+    if ((int)threadIdx.x < groups) {
+        const int64_t i0 = first + (int64_t)threadIdx.x * blockDim.x;
+        if (i0 < n && !line_group(src, i0, n, blockDim.x)) atomicOr(&left, 1u << threadIdx.x);
+    }
+    __syncthreads();
+    float acc = 0.0f;
+    line_groups(
+        g, ib, sheet, sheet + line_words(g), min_run, first, groups, left, n, sh,
+        [&](int64_t i, RayK& r) {
+            acc = 0.0f;
+            return i < n && ray_setup(src, i, g, r);
+        },
+        [&](const RayK& r, const float* sheet, bool on) {
+            if (!on) return;
+            if (sheet) {
+                line_walk<true>(sheet, zs, r, [&](float v, int) { acc += v; },
+                                [&](const float (&v)[4]) { acc += (v[0] + v[1]) + (v[2] + v[3]); });
+            } else {
+                for (int k = r.k_lo; k <= r.k_hi; ++k) acc += stencil_gather(ib, r, stencil_at(r, k));
+            }
+            acc *= r.ell;
+        },
+        [&](int64_t i0, int cnt) {
+            if ((int)threadIdx.x < cnt) p[i0 + threadIdx.x] = acc;
+        });
 }
 
 // ------------------------------------------------------- TOF listmode ----
@@ -225,6 +294,193 @@ __global__ void k_fwd_tof_sino(RaySrc src, int64_t n, GeomK g,
     }
 }
 
+// A ray's row of TOF bins, filled in order (rising or falling): a bin's value waits in the thread's LDS slots until
+// its block of eight is complete, which then goes out as two 16-byte stores.  `next` and `dir` are the
+// wave's in the uniform walk, a lane's own otherwise.
+struct alignas(4) Float4u {
+    float v[4];
+};
+
+struct BinRow {
+    float* out;   // the ray's row of nb bins
+    float* slot;  // eight LDS floats, `step` apart
+    int step, nb;
+    __device__ __forceinline__ void emit(float v, int& next, int dir) {
+        const int s = next & 7;
+        slot[s * step] = v;
+        if (dir > 0 ? (s == 7 || next == nb - 1) : s == 0) {
+            const int b = next & ~7;
+            float x[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[i] = slot[i * step];
+            if (b + 8 <= nb) {
+                *reinterpret_cast<Float4u*>(out + b) = Float4u{{x[0], x[1], x[2], x[3]}};
+                *reinterpret_cast<Float4u*>(out + b + 4) = Float4u{{x[4], x[5], x[6], x[7]}};
+            } else {
+#pragma unroll
+                for (int i = 0; i < 7; ++i)
+                    if (b + i < nb) out[b + i] = x[i];
+            }
+        }
+        next += dir;
+    }
+    // bin b of the row (ignored outside it); the bins since the last one are 0
+    __device__ __forceinline__ void put(int b, float v, int& next, int dir) {
+        if ((unsigned)b >= (unsigned)nb) return;
+        while (next != b) emit(0.0f, next, dir);
+        emit(v, next, dir);
+    }
+    __device__ __forceinline__ void finish(int& next, int dir) {
+        while ((unsigned)next < (unsigned)nb) emit(0.0f, next, dir);
+    }
+};
+
+// TOF sinogram forward with one Gaussian for all rays: samples through line sheets, weights from the fitted
+// edge polynomials.  The 2 R + 1 bins a sample reaches are accumulated in registers; when the ray moves on to
+// the next bin, the one it leaves behind is complete and goes out through BinRow (whose slots leave the LDS
+// for two workgroups per CU beside their sheets).  The rays of a line move through the bins nearly together:
+// where they stay less than a bin apart, the wave keeps one window of 2 R + 2 bins and all its lanes
+// leave a bin in one step; with a window per lane, moving it took as many instructions as the samples.
+template <int R>
+__global__ void __launch_bounds__(kSinoBlock, 4) k_fwd_tof_sino_lines(RaySrc src, int64_t n, GeomK g, TofEdgeK t, int nb,
+                                                                   const float* __restrict__ img,
+                                                                   float* __restrict__ p, int min_run, int groups) {
+    extern __shared__ float line_mem[];
+    __shared__ LineShared sh;
+    float* const slots = line_mem + line_words(g);  // eight per thread (or the planes' records, between the walks)
+    const int zs = line_stride(g);
+    const __amdgpu_buffer_rsrc_t ib = img_buffer(img, g);
+    BinRow row{nullptr, slots + threadIdx.x, (int)blockDim.x, nb};
+    bool walked = false;
+    if constexpr (R <= 3) tof_edge_to_vgprs<R>(t);  // (more would not fit 128 registers)
+    line_groups(
+        g, ib, line_mem, slots, min_run, (int64_t)blockIdx.x * groups * blockDim.x, groups, 0u, n, sh,
+        [&](int64_t i, RayK& r) {
+            walked = false;
+            row.out = p + i * nb;
+            return i < n && ray_setup(src, i, g, r);
+        },
+        [&](const RayK& r, const float* sheet, bool on) __attribute__((always_inline)) {
+            const double B0 = fma(r.s0, t.inv_bw, t.B0), dB = r.ds * t.inv_bw;
+            const float ell = r.ell;
+            float w[2 * R + 1];
+            if (sheet) {
+                const int k0 = __builtin_amdgcn_readfirstlane(wave_min(on ? r.k_lo : INT_MAX));
+                const int k1 = __builtin_amdgcn_readfirstlane(wave_max(on ? r.k_hi : INT_MIN));
+                // the lanes' positions in bins at both ends (linear between): how far they lie apart there
+                const double Ba = fma((double)k0, dB, B0), Bb = fma((double)k1, dB, B0);
+                const int first = __ffsll((long long)__ballot(on)) - 1;
+                const double Ba0 = __shfl(Ba, first, 64), Bb0 = __shfl(Bb, first, 64);
+                const int dir = __builtin_amdgcn_readfirstlane(Bb0 > Ba0 ? 1 : -1);
+                const bool near = fabs(Ba - Ba0) < 0.49 && fabs(Bb - Bb0) < 0.49 && fabs(Ba0) < 4096.0 && fabs(Bb0) < 4096.0;
+                if (__ballot(on && !near) == 0ull) {
+                    if (!on) return;
+                    walked = true;
+                    const double dZ = r.dW + (double)zs, Z0 = r.W0 + 1.0;
+                    float acc[2 * R + 2];  // bins cur - R .. cur + R + 1
+#pragma unroll
+                    for (int i = 0; i <= 2 * R + 1; ++i) acc[i] = 0.0f;
+                    int next = dir > 0 ? 0 : nb - 1;
+                    // cur: the lowest bin a lane lies in (wave-uniform; the others lie in cur or cur + 1)
+                    int cur = __builtin_amdgcn_readfirstlane((int)rint(Ba0)) - dir;
+                    auto up = [&]() __attribute__((always_inline)) {
+                        row.put(cur - R, acc[0] * ell, next, 1);
+#pragma unroll
+                        for (int i = 0; i <= 2 * R; ++i) acc[i] = acc[i + 1];
+                        acc[2 * R + 1] = 0.0f;
+                        ++cur;
+                    };
+                    auto down = [&]() __attribute__((always_inline)) {
+                        row.put(cur + R + 1, acc[2 * R + 1] * ell, next, -1);
+#pragma unroll
+                        for (int i = 2 * R + 1; i > 0; --i) acc[i] = acc[i - 1];
+                        acc[0] = 0.0f;
+                        --cur;
+                    };
+                    double kd = (double)k0;
+                    for (int k = k0; k <= k1; ++k, kd += 1.0) {
+                        float v = 0.0f;
+                        if (k >= r.k_lo && k <= r.k_hi) {
+                            const double Z = fma(kd, dZ, Z0);
+                            const int i = (int)Z;
+                            const float a = sheet[i], b = sheet[i + 1];
+                            v = fmaf((float)__builtin_amdgcn_fract(Z), b - a, a);
+                        }
+                        if (__ballot(v != 0.0f) == 0ull) continue;
+                        const double B = fma(kd, dB, B0), fb = rint(B);
+                        const int q = (int)fb;
+                        tof_edge_weights<R>((float)(B - fb), t, w);
+                        if (__ballot(q != cur)) {
+                            if (dir > 0)
+                                while (__ballot(q <= cur) == 0ull) up();
+                            else
+                                while (__ballot(q < cur)) down();
+                            const bool hi = q != cur;
+                            acc[0] = fmaf(hi ? 0.0f : w[0], v, acc[0]);
+#pragma unroll
+                            for (int i = 1; i <= 2 * R; ++i) acc[i] = fmaf(hi ? w[i - 1] : w[i], v, acc[i]);
+                            acc[2 * R + 1] = fmaf(hi ? w[2 * R] : 0.0f, v, acc[2 * R + 1]);
+                        } else {
+#pragma unroll
+                            for (int i = 0; i <= 2 * R; ++i) acc[i] = fmaf(w[i], v, acc[i]);
+                        }
+                    }
+#pragma unroll 1
+                    for (int i = 0; i <= 2 * R + 1; ++i) {
+                        if (dir > 0) up();
+                        else down();
+                    }
+                    row.finish(next, dir);
+                    return;
+                }
+            }
+            if (!on) return;
+            walked = true;
+            float acc[2 * R + 1];
+#pragma unroll
+            for (int i = 0; i <= 2 * R; ++i) acc[i] = 0.0f;
+            const bool up = dB > 0.0;
+            const int dir = up ? 1 : -1;
+            int next = up ? 0 : nb - 1;
+            int cur = (int)rint(fma((double)r.k_lo, dB, B0));
+            // the bin the ray leaves behind goes out, the others move up
+            auto advance = [&]() __attribute__((always_inline)) {
+                row.put(up ? cur - R : cur + R, (up ? acc[0] : acc[2 * R]) * ell, next, dir);
+                float a[2 * R + 1];
+#pragma unroll
+                for (int i = 0; i <= 2 * R; ++i)
+                    a[i] = up ? (i < 2 * R ? acc[i + 1] : 0.0f) : (i > 0 ? acc[i - 1] : 0.0f);
+#pragma unroll
+                for (int i = 0; i <= 2 * R; ++i) acc[i] = a[i];
+                cur += dir;
+            };
+            auto sample = [&](float v, int k) __attribute__((always_inline)) {
+                if (__ballot(v != 0.0f) == 0ull) return;
+                const double B = fma((double)k, dB, B0), fb = rint(B);
+                const int q = (int)fb;
+                for (int i = 0; cur != q; ++i) {
+                    if (i > 2 * R) cur = q;  // further than the window reaches: it is empty by now
+                    else advance();
+                }
+                tof_edge_weights<R>((float)(B - fb), t, w);
+#pragma unroll
+                for (int i = 0; i <= 2 * R; ++i) acc[i] = fmaf(w[i], v, acc[i]);
+            };
+            if (sheet) {
+                line_walk<false>(sheet, zs, r, sample, [](const float (&)[4]) {});
+            } else {
+                for (int k = r.k_lo; k <= r.k_hi; ++k) sample(stencil_gather<false>(ib, r, stencil_at(r, k)), k);
+            }
+#pragma unroll 1
+            for (int i = 0; i <= 2 * R; ++i) advance();
+            row.finish(next, dir);
+        },
+        [&](int64_t, int cnt) {
+            if (!walked && (int)threadIdx.x < cnt)
+                for (int b = 0; b < nb; ++b) row.out[b] = 0.0f;
+        });
+}
+
 // ------------------------------------------------------- work counter ----
 //
 // Plane samples per ray whose 2x2 stencil has at least one voxel inside the
@@ -266,8 +522,46 @@ __global__ void __launch_bounds__(kBlock) k_count(RaySrc src,
 
 static unsigned grid_for(int64_t n, int block) { return (unsigned)((n + block - 1) / block); }
 
+static int device_cus() {
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) !=
+                                                 hipSuccess || cus <= 0)
+        cus = 256;
+    return cus;
+}
+
+// Groups of T rays per workgroup of a line kernel: about 4096 consecutive rays (a clinical sinogram's line has 2204),
+// unless that leaves CUs idle.
+static int line_groups_of(int64_t n, int T) {
+    const int64_t groups = n / ((int64_t)T * 8 * device_cus());
+    return (int)(groups < 1 ? 1 : groups > 4096 / T ? 4096 / T : groups);
+}
+
+// Shortest run that gets a sheet.  TOF: one that keeps nearly half a workgroup's waves busy (clinical grid, 157 rays a
+// line: 0.58 ms with a sheet for every run, 0.28 ms by gathers); non-TOF, whose groups have long runs but at
+// their ends: what the sheet's entries cost
+constexpr int kLineMinRun = 96, kLineMinRunTof = 224;
+constexpr int kLineMaxWords = 20 * 1024;  // largest sheet (two workgroups of a smaller one share a CU's LDS)
+// Fewest rays the non-TOF line kernel is launched for: below, the second launch and the look at the groups are felt
+// where the lines turn out short (561,600 rays of 39 a line: 62 us by one kernel, 79 by two)
+constexpr int64_t kLineRays = 4 << 20;
+
 hipError_t launch_fwd(const RaySrc& src, int64_t n, const GeomK& g, const float* img, float* p,
                       const int32_t* order, hipStream_t s) {
+    if (!order && n >= kLineRays && line_words(g) <= kLineMaxWords && line_plane_words(g) <= kLineMaxWords) {
+        constexpr int T = kLineBlock;
+        const size_t lds = (size_t)(line_words(g) + line_plane_words(g)) * sizeof(float);
+        const hipError_t e = hipFuncSetAttribute((const void*)k_fwd_lines, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 (int)lds);
+        if (e != hipSuccess) return e;
+        const int groups = line_groups_of(n, T);
+        const int64_t per = n / ((int64_t)kBlock * 64 * device_cus());
+        const int batch = (int)(per < 1 ? 1 : per > 64 ? 64 : per);
+        hipLaunchKernelGGL(k_fwd_left, dim3(grid_for(n, kBlock * batch)), dim3(kBlock), 0, s, src, n, g, img, p, batch);
+        hipLaunchKernelGGL(k_fwd_lines, dim3(grid_for(n, T * groups)), dim3(T), lds, s, src, n, g, img, p, kLineMinRun,
+                           groups);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_fwd, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, src, n, g, img, p, order);
     return hipGetLastError();
 }
@@ -282,10 +576,7 @@ static hipError_t launch_runs(const Mode& m, const RaySrc& src, int64_t n, const
                                        (int)lds);
     if (e != hipSuccess) return e;
     // enough workgroups for about 4 per CU (small subsets), at most kSheetGroups groups each
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) !=
-                                                 hipSuccess || cus <= 0)
-        cus = 256;
+    const int cus = device_cus();
     int64_t groups = (n + (int64_t)kSheetBlock * 4 * cus - 1) / ((int64_t)kSheetBlock * 4 * cus);
     groups = groups < 1 ? 1 : (groups > kSheetGroups ? kSheetGroups : groups);
     hipLaunchKernelGGL(k_back_runs<Mode>, dim3(grid_for(n, kSheetBlock * groups)), dim3(kSheetBlock), lds, s, m, src, n,
@@ -386,8 +677,43 @@ hipError_t launch_back_tof_lm_batch(const RaySrc& src, const int16_t* bins, int6
 
 static int sino_block(int nb) { return nb <= 64 ? 256 : 64; }  // LDS tile <= 64 KiB
 
-hipError_t launch_fwd_tof_sino(const RaySrc& src, int64_t n, const GeomK& g, const TofK& t,
+// Threads of a k_fwd_tof_sino_lines workgroup: as many as leave two workgroups room in a CU's LDS, fewer where n would
+// leave CUs idle; 0 if the grid's sheet does not fit
+static int sino_lines_block(const GeomK& g, int64_t n) {
+    const int words = (80 * 1024 - (int)sizeof(LineShared) - 64) / 4 - line_words(g);
+    if (words < 8 * 64 || words < line_plane_words(g)) return 0;
+    int rays = words / 8 / 64 * 64;
+    rays = rays > kSinoBlock ? kSinoBlock : rays;
+    while (rays > 64 && n < (int64_t)rays * 2 * device_cus()) rays = (rays / 2 + 63) / 64 * 64;
+    return rays;
+}
+
+template <int R>
+static hipError_t launch_sino_lines(const RaySrc& src, int64_t n, const GeomK& g, const TofEdgeK& t, int nb, int T,
+                                    const float* img, float* p, hipStream_t s) {
+    const int extra = 8 * T > line_plane_words(g) ? 8 * T : line_plane_words(g);
+    const size_t lds = (size_t)(line_words(g) + extra) * sizeof(float);
+    const hipError_t e = hipFuncSetAttribute((const void*)k_fwd_tof_sino_lines<R>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    const int groups = line_groups_of(n, T);
+    hipLaunchKernelGGL(k_fwd_tof_sino_lines<R>, dim3(grid_for(n, T * groups)), dim3(T), lds, s, src, n, g, t, nb, img, p,
+                       kLineMinRunTof, groups);
+    return hipGetLastError();
+}
+
+hipError_t launch_fwd_tof_sino(const RaySrc& src, int64_t n, const GeomK& g, const TofK& t, const TofEdgeK* te,
                                const float* img, float* p, hipStream_t s) {
+    const int T = te && te->R ? sino_lines_block(g, n) : 0;
+    if (T) {
+        switch (te->R) {
+            case 1: return launch_sino_lines<1>(src, n, g, *te, t.nb, T, img, p, s);
+            case 2: return launch_sino_lines<2>(src, n, g, *te, t.nb, T, img, p, s);
+            case 3: return launch_sino_lines<3>(src, n, g, *te, t.nb, T, img, p, s);
+            case 4: return launch_sino_lines<4>(src, n, g, *te, t.nb, T, img, p, s);
+            default: return launch_sino_lines<5>(src, n, g, *te, t.nb, T, img, p, s);
+        }
+    }
     const int blk = sino_block(t.nb);
     const size_t lds = (size_t)t.nb * blk * sizeof(float);
     hipLaunchKernelGGL((t.sig_ray || t.off_ray) ? k_fwd_tof_sino<true> : k_fwd_tof_sino<false>, dim3(grid_for(n, blk)),

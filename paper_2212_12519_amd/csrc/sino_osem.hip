@@ -67,7 +67,7 @@ hipError_t launch_tof_sino_osem_subset(const float* xs, const float* xe, const f
         for (int64_t c0 = lo; c0 < hi; c0 += work_lors) {
             const int64_t m = (hi - c0 < work_lors) ? (hi - c0) : work_lors;
             const RaySrc src{xs + 3 * c0, xe + 3 * c0, nullptr, 0};
-            hipError_t e = launch_fwd_tof_sino(src, m, g, t, x, work, s);
+            hipError_t e = launch_fwd_tof_sino(src, m, g, t, nullptr, x, work, s);
             if (e != hipSuccess) return e;
             hipLaunchKernelGGL(k_sino_ratio, dim3(stream_blocks(m * nb, cus)), dim3(kSinoBlock), 0, s, y + c0 * nb,
                                work, m * nb, bg);
