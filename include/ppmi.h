@@ -407,6 +407,18 @@ int64_t pp_osem_chunks(int64_t n_events, int32_t n_sub);
 int pp_lm_osem_subset_batched(const pp_frame_desc_t* d_slots, int32_t n_slots, const pp_image_t* geom,
                               const pp_tof_t* tof, void* stream);
 
+/* Bytes of device memory pp_lm_osem_frame_ws needs for a frame, 0 where pp_lm_osem_subset_batched serves it
+ * better (see pp_back_lm_workspace_bytes).  Host only. */
+size_t pp_lm_osem_frame_workspace_bytes(int64_t n_events, int32_t n_sub, const pp_image_t* geom, const pp_tof_t* tof);
+
+/* The accumulation of pp_lm_osem_subset_batched (Sec. 2.6) for one frame whose description `frame` lies in
+ * HOST memory (its pointers are device pointers): acc += A_j^T (1 / (A_j x + bg)) for subset j =
+ * frame->subset, by image tiles as pp_back_lm_ws, with a workspace of at least
+ * pp_lm_osem_frame_workspace_bytes bytes (16-byte aligned).  chunk_begin, steps_left and active are not used.
+ * A frame without usable pointers or counts is an error (PP_EINVAL_PTR, PP_EINVAL_N). */
+int pp_lm_osem_frame_ws(const pp_frame_desc_t* frame, const pp_image_t* geom, const pp_tof_t* tof, void* workspace,
+                        size_t workspace_bytes, void* stream);
+
 /* Multiplicative image update of every live slot, then acc <- 0, subset
  * advanced, steps_left decremented.  geom: the slots' common image grid.
  * res_fwhm: host array of 3 FWHM values in mm (per image axis) of the

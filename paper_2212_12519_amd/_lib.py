@@ -167,6 +167,7 @@ def load():
         "pp_gather_events": [P, P, P, P, I64, P, P, P, P],
         "pp_osem_init": [P, P, I64, P],
         "pp_lm_osem_subset_batched": [P, I32, G, T, P],
+        "pp_lm_osem_frame_ws": [ctypes.POINTER(COsemSlot), G, T, P, ctypes.c_size_t, P],
         "pp_osem_update_batched": [P, I32, G, P, P],
         "pp_gauss3d": [P, P, P, G, P, P],
         "pp_fill": [P, I64, ctypes.c_float, P],
@@ -191,6 +192,8 @@ def load():
         f.restype = INT
     lib.pp_lm_presort_workspace_bytes.argtypes = [I64]
     lib.pp_lm_presort_workspace_bytes.restype = ctypes.c_size_t
+    lib.pp_lm_osem_frame_workspace_bytes.argtypes = [I64, I32, G, T]
+    lib.pp_lm_osem_frame_workspace_bytes.restype = ctypes.c_size_t
     lib.pp_back_lm_workspace_bytes.argtypes = [I64, G, T]
     lib.pp_back_lm_workspace_bytes.restype = ctypes.c_size_t
     lib.pp_osem_chunks.argtypes = [I64, I32]

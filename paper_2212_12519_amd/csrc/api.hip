@@ -666,6 +666,37 @@ int pp_lm_osem_subset_batched(const pp_frame_desc_t* d_slots, int32_t n_slots, c
     return hip_status(launch_osem_accumulate(d_slots, n_slots, g, t, device_cus(), as_stream(stream)));
 }
 
+size_t pp_lm_osem_frame_workspace_bytes(int64_t n_events, int32_t n_sub, const pp_image_t* geom, const pp_tof_t* tof) {
+    if (n_events <= 0 || n_sub < 1) return 0;
+    return pp_back_lm_workspace_bytes((n_events + n_sub - 1) / n_sub, geom, tof);
+}
+
+int pp_lm_osem_frame_ws(const pp_frame_desc_t* frame, const pp_image_t* geom, const pp_tof_t* tof, void* workspace,
+                        size_t workspace_bytes, void* stream) {
+    GeomK g;
+    TofK t;
+    PP_TRY(make_geom(geom, g));
+    PP_TRY(make_tof(tof, t));
+    if (t.sig_ray || t.off_ray) return PP_EINVAL_TOF;
+    if (!frame) return PP_EINVAL_PTR;
+    const pp_frame_desc_t& f = *frame;
+    if (f.n_events < 0 || f.n_sub < 1 || f.subset < 0 || f.subset >= f.n_sub) return PP_EINVAL_N;
+    // the subset's range of the events (subset-major storage)
+    const int64_t base = f.n_events / f.n_sub, rem = f.n_events - base * f.n_sub, j = f.subset;
+    const int64_t n_j = base + (j < rem ? 1 : 0), off = j * base + (j < rem ? j : rem);
+    if (n_j == 0) return PP_OK;
+    const float* x = f.x_fwd ? f.x_fwd : f.x;
+    if (!x || !f.acc || !f.tof_bin || !workspace || (reinterpret_cast<uintptr_t>(workspace) & 15u) != 0)
+        return PP_EINVAL_PTR;
+    RaySrc src = coords(f.xstart, f.xend);
+    if (f.crystal_pair) PP_TRY(crystals(f.crystal_xyz, f.n_crystals, f.crystal_pair, n_j, src));
+    else if (!f.xstart || !f.xend) return PP_EINVAL_PTR;
+    const size_t need = tile_workspace_bytes(n_j, g, &t);
+    if (need == 0 || workspace_bytes < need) return PP_EINVAL_N;
+    return hip_status(launch_osem_tiles(src.from(off), f.tof_bin + off, n_j, g, t, x, f.bg, f.acc, workspace, device_cus(),
+                                        as_stream(stream)));
+}
+
 int pp_osem_update_batched(pp_frame_desc_t* d_slots, int32_t n_slots, const pp_image_t* geom, const float* res_fwhm,
                       void* stream) {
     GeomK g;

@@ -50,6 +50,9 @@ size_t tile_workspace_bytes(int64_t n, const GeomK& g, const TofK* t);
 hipError_t launch_back_tiles(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK* t,
                              float* imgs, int n_img, const float* p, const int32_t* order, void* ws, int cus,
                              hipStream_t s);
+// the same for one subset of a listmode OSEM frame (its events contiguous): acc += A^T (1 / (A x + bg))
+hipError_t launch_osem_tiles(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK& t,
+                             const float* x, float bg, float* acc, void* ws, int cus, hipStream_t s);
 hipError_t launch_poisson_nll(const float* p, float bg, const float* y, int64_t n, float* grad, double* partial,
                               int n_partial, hipStream_t s);
 size_t presort_workspace_bytes(int64_t n);

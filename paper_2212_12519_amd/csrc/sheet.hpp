@@ -215,6 +215,42 @@ struct ModeTofSino {
     }
 };
 
+// Per event: forward project through the frame's current image (setup), then scatter
+// ell / ybar times the TOF weight (sample) -- listmode OSEM.
+template <int Form>
+struct ModeOsem {
+    static constexpr bool kAux = false;
+    static constexpr bool kBatch = false;
+    const float* __restrict__ x;
+    const int16_t* __restrict__ bins;
+    float bg;
+    TofK t;
+    __device__ bool setup(int64_t l, const RaySrc& src, const GeomK& g, RayK& r, float& cv,
+                          int& /*aux*/) const {
+        const int b = bins[l];
+        if (b < 0 || b >= t.nb || !ray_setup(src, l, g, r)) return false;
+        if (!tof_window_rel(r, t.c0 + b * t.bw, t.lo, t.hi)) return false;
+        const __amdgpu_buffer_rsrc_t ib = img_buffer(x, g);
+        float fwd = 0.0f;
+        for (int k = r.k_lo; k <= r.k_hi; ++k) {
+            const float w = tof_weight_unscaled<Form, true>(fma((double)k, r.ds, r.s0), t, t.u_per_mm);
+            fwd += w * stencil_gather(ib, r, stencil_at(r, k));
+        }
+        const float ybar = r.ell * kTofScale<Form> * fwd + bg;
+        if (!(ybar > 0.0f)) return false;
+        cv = r.ell / ybar * kTofScale<Form>;
+        return true;
+    }
+    __device__ float sample(double x, float cv, int /*aux*/) const {
+        return tof_weight_unscaled<Form>(x, t, t.u_per_mm) * cv;
+    }
+    __device__ void to_vgprs() {
+        if constexpr (Form == kFormPoly) tof_poly_to_vgprs(t);
+    }
+    __device__ float mag(float cv, int /*aux*/) const { return fabsf(cv); }
+    __device__ float weight_bound(float* red) const { return tof_weight_bound<Form>(t, red); }
+};
+
 // The rectangle [k0, k1] x [z0, z1] (planes, z entries) of the sheet that the workgroup's lanes
 // added to since the last flush (each lane passes its own klo, khi, zlo, zhi; empty: k0 > k1 or
 // z0 > z1).  Every thread of the workgroup calls it; part[] takes 4 words; it synchronises once.

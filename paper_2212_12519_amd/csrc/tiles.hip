@@ -215,4 +215,14 @@ hipError_t launch_back_tiles(const RaySrc& src, const int16_t* bins, int64_t n, 
     return launch_tiles_lm<kFormErf, false>(src, bins, n, g, *t, imgs, n_img, p, order, ws, cus, s);
 }
 
+hipError_t launch_osem_tiles(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK& t,
+                             const float* x, float bg, float* acc, void* ws, int cus, hipStream_t s) {
+    const int form = tof_form(t);
+    if (form == kFormLut)
+        return launch_tiles(ModeOsem<kFormLut>{x, bins, bg, t}, src, n, g, &t, acc, 1, nullptr, ws, cus, s);
+    if (form == kFormPoly)
+        return launch_tiles(ModeOsem<kFormPoly>{x, bins, bg, t}, src, n, g, &t, acc, 1, nullptr, ws, cus, s);
+    return launch_tiles(ModeOsem<kFormErf>{x, bins, bg, t}, src, n, g, &t, acc, 1, nullptr, ws, cus, s);
+}
+
 }  // namespace ppmi

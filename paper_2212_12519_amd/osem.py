@@ -143,6 +143,30 @@ def osem_steps(table: SlotTable, geom, tof, n_steps=1, res_fwhm=None):
         check(lib.pp_osem_update_batched(ptr(table.dev), table.capacity, gc, fw, st))
 
 
+def _frame_steps(table: SlotTable, geom, tof, n_steps, res_fwhm):
+    """osem_steps for slot 0 of a table of one frame, whose host mirror describes it: the accumulation by image tiles
+    (pp_lm_osem_frame_ws) with a workspace from torch's allocator where the library prefers it and the memory is
+    there, else as osem_steps."""
+    g, t = as_geom(geom), as_tof(tof)
+    if t.per_ray:
+        raise ValueError("listmode OSEM takes one TOF kernel for every event (no per-ray parameters)")
+    lib, frame, gc, tc = load(), table.host[0], g.c(), t.c()
+    nbytes = lib.pp_lm_osem_frame_workspace_bytes(frame.n_events, frame.n_sub, gc, tc)
+    try:
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=table.dev.device) if nbytes else None
+    except torch.OutOfMemoryError:
+        ws = None
+    if ws is None:
+        osem_steps(table, g, t, n_steps, res_fwhm)
+        return
+    fw = None if res_fwhm is None else fwhm3(res_fwhm)
+    st = stream_of(table.dev)
+    for _ in range(n_steps):
+        check(lib.pp_lm_osem_frame_ws(ctypes.byref(frame), gc, tc, ptr(ws), nbytes, st))
+        check(lib.pp_osem_update_batched(ptr(table.dev), table.capacity, gc, fw, st))
+        table.advance_host(1)
+
+
 def capture_steps(table: SlotTable, geom, tof, n_steps=1, res_fwhm=None):
     """A HIP graph of n_steps subset updates over the table (replay serves any slot mix)."""
     graph = torch.cuda.CUDAGraph()
@@ -179,7 +203,7 @@ def lm_osem_crystals(crystal_xyz, pair, tof_bin, geom, tof, sens, n_iter, n_sub,
     table = SlotTable(1, pair.device)
     table.set_crystals(0, crystal_xyz, pr, tb, x, acc, sens, n_sub, n_iter * n_sub, bg, x_fwd, tmp)
     table.upload()
-    osem_steps(table, g, tof, n_iter * n_sub, res_fwhm)
+    _frame_steps(table, g, tof, n_iter * n_sub, res_fwhm)
     torch.cuda.current_stream(x.device).synchronize()
     del pr, tb
     return x
@@ -199,7 +223,7 @@ def lm_osem(xstart, xend, tof_bin, geom, tof, sens, n_iter, n_sub, bg=0.1, x0=No
     table = SlotTable(1, xstart.device)
     table.set(0, xs, xe, tb, x, acc, sens, n_sub, n_iter * n_sub, bg, x_fwd, tmp)
     table.upload()
-    osem_steps(table, g, tof, n_iter * n_sub, res_fwhm)
+    _frame_steps(table, g, tof, n_iter * n_sub, res_fwhm)
     torch.cuda.current_stream(x.device).synchronize()
     del xs, xe, tb
     return x

@@ -127,3 +127,38 @@ def test_values_far_apart(gpu):
     hit = oracle.back(xs[:1], xe[:1], o, h, dim, np.ones(1, np.float32)) != 0
     near = binary_dilation(hit, np.ones((3, 3, 3)))  # neighbours of weight 0 may take 0 * inf
     assert np.isfinite(bad[~near]).all() and not np.isfinite(bad[hit]).all()
+
+
+@pytest.mark.parametrize("sigma,table", [(24.8, False), (3.0, False), (24.8, True)])
+@pytest.mark.parametrize("n,n_sub", [(1, 1), (7, 9), (4001, 3)])
+def test_osem_frame_against_slots(gpu, sigma, table, n, n_sub):
+    """Every subset of a frame accumulated by tiles and by the fused kernel over the slot table: the float32 forward is
+    the same code; 1 / ybar and the sums differ by roundings (TOL)."""
+    from paper_2212_12519_amd import osem
+
+    dim, vox, o, h, xs, xe, bins, _ = _case("whole_slices", max(n, 10), 8)
+    dev = torch.device("cuda")
+    xs, xe, bins = (torch.from_numpy(a[-n:].copy()).to(dev) for a in (xs, xe, bins))
+    geom, T = gpu.ImageGeom(dim, vox), gpu.TofParams(28.0, sigma, 3.0, 29)
+    if table:
+        T = gpu.gaussian_tof_table(T, 0.05)
+    a, b, c = osem.prepare_frame(xs, xe, bins, geom, T, n_sub)
+    x = torch.rand(dim, device=dev) + 0.1
+    sens = torch.ones(dim, device=dev)
+    lib = gpu.load()
+    for j in range(n_sub):
+        acc = [torch.zeros(dim, device=dev) for _ in range(2)]
+        for q in range(2):
+            tab = osem.SlotTable(1, dev)
+            tab.set(0, a, b, c, x, acc[q], sens, n_sub, 1, 0.1)
+            tab.host[0].subset = j
+            tab.upload()
+            if q == 0:
+                osem.check(lib.pp_lm_osem_subset_batched(osem.ptr(tab.dev), 1, geom.c(), T.c(), osem.stream_of(x)))
+            else:
+                nb = lib.pp_lm_osem_frame_workspace_bytes(n, n_sub, geom.c(), T.c())
+                ws = torch.empty(nb, dtype=torch.uint8, device=dev)
+                osem.check(lib.pp_lm_osem_frame_ws(tab.host[0], geom.c(), T.c(), osem.ptr(ws), nb, osem.stream_of(x)))
+            torch.cuda.synchronize()
+        want, got = (t.cpu().numpy() for t in acc)
+        assert rel_l2(got, want) <= TOL, j
