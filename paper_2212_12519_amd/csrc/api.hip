@@ -360,7 +360,7 @@ int pp_back_tof_sino(const float* xstart, const float* xend, int64_t n, const pp
     PP_TRY(check_n_sino(n));
     if (n == 0) return PP_OK;
     if (!xstart || !xend || !img || !p) return PP_EINVAL_PTR;
-    return hip_status(launch_back_tof_sino(coords(xstart, xend), n, g, t, img, p, as_stream(stream)));
+    return hip_status(launch_back_tof_sino(coords(xstart, xend), n, g, t, &te, img, p, as_stream(stream)));
 }
 
 int pp_fwd_tof_lm(const float* xstart, const float* xend, const int16_t* tof_bin, int64_t n, const pp_image_t* geom,

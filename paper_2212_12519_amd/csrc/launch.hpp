@@ -28,7 +28,7 @@ hipError_t launch_back(const RaySrc& src, int64_t n, const GeomK& g, float* img,
 // te: the fitted edge polynomials, or nullptr (or no fit): the erf form
 hipError_t launch_fwd_tof_sino(const RaySrc& src, int64_t n, const GeomK& g, const TofK& t, const TofEdgeK* te,
                                const float* img, float* p, hipStream_t s);
-hipError_t launch_back_tof_sino(const RaySrc& src, int64_t n, const GeomK& g, const TofK& t,
+hipError_t launch_back_tof_sino(const RaySrc& src, int64_t n, const GeomK& g, const TofK& t, const TofEdgeK* te,
                                 float* img, const float* p, hipStream_t s);
 hipError_t launch_tof_gauss_table(float* lut, int n, double x0, double dx, double bw, double sigma, double n_sigmas,
                                   hipStream_t s);

@@ -16,25 +16,33 @@
 namespace ppmi {
 
 constexpr int kLineMaxBlock = 1024;
+constexpr int kLineBlock = 512;  // rays of a group of k_fwd_lines and k_back_lines
+// Shortest run that gets a sheet.  TOF forward: one that keeps nearly half a workgroup's waves busy (clinical grid, 157
+// rays a line: 0.58 ms with a sheet for every run, 0.28 ms by gathers); where the groups have long runs but at
+// their ends (line_group): what the sheet's entries cost
+constexpr int kLineMinRun = 96, kLineMinRunTof = 224;
 constexpr int kLineHeads = 32;  // a group with more runs than its rays / kLineHeads gathers them all
 
-// Whether the runs of a group of T rays are long enough for the group's waves to share sheets: by the transaxial
-// end points of three of its rays, half a group apart, two neighbours of which lie on one line.  (Much shorter
-// runs would be walked one after the other by a few of the waves.)
+// Whether the runs of a group of T rays are long enough for the group's waves to share sheets: the first or the last
+// 9/16 of the group lie on one line, by the transaxial end points of the first and last ray of either stretch.
+// (Much shorter runs would be walked one after the other by a few of the waves.  A group of a long list that
+// holds a line's end fails this with probability 1/8; with half a group asked, lists of 268 rays a line had
+// a few groups taken and took a tenth longer.)
 __device__ inline bool line_group(const RaySrc& src, int64_t i0, int64_t n, int T) {
-    const float *s[3], *e[3];
+    const int at[4] = {0, T * 9 / 16, T - 1 - T * 9 / 16, T - 1};
+    const float *s[4], *e[4];
     bool ok = true;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        const int64_t i = i0 + q * T / 2 - (q == 2);
+    for (int q = 0; q < 4; ++q) {
+        const int64_t i = i0 + at[q];
         ok &= src.ends(i < n ? i : n - 1, s[q], e[q]);
     }
     if (!ok) return false;
-    float2 a[3], b[3];
+    float2 a[4], b[4];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) a[q] = make_float2(s[q][0], s[q][1]), b[q] = make_float2(e[q][0], e[q][1]);
+    for (int q = 0; q < 4; ++q) a[q] = make_float2(s[q][0], s[q][1]), b[q] = make_float2(e[q][0], e[q][1]);
     auto same = [&](int q) { return a[q].x == a[q + 1].x && a[q].y == a[q + 1].y && b[q].x == b[q + 1].x && b[q].y == b[q + 1].y; };
-    return same(0) || same(1);
+    return same(0) || same(2);
 }
 
 // Rows of the sheet: planes 0 .. n_p - 1, nw + 2 entries each (slices -1 .. nw)

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "joseph.hpp"
+#include "back_lines.hpp"
 #include "launch.hpp"
 #include "line.hpp"
 #include "sheet.hpp"
@@ -11,7 +12,6 @@
 namespace ppmi {
 
 constexpr int kBlock = 256;
-constexpr int kLineBlock = 512;  // k_fwd_lines, k_fwd_left
 constexpr int kSinoBlock = 512;  // k_fwd_tof_sino_lines, at most
 
 // ------------------------------------------------------------- non-TOF ----
@@ -86,6 +86,8 @@ __global__ void __launch_bounds__(kLineBlock) k_fwd_lines(RaySrc src, int64_t n,
         if (i0 < n && !line_group(src, i0, n, blockDim.x)) atomicOr(&left, 1u << threadIdx.x);
     }
     __syncthreads();
+    const int64_t here = (n - first + blockDim.x - 1) / blockDim.x;  // groups with rays
+    if (__popc(left) >= (here < groups ? here : groups)) return;
     float acc = 0.0f;
     line_groups(
         g, ib, sheet, sheet + line_words(g), min_run, first, groups, left, n, sh,
@@ -530,21 +532,18 @@ static int device_cus() {
     return cus;
 }
 
-// Groups of T rays per workgroup of a line kernel: about 4096 consecutive rays (a clinical sinogram's line has 2204),
+// Groups of T rays per workgroup of a line kernel: about `rays` consecutive rays (a clinical sinogram's line has 2204),
 // unless that leaves CUs idle.
-static int line_groups_of(int64_t n, int T) {
+static int line_groups_of(int64_t n, int T, int rays) {
     const int64_t groups = n / ((int64_t)T * 8 * device_cus());
-    return (int)(groups < 1 ? 1 : groups > 4096 / T ? 4096 / T : groups);
+    return (int)(groups < 1 ? 1 : groups > rays / T ? rays / T : groups);
 }
 
-// Shortest run that gets a sheet.  TOF: one that keeps nearly half a workgroup's waves busy (clinical grid, 157 rays a
-// line: 0.58 ms with a sheet for every run, 0.28 ms by gathers); non-TOF, whose groups have long runs but at
-// their ends: what the sheet's entries cost
-constexpr int kLineMinRun = 96, kLineMinRunTof = 224;
 constexpr int kLineMaxWords = 20 * 1024;  // largest sheet (two workgroups of a smaller one share a CU's LDS)
 // Fewest rays the non-TOF line kernel is launched for: below, the second launch and the look at the groups are felt
 // where the lines turn out short (561,600 rays of 39 a line: 62 us by one kernel, 79 by two)
-constexpr int64_t kLineRays = 4 << 20;
+constexpr int64_t kLineRays = 11 << 19;
+constexpr int64_t kLineRaysTof = 1 << 20;  // TOF back projection
 
 hipError_t launch_fwd(const RaySrc& src, int64_t n, const GeomK& g, const float* img, float* p,
                       const int32_t* order, hipStream_t s) {
@@ -554,7 +553,7 @@ hipError_t launch_fwd(const RaySrc& src, int64_t n, const GeomK& g, const float*
         const hipError_t e = hipFuncSetAttribute((const void*)k_fwd_lines, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  (int)lds);
         if (e != hipSuccess) return e;
-        const int groups = line_groups_of(n, T);
+        const int groups = line_groups_of(n, T, 16384);
         const int64_t per = n / ((int64_t)kBlock * 64 * device_cus());
         const int batch = (int)(per < 1 ? 1 : per > 64 ? 64 : per);
         hipLaunchKernelGGL(k_fwd_left, dim3(grid_for(n, kBlock * batch)), dim3(kBlock), 0, s, src, n, g, img, p, batch);
@@ -566,27 +565,56 @@ hipError_t launch_fwd(const RaySrc& src, int64_t n, const GeomK& g, const float*
     return hipGetLastError();
 }
 
-// Back projections of ray lists go through the run/sheet kernel (sheet.hpp).
-template <class Mode>
+// Back projections of ray lists go through the run/sheet kernel (sheet.hpp); Left: only what k_back_lines leaves of a
+// list without an order.
+template <bool Left = false, class Mode>
 static hipError_t launch_runs(const Mode& m, const RaySrc& src, int64_t n, const GeomK& g, float* img,
                               const int32_t* order, hipStream_t s, int n_img = 1, int64_t img_stride = 0) {
     const int nw = (g.n[2] <= kSheetMaxW) ? g.n[2] : 0;
     const size_t lds = SheetLayout::bytes(nw, g);
-    hipError_t e = hipFuncSetAttribute((const void*)k_back_runs<Mode>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)lds);
+    const void* k;
+    if constexpr (Left) k = (const void*)k_back_runs_left<Mode>;
+    else k = (const void*)k_back_runs<Mode>;
+    hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     // enough workgroups for about 4 per CU (small subsets), at most kSheetGroups groups each
     const int cus = device_cus();
     int64_t groups = (n + (int64_t)kSheetBlock * 4 * cus - 1) / ((int64_t)kSheetBlock * 4 * cus);
     groups = groups < 1 ? 1 : (groups > kSheetGroups ? kSheetGroups : groups);
-    hipLaunchKernelGGL(k_back_runs<Mode>, dim3(grid_for(n, kSheetBlock * groups)), dim3(kSheetBlock), lds, s, m, src, n,
-                       g, img, order, nw, (int)groups, n_img, img_stride);
+    const dim3 grid(grid_for(n, kSheetBlock * groups));
+    if constexpr (Left)
+        hipLaunchKernelGGL(k_back_runs_left<Mode>, grid, dim3(kSheetBlock), lds, s, m, src, n, g, img, nw, (int)groups);
+    else
+        hipLaunchKernelGGL(k_back_runs<Mode>, grid, dim3(kSheetBlock), lds, s, m, src, n, g, img, order, nw, (int)groups,
+                           n_img, img_stride);
     return hipGetLastError();
+}
+
+// The groups of rays with long runs by k_back_lines, the others by the run/sheet kernel
+template <class LineMode, class Mode>
+static hipError_t launch_back_lines(const LineMode& lm, const Mode& m, const RaySrc& src, int64_t n, const GeomK& g,
+                                    float* img, hipStream_t s) {
+    const size_t lds = (size_t)(line_words(g) + line_plane_words(g)) * sizeof(float);
+    hipError_t e = hipFuncSetAttribute((const void*)k_back_lines<LineMode>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)lds);
+    if (e != hipSuccess) return e;
+    const int groups = line_groups_of(n, kLineBlock, 16384);
+    hipLaunchKernelGGL(k_back_lines<LineMode>, dim3(grid_for(n, kLineBlock * groups)), dim3(kLineBlock), lds, s, lm, src, n,
+                       g, img, groups);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_runs<true>(m, src, n, g, img, nullptr, s);
+}
+
+static bool back_lines_fit(const GeomK& g) {
+    return line_words(g) <= kLineMaxWords && line_plane_words(g) <= kLineMaxWords;
 }
 
 hipError_t launch_back(const RaySrc& src, int64_t n, const GeomK& g, float* img, const float* p,
                        const int32_t* order, hipStream_t s) {
     ModeNonTof m{p};
+    if (!order && n >= kLineRays && back_lines_fit(g))
+        return launch_back_lines(LineBackNonTof{p}, m, src, n, g, img, s);
     return launch_runs(m, src, n, g, img, order, s);
 }
 
@@ -696,7 +724,7 @@ static hipError_t launch_sino_lines(const RaySrc& src, int64_t n, const GeomK& g
     const hipError_t e = hipFuncSetAttribute((const void*)k_fwd_tof_sino_lines<R>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    const int groups = line_groups_of(n, T);
+    const int groups = line_groups_of(n, T, 16384);
     hipLaunchKernelGGL(k_fwd_tof_sino_lines<R>, dim3(grid_for(n, T * groups)), dim3(T), lds, s, src, n, g, t, nb, img, p,
                        kLineMinRunTof, groups);
     return hipGetLastError();
@@ -721,8 +749,18 @@ hipError_t launch_fwd_tof_sino(const RaySrc& src, int64_t n, const GeomK& g, con
     return hipGetLastError();
 }
 
-hipError_t launch_back_tof_sino(const RaySrc& src, int64_t n, const GeomK& g, const TofK& t,
+hipError_t launch_back_tof_sino(const RaySrc& src, int64_t n, const GeomK& g, const TofK& t, const TofEdgeK* te,
                                 float* img, const float* p, hipStream_t s) {
+    if (te && te->R && n >= kLineRaysTof && back_lines_fit(g)) {
+        const ModeTofSino<false> m{p, t};
+        switch (te->R) {
+            case 1: return launch_back_lines(LineBackTofSino<1>{p, *te, t.nb}, m, src, n, g, img, s);
+            case 2: return launch_back_lines(LineBackTofSino<2>{p, *te, t.nb}, m, src, n, g, img, s);
+            case 3: return launch_back_lines(LineBackTofSino<3>{p, *te, t.nb}, m, src, n, g, img, s);
+            case 4: return launch_back_lines(LineBackTofSino<4>{p, *te, t.nb}, m, src, n, g, img, s);
+            default: return launch_back_lines(LineBackTofSino<5>{p, *te, t.nb}, m, src, n, g, img, s);
+        }
+    }
     // the run/sheet kernel carries ray indices in 32 bits: the C ABI takes n < 2^31
     if (t.sig_ray || t.off_ray) {
         if (t.lut) return launch_runs(ModeTofSino<true, true>{p, t}, src, n, g, img, nullptr, s);

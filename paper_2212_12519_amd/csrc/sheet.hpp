@@ -29,6 +29,7 @@
 #include <type_traits>
 
 #include "joseph.hpp"
+#include "line.hpp"
 
 namespace ppmi {
 
@@ -728,6 +729,29 @@ __global__ void __launch_bounds__(kSheetBlock) k_back_runs(Mode m, RaySrc src, i
     extern __shared__ double smem[];
     const int64_t chunk0 = (int64_t)blockIdx.x * groups * kSheetBlock;
     back_runs_chunk(m, src, n, g, img, order, nw_lds, groups, chunk0, smem, n_img, img_stride);
+}
+
+// The groups of kLineBlock rays that k_back_lines leaves (line_group), stretch by stretch of a workgroup's chunk
+template <class Mode>
+__global__ void __launch_bounds__(kSheetBlock) k_back_runs_left(Mode m, RaySrc src, int64_t n, GeomK g,
+                                                               float* __restrict__ img, int nw_lds, int groups) {
+    extern __shared__ double smem[];
+    const int64_t chunk0 = (int64_t)blockIdx.x * groups * kSheetBlock;
+    unsigned* const word = reinterpret_cast<unsigned*>(smem);
+    if (threadIdx.x == 0) *word = 0;
+    __syncthreads();
+    if ((int)threadIdx.x < groups) {  // bit q: the q-th 256 rays of the chunk
+        const int64_t i = chunk0 + (int64_t)threadIdx.x * kSheetBlock;
+        if (i < n && !line_group(src, i / kLineBlock * kLineBlock, n, kLineBlock)) atomicOr(word, 1u << threadIdx.x);
+    }
+    __syncthreads();
+    unsigned left = __builtin_amdgcn_readfirstlane(*word);
+    __syncthreads();
+    while (left) {
+        const int q = __ffs((int)left) - 1, len = __ffs((int)~(left >> q)) - 1;
+        back_runs_chunk(m, src, n, g, img, nullptr, nw_lds, len, chunk0 + (int64_t)q * kSheetBlock, smem);
+        left &= ~(((1u << len) - 1u) << q);
+    }
 }
 
 }  // namespace ppmi

@@ -73,7 +73,7 @@ hipError_t launch_tof_sino_osem_subset(const float* xs, const float* xe, const f
                                work, m * nb, bg);
             e = hipGetLastError();
             if (e != hipSuccess) return e;
-            e = launch_back_tof_sino(src, m, g, t, acc_s, work, s);
+            e = launch_back_tof_sino(src, m, g, t, nullptr, acc_s, work, s);
             if (e != hipSuccess) return e;
         }
     }
@@ -89,7 +89,7 @@ hipError_t launch_tof_sino_sensitivity(const float* xs, const float* xe, int64_t
     if (e != hipSuccess) return e;
     for (int64_t c0 = 0; c0 < n; c0 += work_lors) {
         const int64_t m = (n - c0 < work_lors) ? (n - c0) : work_lors;
-        e = launch_back_tof_sino(RaySrc{xs + 3 * c0, xe + 3 * c0, nullptr, 0}, m, g, t, sens, work, s);
+        e = launch_back_tof_sino(RaySrc{xs + 3 * c0, xe + 3 * c0, nullptr, 0}, m, g, t, nullptr, sens, work, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -1,20 +1,21 @@
-"""The forward projections of ray lists through line sheets (runs of rays on one transaxial line) against the FP64
-oracle: run lengths around the wave and workgroup sizes and the shortest run that gets a sheet, single rays and rays
+"""The projections of ray lists through line sheets (runs of rays on one transaxial line) against the FP64 oracle: run lengths around the wave and workgroup sizes and the shortest run that gets a sheet, single rays and rays
 along axis 2 between them, both directions of a ray, odd grids, bin counts around the blocks of eight that a row is
 written in, and TOF kernels with one to five bin edges on a side, with and without a fit.
 
 Tolerance: a projection sums up to some 200 samples of a dozen float32 roundings each, mostly of one sign; the TOF
-weights are within 3.4e-7 of a largest weight of 0.4 to 1: 5e-6 in relative L2."""
+weights are within 3.4e-7 of a largest weight of 0.4 to 1: 5e-6 in relative L2.  A back projection's sheets keep at
+least 8 bits of every value and carry the remainders: 1e-4, the bar of the other back projections."""
 import numpy as np
 import pytest
 import torch
+from scipy.ndimage import binary_dilation
 
 import oracle
 from helpers import f32, random_rays, rel_l2, tofd
 
 pytestmark = pytest.mark.gpu
 
-TOL = 5e-6
+TOL, BACK_TOL = 5e-6, 1e-4
 GRIDS = {"flat": ((40, 37, 1), (5.0, 5.5, 9.0)), "odd": ((61, 75, 33), (3.1, 2.7, 2.5)), "tall": ((30, 30, 130), (6.0, 6.0, 1.2))}
 
 
@@ -85,3 +86,55 @@ def test_tof_grids(gpu, name):
     got = gpu.fwd_tof_sino(torch.from_numpy(xs).to(dev), torch.from_numpy(xe).to(dev), gpu.ImageGeom(dim, vox),
                            gpu.TofParams(28.0, 24.8, 3.0, 29), torch.from_numpy(img).to(dev)).cpu().numpy()
     assert rel_l2(got, oracle.fwd_tof_sino(xs, xe, o, h, dim, t, img)) <= TOL
+
+
+def _large(name, n, seed):
+    """At least n rays: long runs, with short ones and strays among them, and a stretch of short runs only."""
+    runs = RUNS["long"] * max(1, n // 7000) + RUNS["edges"] * 60 + RUNS["short"] * 200
+    dim, vox, o, h, xs, xe, img = _rays(name, runs, seed)
+    assert xs.shape[0] >= n
+    rng = np.random.default_rng(seed)
+    y = rng.normal(1.0, 0.6, xs.shape[0]) * 10.0 ** rng.integers(-2, 3, xs.shape[0])
+    y[rng.random(xs.shape[0]) < 0.1] = 0.0
+    return dim, vox, o, h, xs, xe, img, y.astype(np.float32)
+
+
+@pytest.mark.parametrize("name", ["flat", "odd"])
+def test_large_lists(gpu, name):
+    """Lists long enough for the non-TOF line kernels, which small ones do not reach."""
+    dim, vox, o, h, xs, xe, img, y = _large(name, 4_200_000, 6)
+    dev = torch.device("cuda")
+    t = lambda a: torch.from_numpy(a).to(dev)  # noqa: E731
+    G = gpu.ImageGeom(dim, vox)
+    got = gpu.fwd(t(xs), t(xe), G, t(img)).cpu().numpy()
+    assert rel_l2(got, oracle.fwd(xs, xe, o, h, dim, img)) <= TOL
+    got = gpu.back(t(xs), t(xe), G, t(y)).cpu().numpy()
+    assert rel_l2(got, oracle.back(xs, xe, o, h, dim, y)) <= BACK_TOL
+
+
+@pytest.mark.parametrize("tof", [(90.0, 24.8, 3.0, 5), (40.0, 24.8, 3.0, 8), (28.0, 24.8, 3.0, 13), (20.0, 24.8, 3.0, 9),
+                                 (15.0, 24.8, 3.0, 9)], ids=lambda t: str(t[0]))
+def test_large_tof_back(gpu, tof):
+    dim, vox, o, h, xs, xe, _, y = _large("flat", 1_060_000, 7)
+    dev = torch.device("cuda")
+    t = lambda a: torch.from_numpy(a).to(dev)  # noqa: E731
+    rng = np.random.default_rng(8)
+    y = (y[:, None] * rng.uniform(-0.2, 1.0, (y.size, tof[3]))).astype(np.float32)
+    y[rng.random(y.shape) < 0.3] = 0.0
+    T = gpu.TofParams(*tof, center_offset=-4.0)
+    got = gpu.back_tof_sino(t(xs), t(xe), gpu.ImageGeom(dim, vox), T, t(y)).cpu().numpy()
+    want = oracle.back_tof_sino(xs, xe, o, h, dim, tofd(*tof, center_offset=-4.0), y)
+    assert rel_l2(got, want) <= BACK_TOL
+
+
+def test_large_back_values_not_finite(gpu):
+    """A ray with an infinite value reaches its own voxels only."""
+    dim, vox, o, h, xs, xe, _, y = _large("flat", 4_200_000, 9)
+    dev = torch.device("cuda")
+    t = lambda a: torch.from_numpy(a).to(dev)  # noqa: E731
+    at = 100_000
+    y[at] = np.inf
+    got = gpu.back(t(xs), t(xe), gpu.ImageGeom(dim, vox), t(y)).cpu().numpy()
+    hit = oracle.back(xs[at:at + 1], xe[at:at + 1], o, h, dim, np.ones(1, np.float32)) != 0
+    near = binary_dilation(hit, np.ones((3, 3, 3)))
+    assert np.isfinite(got[~near]).all()
