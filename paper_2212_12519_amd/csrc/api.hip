@@ -97,7 +97,7 @@ float tof_poly_host(float x, const TofK& t) {
 // weight everywhere (checked on a grid 1/4096 of the support apart, up to 2% past its end);
 // otherwise the kernels use the erf form.
 void fit_tof_poly(TofK& t, double sig, double ns, double bw) {
-    t.poly = 0;
+    t = TofK{};
     const double hbw = 0.5 * bw, trunc = ns * sig, inv_s2 = 1.0 / (std::sqrt(2.0) * sig);
     const double k1 = std::fabs(trunc - hbw), k2 = trunc + hbw;
     if (!(k1 > 1e-3 * k2) || !(k2 - k1 > 1e-3 * k2)) return;  // a piece too short to fit
@@ -137,17 +137,14 @@ float tof_edge_host(float g, int m, bool upper, const TofEdgeK& e) {
 // Fits the edge polynomials of the sinogram kernels (TofEdgeK), one Gaussian for all rays.  Kept (R > 0) if the
 // float32 evaluation stays within 1.5e-7 of the exact Phi at every edge (checked at 257 offsets per edge): a
 // bin's weight, a difference of two, then is as near as the erf form's (3.4e-7).
-void fit_tof_edges(const TofK& t, double sig, double ns, double bw, TofEdgeK& e) {
-    e.R = 0;
-    if (t.lut || t.sig_ray || t.off_ray) return;
+void fit_tof_edges(double sig, double ns, double bw, TofEdgeK& e) {
+    e = TofEdgeK{};
     const double X = ns * sig / bw, k = bw / (std::sqrt(2.0) * sig);
     if (!(X > 0.0 && X <= (double)kEdgeMaxR)) return;
     const int R = std::max((int)std::ceil(X), 1);
     static_assert(kEdgeDegree == 7, "tof_edge_weights is written for degree 7");
     auto phi = [&](double x) { return 0.5 * std::erf(k * std::fmin(std::fmax(x, -X), X)); };
     e.R = R;
-    e.inv_bw = 1.0 / bw;
-    e.B0 = -t.c0 / bw;
     e.sat = (float)phi(X);
     e.t_max = (float)(X - (R - 0.5));
     for (int m = 0; m < R; ++m) {
@@ -163,6 +160,28 @@ void fit_tof_edges(const TofK& t, double sig, double ns, double bw, TofEdgeK& e)
             err = std::fmax(err, std::fabs(tof_edge_host(g, m, true, e) - phi(m + 0.5 - (double)g)));
         }
     if (!(err <= 1.5e-7)) e.R = 0;
+}
+
+// The fits of the last few TOF kernels a thread used, by their parameters: a fit and its check evaluate some eight
+// thousand erf, 100 us on the host, more than a small projection takes on the GPU.
+struct TofFits {
+    double sig = 0.0, ns = 0.0, bw = 0.0;
+    bool poly_set = false, edges_set = false;
+    TofK poly;
+    TofEdgeK edges;
+};
+constexpr int kTofFits = 4;
+thread_local TofFits g_fits[kTofFits];
+thread_local int g_fit_next = 0;
+
+TofFits& tof_fits(double sig, double ns, double bw) {
+    for (TofFits& f : g_fits)
+        if ((f.poly_set || f.edges_set) && f.sig == sig && f.ns == ns && f.bw == bw) return f;
+    TofFits& f = g_fits[g_fit_next];
+    g_fit_next = (g_fit_next + 1) % kTofFits;
+    f.sig = sig, f.ns = ns, f.bw = bw;
+    f.poly_set = f.edges_set = false;
+    return f;
 }
 
 int make_tof(const pp_tof_t* ti, TofK& t, TofEdgeK* edges = nullptr) {
@@ -218,12 +237,22 @@ int make_tof(const pp_tof_t* ti, TofK& t, TofEdgeK* edges = nullptr) {
     t.lut = nullptr;
     t.lut_n = 0;
     t.lut_inv_dx = 0.0f;
+    TofFits& fits = tof_fits(sig, ns, bw);
     if (edges) {  // the sinogram kernels
         t.poly = 0;
-        fit_tof_edges(t, sig, ns, bw, *edges);
-    } else {
-        fit_tof_poly(t, sig, ns, bw);
+        if (!fits.edges_set) fit_tof_edges(sig, ns, bw, fits.edges), fits.edges_set = true;
+        *edges = fits.edges;
+        edges->inv_bw = t.inv_bw;
+        edges->B0 = -t.c0 / bw;
+        if (t.sig_ray || t.off_ray) edges->R = 0;  // one Gaussian for all rays only
+        return PP_OK;
     }
+    if (!fits.poly_set) fit_tof_poly(fits.poly, sig, ns, bw), fits.poly_set = true;
+    const TofK& f = fits.poly;
+    t.poly = f.poly;
+    t.pk1 = f.pk1, t.pk2 = f.pk2, t.pq1 = f.pq1, t.pa2 = f.pa2, t.pb2 = f.pb2;
+    std::copy(f.pc, f.pc + kPolyCentral + 1, t.pc);
+    std::copy(f.pt, f.pt + kPolyTail + 1, t.pt);
     return PP_OK;
 }
 
