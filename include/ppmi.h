@@ -211,11 +211,12 @@ int pp_back_tof_lm_batch(const float* xstart, const float* xend, const int16_t* 
 
 /* Bytes of device memory pp_back_lm_ws needs for n events on this grid (tof NULL: non-TOF), 0 where
  * the call is better served by pp_back, pp_back_tof_lm or their variants (many events per transaxial
- * line, or a grid the tiles do not suit; invalid arguments also give 0).  Host only. */
-size_t pp_back_lm_workspace_bytes(int64_t n_events, const pp_image_t* geom, const pp_tof_t* tof);
+ * line, or a grid the tiles do not suit; invalid arguments also give 0).  listmode 0: the rays are a
+ * sinogram's or another list of whole lines.  Host only. */
+size_t pp_back_lm_workspace_bytes(int64_t n_events, const pp_image_t* geom, const pp_tof_t* tof, int32_t listmode);
 
 /* The listmode back projections (Sec. 2.2) with a caller workspace (16-byte aligned, at least
- * pp_back_lm_workspace_bytes(n_events, geom, tof) bytes, else PP_EINVAL_N): the events' planes are
+ * pp_back_lm_workspace_bytes(n_events, geom, tof, ...) bytes, else PP_EINVAL_N): the events' planes are
  * collected per image tile and added up in LDS, so that the events need no order and sparse lines
  * cost no more than dense ones.  Same results as pp_back (tof_bin NULL, tof unused),
  * pp_back_tof_lm, pp_back_tof_lm_batch (n_img images and value arrays; n_img <= 1 without TOF) or, with

@@ -127,6 +127,7 @@ static int pieces_bound(const GeomK& g, const TileGeom& tg, const TofK* t) {
 // limits lie a little below the crossings (serving grid 128 x 128 x 64: 13 M and 8 M).
 constexpr int64_t kTileEventsTof = 10'000'000;
 constexpr int64_t kTileEventsNonTof = 7'000'000;
+constexpr int64_t kTileRaysList = 5'700'000;
 
 static size_t up256(size_t b) { return (b + 255) & ~size_t(255); }
 
@@ -148,12 +149,24 @@ static size_t tile_layout(int64_t events, int tiles, int bound, char* base, Tile
     return at;
 }
 
-// 0: the call is better served by the run/sheet kernel, or the grid does not suit the tiles
-size_t tile_workspace_bytes(int64_t n, const GeomK& g, const TofK* t) {
+constexpr int64_t kTileEventsMost = 40'000'000;
+
+// 0: a grid the tiles do not suit, or more events than their counts (32 bits) or 16 GB of workspace hold
+size_t tile_bytes(int64_t n, const GeomK& g, const TofK* t) {
     TileGeom tg;
-    if (n <= 0 || n > (t ? kTileEventsTof : kTileEventsNonTof) || !tile_geom(g, tg)) return 0;
+    if (n <= 0 || n > kTileEventsMost || !tile_geom(g, tg)) return 0;
     TileWork w;
-    return tile_layout(n, tg.count(), pieces_bound(g, tg, t), nullptr, w);
+    const size_t bytes = tile_layout(n, tg.count(), pieces_bound(g, tg, t), nullptr, w);
+    return w.capacity <= INT32_MAX && bytes <= (size_t(16) << 30) ? bytes : 0;
+}
+
+// Grids of more slices than a sheet holds have no other way than float atomics (12 M presorted TOF events, 160
+// slices: 28 ms), so the tiles take all they can there, of a ray list what is left below the line kernels' size.
+size_t tile_workspace_bytes(int64_t n, const GeomK& g, const TofK* t, bool listmode) {
+    const bool sheets = g.n[2] <= kSheetMaxW;
+    const int64_t most = !sheets ? (listmode ? kTileEventsMost : kTileRaysList) : !listmode ? 0
+                         : t ? kTileEventsTof : kTileEventsNonTof;
+    return n <= most ? tile_bytes(n, g, t) : 0;
 }
 
 template <class Mode>

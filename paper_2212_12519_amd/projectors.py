@@ -14,11 +14,11 @@ from ._lib import (TofParams, _bins, _crystal_events, _dev, _img, _order, _rays,
                    stream_of)
 
 
-def _back_lm_tiles(xs, xe, n_crystals, pair, tof_bin, n, gc, tc, imgs, n_img, p, order):
+def _back_lm_tiles(xs, xe, n_crystals, pair, tof_bin, n, gc, tc, imgs, n_img, p, order, listmode=True):
     """A listmode back projection by image tiles (pp_back_lm_ws) with a workspace from torch's allocator; False,
     with nothing launched, where the library prefers its run/sheet kernel or the memory for it is not there."""
     lib = load()
-    nbytes = lib.pp_back_lm_workspace_bytes(n, gc, tc) if n > 0 and n_img > 0 else 0
+    nbytes = lib.pp_back_lm_workspace_bytes(n, gc, tc, int(listmode)) if n > 0 and n_img > 0 else 0
     if nbytes == 0:
         return False
     try:
@@ -53,8 +53,8 @@ def pp_back(xstart, xend, geom, img, p, order=None):
     _order(order, n)
     if p.dtype != torch.float32 or p.numel() != n:
         raise ValueError("p must be float32 [n]")
-    # an order makes it a listmode call; ray lists without one (sinograms) are runs of one line each
-    if order is None or not _back_lm_tiles(xstart, xend, 0, None, None, n, g.c(), None, img, 1, p, order):
+    # an order makes it a listmode call; ray lists without one are taken for sinograms, runs of one line each
+    if not _back_lm_tiles(xstart, xend, 0, None, None, n, g.c(), None, img, 1, p, order, order is not None):
         check(load().pp_back(ptr(xstart), ptr(xend), n, g.c(), ptr(img), ptr(p), ptr(order), stream_of(img)))
     return img
 

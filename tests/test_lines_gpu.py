@@ -102,7 +102,7 @@ def _large(name, n, seed):
 @pytest.mark.parametrize("name", ["flat", "odd"])
 def test_large_lists(gpu, name):
     """Lists long enough for the non-TOF line kernels, which small ones do not reach."""
-    dim, vox, o, h, xs, xe, img, y = _large(name, 4_200_000, 6)
+    dim, vox, o, h, xs, xe, img, y = _large(name, 5_800_000, 6)
     dev = torch.device("cuda")
     t = lambda a: torch.from_numpy(a).to(dev)  # noqa: E731
     G = gpu.ImageGeom(dim, vox)
@@ -129,7 +129,7 @@ def test_large_tof_back(gpu, tof):
 
 def test_large_back_values_not_finite(gpu):
     """A ray with an infinite value reaches its own voxels only."""
-    dim, vox, o, h, xs, xe, _, y = _large("flat", 4_200_000, 9)
+    dim, vox, o, h, xs, xe, _, y = _large("flat", 5_800_000, 9)
     dev = torch.device("cuda")
     t = lambda a: torch.from_numpy(a).to(dev)  # noqa: E731
     at = 100_000

@@ -129,6 +129,26 @@ def test_values_far_apart(gpu):
     assert np.isfinite(bad[~near]).all() and not np.isfinite(bad[hit]).all()
 
 
+@pytest.mark.parametrize("listmode", [False, True])
+def test_tall_grid_rule(gpu, listmode):
+    """Grids of more slices than a sheet holds: the tiles also take ray lists without an order, and more events."""
+    lib = gpu.load()
+    n = 20_011
+    dim, vox, o, h, xs, xe, _, p = _case("cut_slices", n, 8)
+    geom = gpu.ImageGeom(dim, vox)
+    most = 40_000_000 if listmode else 5_700_000
+    bytes_of = lambda d, k: lib.pp_back_lm_workspace_bytes(k, gpu.ImageGeom(d, vox).c(), None, int(listmode))  # noqa: E731
+    assert bytes_of(dim, most) > 0 and bytes_of(dim, most + 1) == 0
+    assert (bytes_of((33, 20, 128), 1000) > 0) == listmode
+    assert bytes_of((33, 20, 128), 7_000_001) == 0
+    assert bytes_of((2000, 2000, 700), 40_000_000) == 0  # the workspace's own limit
+    dev = torch.device("cuda")
+    t = lambda a: torch.from_numpy(a).to(dev)  # noqa: E731
+    order = t(np.random.default_rng(3).permutation(n).astype(np.int32)) if listmode else None
+    img = gpu.back(t(xs), t(xe), geom, t(p), order=order)
+    assert rel_l2(img.cpu().numpy(), oracle.back(xs, xe, o, h, dim, p)) <= TOL
+
+
 @pytest.mark.parametrize("sigma,table", [(24.8, False), (3.0, False), (24.8, True)])
 @pytest.mark.parametrize("n,n_sub", [(1, 1), (7, 9), (4001, 3)])
 def test_osem_frame_against_slots(gpu, sigma, table, n, n_sub):
