@@ -275,6 +275,13 @@ __device__ __forceinline__ bool tof_window_rel(RayK& r, double centre, double lo
     return any;
 }
 
+// Workgroups go to the 8 XCDs in turn.  This block index gives each XCD, with its own L2, one contiguous stretch of
+// a launch's work instead of every eighth block of it.
+__device__ __forceinline__ unsigned xcd_block() {
+    const unsigned per = gridDim.x >> 3, more = gridDim.x & 7u, x = blockIdx.x & 7u;
+    return x * per + (x < more ? x : more) + (blockIdx.x >> 3);
+}
+
 struct Stencil {
     int base;      // flat index of voxel (k, i0, j0)
     float fu, fw;  // fractional position inside the 2x2 cell
@@ -354,6 +361,81 @@ __device__ __forceinline__ float stencil_gather(__amdgpu_buffer_rsrc_t ib, const
     stencil_load<Pairs>(ib, r, st, st.base, v00, v01, v10, v11);
     const float gu = 1.0f - st.fu, gw = 1.0f - st.fw;
     return gu * (gw * v00 + st.fw * v01) + st.fu * (gw * v10 + st.fw * v11);
+}
+
+// The planes [ka, kb] of a ray whose four neighbours all lie inside the grid, with axis 2 among them (ka > kb: none).
+// U and W are monotonic in k, rounding included, so the ends vouch for the planes between them.
+__device__ __forceinline__ void inner_planes(const RayK& r, int& ka, int& kb) {
+    ka = r.k_lo, kb = r.k_hi;
+    if (r.sw != 1 || r.su >= (1 << 22)) kb = ka - 1;  // 24-bit products below
+    clip_affine(r.U0, r.dU, 0.0, (double)(r.nu - 1), ka, kb);
+    clip_affine(r.W0, r.dW, 0.0, (double)(r.nw - 1), ka, kb);
+    auto in = [&](int k) {
+        const double U = fma((double)k, r.dU, r.U0), W = fma((double)k, r.dW, r.W0);
+        return U >= 0.0 && U < (double)(r.nu - 1) && W >= 0.0 && W < (double)(r.nw - 1);
+    };
+    while (ka <= kb && !in(ka)) ++ka;
+    while (ka <= kb && !in(kb)) --kb;
+}
+
+// edge(k) for the planes outside [ka, kb] (inner_planes) that lane `part` of the ray's Parts lanes takes
+template <int Parts = 1, class Edge>
+__device__ __forceinline__ void edge_planes(const RayK& r, int ka, int kb, Edge&& edge, int part = 0) {
+    for (int k = r.k_lo + part;; k += Parts) {
+        if (k >= ka && k <= kb) k += ((kb - k) / Parts + 1) * Parts;
+        if (k > r.k_hi) break;
+        edge(k);
+    }
+}
+
+// Offset in voxels of (k, i0, j0) and the position inside the cell of an inner plane's sample
+__device__ __forceinline__ unsigned inner_at(const RayK& r, double kd, unsigned plane, float& fu, float& fw) {
+    const double U = fma(kd, r.dU, r.U0), W = fma(kd, r.dW, r.W0);
+    fu = (float)__builtin_amdgcn_fract(U), fw = (float)__builtin_amdgcn_fract(W);
+    return __umul24((unsigned)(int)U, (unsigned)r.su) + plane + (unsigned)(int)W;
+}
+
+// The sample from the two columns' pairs of slices
+__device__ __forceinline__ float inner_value(float a0, float a1, float c0, float c1, float fu, float fw) {
+    const float va = fmaf(fw, a1 - a0, a0), vc = fmaf(fw, c1 - c0, c0);
+    return fmaf(fu, vc - va, va);
+}
+
+// A forward sum over the planes of a ray: add(k, v) with the interpolated value of every plane sample.  Planes inside
+// (inner_planes) need neither their neighbours' bounds nor a choice of how to read them, half of the arithmetic
+// (4.24 -> 2.85 G vector instructions for 40 M presorted TOF events, 8.06 -> 6.8 ms; 7 M non-TOF events 2.54 -> 2.06 ms),
+// and are read kWalk at a time, so that a wave waits for memory once in kWalk samples (1.5 M TOF events: 569 -> 517 us);
+// past the last plane the loads are sent beyond the buffer's end, which reads 0.  Of Parts lanes that share a ray,
+// lane `part` adds its share of the planes.
+constexpr int kWalk = 4;
+
+template <int Parts = 1, class Add>
+__device__ __forceinline__ void ray_walk(__amdgpu_buffer_rsrc_t ib, const RayK& r, Add&& add, int part = 0) {
+    int ka, kb;
+    inner_planes(r, ka, kb);
+    edge_planes<Parts>(r, ka, kb, [&](int k) { add((double)k, stencil_gather(ib, r, stencil_at(r, k))); }, part);
+    ka += part * kWalk;
+    unsigned plane = (unsigned)(ka * r.sp);
+    double kd = (double)ka;
+    for (int k = ka; k <= kb; k += Parts * kWalk) {
+        uint2 a[kWalk], c[kWalk];
+        float fu[kWalk], fw[kWalk];
+        double ks = kd;
+#pragma unroll
+        for (int q = 0; q < kWalk; ++q, ks += 1.0, plane += (unsigned)r.sp) {
+            unsigned off = inner_at(r, ks, plane, fu[q], fw[q]) * 4u, off1 = off + (unsigned)r.su * 4u;
+            if (q > 0 && k + q > kb) off = off1 = 0xFFFFFFF0u;
+            const auto va = __builtin_amdgcn_raw_buffer_load_b64(ib, off, 0, 0);
+            const auto vc = __builtin_amdgcn_raw_buffer_load_b64(ib, off1, 0, 0);
+            a[q] = make_uint2(va[0], va[1]), c[q] = make_uint2(vc[0], vc[1]);
+        }
+#pragma unroll
+        for (int q = 0; q < kWalk; ++q, kd += 1.0) {
+            add(kd, inner_value(__uint_as_float(a[q].x), __uint_as_float(a[q].y), __uint_as_float(c[q].x),
+                                __uint_as_float(c[q].y), fu[q], fw[q]));
+        }
+        if (Parts > 1) kd += (Parts - 1) * kWalk, plane += (unsigned)(r.sp * ((Parts - 1) * kWalk));
+    }
 }
 
 // stencil_gather of the image that starts `img_off` voxels into the buffer (same arithmetic)

@@ -108,6 +108,7 @@ __device__ inline float tof_weight_bound(const TofK& t, float* red) {
 struct ModeNonTof {
     static constexpr bool kAux = false;
     static constexpr bool kBatch = false;
+    static constexpr bool kReads = false;  // setup reads an image
     const float* __restrict__ p;
     __device__ bool setup(int64_t l, const RaySrc& src, const GeomK& g, RayK& r, float& cv,
                           int& /*aux*/) const {
@@ -131,6 +132,7 @@ template <int Form, bool PerRay = false, bool Batch = false>
 struct ModeTofLm {
     static constexpr bool kAux = PerRay;
     static constexpr bool kBatch = Batch;
+    static constexpr bool kReads = false;  // setup reads an image
     const float* __restrict__ p;
     const int16_t* __restrict__ bins;
     TofK t;
@@ -169,6 +171,7 @@ template <bool Lut, bool PerRay = false>
 struct ModeTofSino {
     static constexpr bool kAux = true;
     static constexpr bool kBatch = false;
+    static constexpr bool kReads = false;  // setup reads an image
     const float* __restrict__ p;  // [n][n_bins]
     TofK t;
     __device__ bool setup(int64_t l, const RaySrc& src, const GeomK& g, RayK& r, float& cv,
@@ -222,6 +225,7 @@ template <int Form>
 struct ModeOsem {
     static constexpr bool kAux = false;
     static constexpr bool kBatch = false;
+    static constexpr bool kReads = true;  // setup reads an image
     const float* __restrict__ x;
     const int16_t* __restrict__ bins;
     float bg;
@@ -233,10 +237,9 @@ struct ModeOsem {
         if (!tof_window_rel(r, t.c0 + b * t.bw, t.lo, t.hi)) return false;
         const __amdgpu_buffer_rsrc_t ib = img_buffer(x, g);
         float fwd = 0.0f;
-        for (int k = r.k_lo; k <= r.k_hi; ++k) {
-            const float w = tof_weight_unscaled<Form, true>(fma((double)k, r.ds, r.s0), t, t.u_per_mm);
-            fwd += w * stencil_gather(ib, r, stencil_at(r, k));
-        }
+        ray_walk(ib, r, [&](double kd, float v) {
+            fwd += tof_weight_unscaled<Form, true>(fma(kd, r.ds, r.s0), t, t.u_per_mm) * v;
+        });
         const float ybar = r.ell * kTofScale<Form> * fwd + bg;
         if (!(ybar > 0.0f)) return false;
         cv = r.ell / ybar * kTofScale<Form>;

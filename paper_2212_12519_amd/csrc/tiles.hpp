@@ -144,9 +144,12 @@ __global__ void __launch_bounds__(kBinBlock) k_tile_bin(Mode m, RaySrc src, int6
     static_assert(kBinBlock == kSheetBlock, "weight_bound reduces over kSheetBlock threads");
     const float wb = m.weight_bound(red);
     __syncthreads();
+    // OSEM projects here: neighbouring events, in the same L2, share the image's lines (125,000 events of a subset,
+    // 13 MB image: 158 -> 143 us; without image reads the plain order is the faster, 52 against 56 us)
+    const unsigned block = Mode::kReads ? xcd_block() : blockIdx.x;
     for (int e = 0; e < rays; ++e) {
-        const int q = (blockIdx.x * rays + e) * kBinBlock + threadIdx.x;
-        if ((blockIdx.x * rays + e) * kBinBlock >= n) break;  // block-uniform
+        const int q = (block * rays + e) * kBinBlock + threadIdx.x;
+        if ((block * rays + e) * kBinBlock >= n) break;  // block-uniform
         int64_t l = -1;
         if (q < n) {
             l = order ? (int64_t)order[q] : q;
