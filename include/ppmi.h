@@ -194,6 +194,17 @@ int pp_fwd_tof_lm_batch(const float* xstart, const float* xend, const int16_t* t
                         const pp_image_t* geom, const pp_tof_t* tof, const float* imgs, int32_t n_img, float* p,
                         const int32_t* order, void* stream);
 
+/* Bytes of device memory pp_fwd_tof_lm_batch_ws needs, 0 where pp_fwd_tof_lm_batch is the better call (one image,
+ * per-ray TOF parameters, few events for the grid; invalid arguments also give 0).  Host only. */
+size_t pp_fwd_tof_lm_batch_workspace_bytes(int64_t n_events, const pp_image_t* geom, const pp_tof_t* tof, int32_t n_img);
+
+/* pp_fwd_tof_lm_batch with the same results through a copy of the images interleaved voxel by voxel, made in
+ * workspace (16-byte aligned, else PP_EINVAL_PTR; at least pp_fwd_tof_lm_batch_workspace_bytes(...) bytes, not 0, else
+ * PP_EINVAL_N; in use until the launched work has ended). */
+int pp_fwd_tof_lm_batch_ws(const float* xstart, const float* xend, const int16_t* tof_bin, int64_t n_events,
+                           const pp_image_t* geom, const pp_tof_t* tof, const float* imgs, int32_t n_img, float* p,
+                           const int32_t* order, void* workspace, size_t workspace_bytes, void* stream);
+
 /* pp_back_tof_lm of the same events for n_img value arrays at once (the
  * adjoint of pp_fwd_tof_lm_batch, Sec. 2.2): imgs float32
  * [n_img][dim0][dim1][dim2] += the back projection of p[b] (float32

@@ -159,6 +159,7 @@ def load():
         "pp_fwd_tof_lm": [P, P, P, I64, G, T, P, P, P, P],
         "pp_back_tof_lm": [P, P, P, I64, G, T, P, P, P, P],
         "pp_fwd_tof_lm_batch": [P, P, P, I64, G, T, P, I32, P, P, P],
+        "pp_fwd_tof_lm_batch_ws": [P, P, P, I64, G, T, P, I32, P, P, P, ctypes.c_size_t, P],
         "pp_fwd_tof_lm_gather": [P, P, P, I64, G, T, P, P, P, P, P, P, P, P],
         "pp_back_tof_lm_batch": [P, P, P, I64, G, T, P, I32, P, P, P],
         "pp_back_lm_ws": [P, P, I32, P, P, I64, G, T, P, I32, P, P, P, ctypes.c_size_t, P],
@@ -194,6 +195,8 @@ def load():
     lib.pp_lm_presort_workspace_bytes.restype = ctypes.c_size_t
     lib.pp_lm_osem_frame_workspace_bytes.argtypes = [I64, I32, G, T]
     lib.pp_lm_osem_frame_workspace_bytes.restype = ctypes.c_size_t
+    lib.pp_fwd_tof_lm_batch_workspace_bytes.argtypes = [I64, G, T, I32]
+    lib.pp_fwd_tof_lm_batch_workspace_bytes.restype = ctypes.c_size_t
     lib.pp_back_lm_workspace_bytes.argtypes = [I64, G, T, I32]
     lib.pp_back_lm_workspace_bytes.restype = ctypes.c_size_t
     lib.pp_osem_chunks.argtypes = [I64, I32]

@@ -420,9 +420,9 @@ int pp_fwd_tof_lm_gather(const float* xstart, const float* xend, const int16_t* 
                                                EventsOut{xstart_out, xend_out, tof_bin_out, p_out}, as_stream(stream)));
 }
 
-int pp_fwd_tof_lm_batch(const float* xstart, const float* xend, const int16_t* tof_bin, int64_t n,
-                        const pp_image_t* geom, const pp_tof_t* tof, const float* imgs, int32_t n_img, float* p,
-                        const int32_t* order, void* stream) {
+static int fwd_batch(const float* xstart, const float* xend, const int16_t* tof_bin, int64_t n, const pp_image_t* geom,
+                     const pp_tof_t* tof, const float* imgs, int32_t n_img, float* p, const int32_t* order, bool use_ws,
+                     void* workspace, size_t workspace_bytes, void* stream) {
     GeomK g;
     TofK t;
     PP_TRY(make_geom(geom, g));
@@ -431,8 +431,33 @@ int pp_fwd_tof_lm_batch(const float* xstart, const float* xend, const int16_t* t
     if (n_img < 0 || n_img > (1 << 20)) return PP_EINVAL_N;
     if (n == 0 || n_img == 0) return PP_OK;
     if (!xstart || !xend || !tof_bin || !imgs || !p) return PP_EINVAL_PTR;
-    return hip_status(
-        launch_fwd_tof_lm_batch(coords(xstart, xend), tof_bin, n, g, t, imgs, n_img, p, order, as_stream(stream)));
+    if (use_ws) {
+        if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 15u) != 0) return PP_EINVAL_PTR;
+        const size_t need = fwd_batch_bytes(n, g, t, n_img);
+        if (need == 0 || workspace_bytes < need) return PP_EINVAL_N;
+    }
+    return hip_status(launch_fwd_tof_lm_batch(coords(xstart, xend), tof_bin, n, g, t, imgs, n_img, p, order,
+                                              static_cast<float*>(workspace), as_stream(stream)));
+}
+
+int pp_fwd_tof_lm_batch(const float* xstart, const float* xend, const int16_t* tof_bin, int64_t n,
+                        const pp_image_t* geom, const pp_tof_t* tof, const float* imgs, int32_t n_img, float* p,
+                        const int32_t* order, void* stream) {
+    return fwd_batch(xstart, xend, tof_bin, n, geom, tof, imgs, n_img, p, order, false, nullptr, 0, stream);
+}
+
+size_t pp_fwd_tof_lm_batch_workspace_bytes(int64_t n, const pp_image_t* geom, const pp_tof_t* tof, int32_t n_img) {
+    GeomK g;
+    TofK t;
+    if (n <= 0 || make_geom(geom, g) != PP_OK || make_tof(tof, t) != PP_OK) return 0;
+    return fwd_batch_bytes(n, g, t, n_img);
+}
+
+int pp_fwd_tof_lm_batch_ws(const float* xstart, const float* xend, const int16_t* tof_bin, int64_t n,
+                           const pp_image_t* geom, const pp_tof_t* tof, const float* imgs, int32_t n_img, float* p,
+                           const int32_t* order, void* workspace, size_t workspace_bytes, void* stream) {
+    return fwd_batch(xstart, xend, tof_bin, n, geom, tof, imgs, n_img, p, order, true, workspace, workspace_bytes,
+                     stream);
 }
 
 int pp_back_tof_lm_batch(const float* xstart, const float* xend, const int16_t* tof_bin, int64_t n,

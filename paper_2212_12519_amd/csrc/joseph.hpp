@@ -401,10 +401,22 @@ __device__ __forceinline__ float inner_value(float a0, float a1, float c0, float
     return fmaf(fu, vc - va, va);
 }
 
+// The sample of an edge plane, zero padding; spelled out, so that every kernel rounds it alike
+__device__ __forceinline__ float edge_value(const Stencil& st, float v00, float v01, float v10, float v11) {
+    const float gu = 1.0f - st.fu, gw = 1.0f - st.fw;
+    return fmaf(gu, fmaf(gw, v00, st.fw * v01), st.fu * fmaf(gw, v10, st.fw * v11));
+}
+
+__device__ __forceinline__ float edge_gather(__amdgpu_buffer_rsrc_t ib, const RayK& r, const Stencil& st, int base) {
+    float v00, v01, v10, v11;
+    stencil_load(ib, r, st, base, v00, v01, v10, v11);
+    return edge_value(st, v00, v01, v10, v11);
+}
+
 // A forward sum over the planes of a ray: add(k, v) with the interpolated value of every plane sample.  Planes inside
 // (inner_planes) need neither their neighbours' bounds nor a choice of how to read them, half of the arithmetic
-// (4.24 -> 2.85 G vector instructions for 40 M presorted TOF events, 8.06 -> 6.8 ms; 7 M non-TOF events 2.54 -> 2.06 ms),
-// and are read kWalk at a time, so that a wave waits for memory once in kWalk samples (1.5 M TOF events: 569 -> 517 us);
+// (4.24 -> 2.85 G vector instructions for 40 M presorted TOF events, 8.06 -> 6.8 ms; 10 M non-TOF events 2.54 -> 2.06 ms),
+// and are read kWalk at a time, so that a wave waits for memory once in kWalk samples (777,777 TOF events: 569 -> 517 us);
 // past the last plane the loads are sent beyond the buffer's end, which reads 0.  Of Parts lanes that share a ray,
 // lane `part` adds its share of the planes.
 constexpr int kWalk = 4;
@@ -413,7 +425,11 @@ template <int Parts = 1, class Add>
 __device__ __forceinline__ void ray_walk(__amdgpu_buffer_rsrc_t ib, const RayK& r, Add&& add, int part = 0) {
     int ka, kb;
     inner_planes(r, ka, kb);
-    edge_planes<Parts>(r, ka, kb, [&](int k) { add((double)k, stencil_gather(ib, r, stencil_at(r, k))); }, part);
+    auto edge = [&](int k) {
+        const Stencil st = stencil_at(r, k);
+        add((double)k, edge_gather(ib, r, st, st.base));
+    };
+    edge_planes<Parts>(r, ka, kb, edge, part);
     ka += part * kWalk;
     unsigned plane = (unsigned)(ka * r.sp);
     double kd = (double)ka;

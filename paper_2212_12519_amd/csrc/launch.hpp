@@ -38,7 +38,10 @@ hipError_t launch_fwd_tof_lm_gather(const RaySrc& src, const int16_t* bins, int6
                                     const TofK& t, const float* img, float* p, const int32_t* order,
                                     const EventsOut& eo, hipStream_t s);
 hipError_t launch_fwd_tof_lm_batch(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK& t,
-                                   const float* imgs, int n_img, float* p, const int32_t* order, hipStream_t s);
+                                   const float* imgs, int n_img, float* p, const int32_t* order, float* ws,
+                                   hipStream_t s);
+// bytes of the batched forward's interleaved copy of its images, 0: it reads them where they are
+size_t fwd_batch_bytes(int64_t n, const GeomK& g, const TofK& t, int n_img);
 hipError_t launch_back_tof_lm(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g,
                               const TofK& t, float* img, const float* p, const int32_t* order, hipStream_t s);
 hipError_t launch_back_tof_lm_batch(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g,

@@ -182,7 +182,7 @@ __global__ void __launch_bounds__(kBlock) k_fwd_tof_lm(RaySrc src,
         for (int k = k0; k <= k1; ++k) {
             if (k >= lo && k <= hi) {
                 const float w = tof_weight_unscaled<Form, true>(fma((double)k, r.ds, r.s0), t, q.inv);
-                acc = fmaf(w, stencil_gather<!PerRay>(ib, r, stencil_at(r, k)), acc);  // per-ray: arithmetic-bound
+                acc = fmaf(w, stencil_gather<false>(ib, r, stencil_at(r, k)), acc);  // per-ray: arithmetic-bound
             }
         }
     } else if (on) {
@@ -233,7 +233,11 @@ __global__ void __launch_bounds__(kBlock) k_fwd_tof_lm_batch(RaySrc src, const i
         const Stencil st = stencil_at(r, k);
 #pragma unroll
         for (int q = 0; q < kFwdBatch; ++q)
-            if (q < nimg) acc[q] = fmaf(w, stencil_gather_at<!PerRay>(ib, r, st, q * nv), acc[q]);  // nimg: uniform
+            if (q < nimg) {  // uniform
+                const float v = PerRay ? stencil_gather_at<false>(ib, r, st, q * nv)
+                                       : edge_gather(ib, r, st, st.base + q * nv);
+                acc[q] = fmaf(w, v, acc[q]);
+            }
     };
     if (kWaveSync) {  // every lane of the wave reaches this point
         const int lo = on ? r.k_lo : (1 << 30), hi = on ? r.k_hi : -(1 << 30);
@@ -265,6 +269,92 @@ __global__ void __launch_bounds__(kBlock) k_fwd_tof_lm_batch(RaySrc src, const i
     const float scale = on ? r.ell * kTofScale<Form> : 0.0f;
 #pragma unroll
     for (int q = 0; q < kFwdBatch; ++q)
+        if (q < nimg) p[(int64_t)q * n + l] = on ? acc[q] * scale : 0.0f;
+}
+
+// imgs[0 .. count) of nv voxels -> out[voxel][B], zeros for images count .. B - 1
+template <int B>
+__global__ void __launch_bounds__(kBlock) k_interleave(const float* __restrict__ imgs, int count, int64_t nv,
+                                                       float* __restrict__ out) {
+    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < nv; v += (int64_t)gridDim.x * kBlock) {
+        float x[B];
+#pragma unroll
+        for (int q = 0; q < B; ++q) x[q] = q < count ? imgs[q * nv + v] : 0.0f;
+#pragma unroll
+        for (int q = 0; q < B; q += 2) *reinterpret_cast<float2*>(out + v * B + q) = make_float2(x[q], x[q + 1]);
+    }
+}
+
+// A voxel of all B images from the interleaved copy, `at` its byte offset
+template <int B>
+__device__ __forceinline__ void load_images(__amdgpu_buffer_rsrc_t ib, unsigned at, float (&v)[B]) {
+    if constexpr (B == 2) {
+        const auto a = __builtin_amdgcn_raw_buffer_load_b64(ib, at, 0, 0);
+        v[0] = __uint_as_float(a[0]), v[1] = __uint_as_float(a[1]);
+    } else {
+#pragma unroll
+        for (int q = 0; q < B; q += 4) {
+            const auto a = __builtin_amdgcn_raw_buffer_load_b128(ib, at + q * 4u, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[q + i] = __uint_as_float(a[i]);
+        }
+    }
+}
+
+// k_fwd_tof_lm_batch over images interleaved voxel by voxel (k_interleave).  With the images apart a sample asks for
+// two cache lines of every image, and the lines of eight images, not one, have to stay in an L2 of 4 MB: 10 M
+// presorted events through eight images of 128 x 128 x 64 took 0.95 G misses, 17.8 ms.  Interleaved, a column's two
+// slices of all images are 64 bytes together: 0.45 G misses, 6.9 ms, the address units busy for most of it.  The same
+// arithmetic in the same order per image.
+template <int Form, int B>
+__global__ void __launch_bounds__(kBlock) k_fwd_tof_lm_mixed(RaySrc src, const int16_t* __restrict__ bins, int64_t n,
+                                                             GeomK g, TofK t, const float* __restrict__ mixed,
+                                                             int nimg, float* __restrict__ p,
+                                                             const int32_t* __restrict__ order) {
+    const __amdgpu_buffer_rsrc_t ib = img_buffer_n(mixed, g, B);
+    const int64_t l = ray_index(order, n);
+    const int64_t lc = l >= 0 ? l : 0;
+    const int b = bins[lc];
+    float acc[B];
+#pragma unroll
+    for (int q = 0; q < B; ++q) acc[q] = 0.0f;
+    RayK r;
+    const bool geo = ray_setup(src, lc, g, r);
+    const bool on = l >= 0 && b >= 0 && b < t.nb && geo && tof_window_rel(r, t.c0 + b * t.bw, t.lo, t.hi);
+    if (on) {
+        int ka, kb;
+        inner_planes(r, ka, kb);
+        edge_planes(r, ka, kb, [&](int k) {
+            const Stencil st = stencil_at(r, k);
+            const float w = tof_weight_unscaled<Form, true>(fma((double)k, r.ds, r.s0), t, t.u_per_mm);
+            const unsigned at = (unsigned)st.base * (B * 4u), su = (unsigned)r.su * (B * 4u), sw = (unsigned)r.sw * (B * 4u);
+            float v00[B], v01[B], v10[B], v11[B];
+            load_images<B>(ib, st.i0ok && st.j0ok ? at : 0xFFFFFF00u, v00);
+            load_images<B>(ib, st.i0ok && st.j1ok ? at + sw : 0xFFFFFF00u, v01);
+            load_images<B>(ib, st.i1ok && st.j0ok ? at + su : 0xFFFFFF00u, v10);
+            load_images<B>(ib, st.i1ok && st.j1ok ? at + su + sw : 0xFFFFFF00u, v11);
+#pragma unroll
+            for (int q = 0; q < B; ++q)
+                acc[q] = fmaf(w, edge_value(st, v00[q], v01[q], v10[q], v11[q]), acc[q]);
+        });
+        unsigned plane = (unsigned)(ka * r.sp);
+        double kd = (double)ka;
+        for (int k = ka; k <= kb; ++k, kd += 1.0, plane += (unsigned)r.sp) {
+            float fu, fw, a0[B], a1[B], c0[B], c1[B];
+            const unsigned at = inner_at(r, kd, plane, fu, fw) * (B * 4u), at1 = at + (unsigned)r.su * (B * 4u);
+            load_images<B>(ib, at, a0);
+            load_images<B>(ib, at + B * 4u, a1);
+            load_images<B>(ib, at1, c0);
+            load_images<B>(ib, at1 + B * 4u, c1);
+            const float w = tof_weight_unscaled<Form, true>(fma(kd, r.ds, r.s0), t, t.u_per_mm);
+#pragma unroll
+            for (int q = 0; q < B; ++q) acc[q] = fmaf(w, inner_value(a0[q], a1[q], c0[q], c1[q], fu, fw), acc[q]);
+        }
+    }
+    if (l < 0) return;
+    const float scale = on ? r.ell * kTofScale<Form> : 0.0f;
+#pragma unroll
+    for (int q = 0; q < B; ++q)
         if (q < nimg) p[(int64_t)q * n + l] = on ? acc[q] * scale : 0.0f;
 }
 
@@ -574,8 +664,8 @@ constexpr int64_t kLineRaysTof = 1 << 20;  // TOF back projection
 
 // Lanes that share a ray in the ray-per-thread forwards: kParts of them while that leaves lanes of the chip idle.
 // A small call's time is one ray's, a wait for memory per kWalk planes: 25 of them on a grid of 100 planes (64,000
-// rays: 22.2 -> 18.6 us).  Only where rays are sinograms' or sorted: 25,000 unsorted TOF events stay at 61 us, bound
-// by their 5 M requests for cache lines.
+// rays: 22.2 -> 18.6 us).  Only where rays are sinograms' or sorted: 100,001 unsorted TOF events stay at 61 us,
+// bound by their 20 M requests for cache lines.
 static bool split_rays(int64_t n) { return n <= (int64_t)device_cus() * (kBlock * 8 / kParts); }
 
 hipError_t launch_fwd(const RaySrc& src, int64_t n, const GeomK& g, const float* img, float* p,
@@ -677,8 +767,41 @@ hipError_t launch_fwd_tof_lm_gather(const RaySrc& src, const int16_t* bins, int6
     return hipGetLastError();
 }
 
+// Images interleaved per launch of k_fwd_tof_lm_mixed for a batch of n_img: 8, 4 or 2; 0 where the images stay apart.
+// The copy costs two passes over the images (eight of 128 x 128 x 64: 14 us).  At n = voxels / 16 the events already
+// repay it twice over (two images 46 -> 32 us, eight 392 -> 63 us; 12 mm bins, unsorted), below voxels / 32 two
+// images would gain nothing.
+static int mixed_images(int64_t n, const GeomK& g, const TofK& t, int n_img) {
+    const int64_t nv = (int64_t)g.n[0] * g.n[1] * g.n[2];
+    if (n_img < 2 || t.sig_ray || t.off_ray || n < nv / 32) return 0;
+    int B = n_img > 4 ? 8 : n_img > 2 ? 4 : 2;
+    while (B > 1 && nv * B * 4 >= 0xFFFFFF00ll) B /= 2;
+    return B > 1 ? B : 0;
+}
+
+size_t fwd_batch_bytes(int64_t n, const GeomK& g, const TofK& t, int n_img) {
+    return (size_t)g.n[0] * g.n[1] * g.n[2] * mixed_images(n, g, t, n_img) * sizeof(float);
+}
+
+template <int B>
+static hipError_t launch_mixed(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK& t,
+                               const float* imgs, int cnt, float* p, const int32_t* order, float* ws, hipStream_t s) {
+    const int64_t nv = (int64_t)g.n[0] * g.n[1] * g.n[2];
+    const int64_t blocks = (nv + kBlock - 1) / kBlock;
+    hipLaunchKernelGGL(k_interleave<B>, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(kBlock), 0, s, imgs, cnt,
+                       nv, ws);
+    const int form = tof_form(t);
+    auto* k = form == kFormLut    ? k_fwd_tof_lm_mixed<kFormLut, B>
+              : form == kFormPoly ? k_fwd_tof_lm_mixed<kFormPoly, B>
+                                  : k_fwd_tof_lm_mixed<kFormErf, B>;
+    hipLaunchKernelGGL(k, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, src, bins, n, g, t, ws, cnt, p, order);
+    return hipGetLastError();
+}
+
+// ws: fwd_batch_bytes of device memory, or nullptr
 hipError_t launch_fwd_tof_lm_batch(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK& t,
-                                   const float* imgs, int n_img, float* p, const int32_t* order, hipStream_t s) {
+                                   const float* imgs, int n_img, float* p, const int32_t* order, float* ws,
+                                   hipStream_t s) {
     const bool per = t.sig_ray || t.off_ray;
     const int form = tof_form(t);
     auto* k = form == kFormLut    ? (per ? k_fwd_tof_lm_batch<kFormLut, true> : k_fwd_tof_lm_batch<kFormLut, false>)
@@ -686,13 +809,22 @@ hipError_t launch_fwd_tof_lm_batch(const RaySrc& src, const int16_t* bins, int64
                                   : (per ? k_fwd_tof_lm_batch<kFormErf, true> : k_fwd_tof_lm_batch<kFormErf, false>);
     // images per launch: at most kFwdBatch, and their bytes within the 32-bit buffer range
     const int64_t nv = (int64_t)g.n[0] * g.n[1] * g.n[2];
+    const int most = ws ? mixed_images(n, g, t, n_img) : 0;
     int64_t per_launch = ((int64_t(1) << 32) - 1) / (nv * 4);
     if (per_launch > kFwdBatch) per_launch = kFwdBatch;
+    if (most) per_launch = most;
     for (int b0 = 0; b0 < n_img; b0 += (int)per_launch) {
         const int cnt = (n_img - b0 < per_launch) ? (n_img - b0) : (int)per_launch;
-        hipLaunchKernelGGL(k, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, src, bins, n, g, t, imgs + b0 * nv, cnt,
-                           p + b0 * n, order);
-        const hipError_t e = hipGetLastError();
+        const float* im = imgs + b0 * nv;
+        float* pb = p + b0 * n;
+        hipError_t e = hipSuccess;
+        if (most && cnt > 4) e = launch_mixed<8>(src, bins, n, g, t, im, cnt, pb, order, ws, s);
+        else if (most && cnt > 2) e = launch_mixed<4>(src, bins, n, g, t, im, cnt, pb, order, ws, s);
+        else if (most && cnt == 2) e = launch_mixed<2>(src, bins, n, g, t, im, cnt, pb, order, ws, s);
+        else {
+            hipLaunchKernelGGL(k, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, src, bins, n, g, t, im, cnt, pb, order);
+            e = hipGetLastError();
+        }
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -14,19 +14,25 @@ from ._lib import (TofParams, _bins, _crystal_events, _dev, _img, _order, _rays,
                    stream_of)
 
 
+def _workspace(nbytes, like):
+    """nbytes from torch's allocator on the device of `like`; None for 0, or where the memory is not there."""
+    if nbytes == 0:
+        return None
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=like.device)
+    except torch.OutOfMemoryError:
+        return None
+
+
 def _back_lm_tiles(xs, xe, n_crystals, pair, tof_bin, n, gc, tc, imgs, n_img, p, order, listmode=True):
     """A listmode back projection by image tiles (pp_back_lm_ws) with a workspace from torch's allocator; False,
     with nothing launched, where the library prefers its run/sheet kernel or the memory for it is not there."""
     lib = load()
-    nbytes = lib.pp_back_lm_workspace_bytes(n, gc, tc, int(listmode)) if n > 0 and n_img > 0 else 0
-    if nbytes == 0:
-        return False
-    try:
-        ws = torch.empty(nbytes, dtype=torch.uint8, device=imgs.device)
-    except torch.OutOfMemoryError:
+    ws = _workspace(lib.pp_back_lm_workspace_bytes(n, gc, tc, int(listmode)) if n > 0 and n_img > 0 else 0, imgs)
+    if ws is None:
         return False
     check(lib.pp_back_lm_ws(ptr(xs), ptr(xe), n_crystals, ptr(pair), ptr(tof_bin), n, gc, tc, ptr(imgs), n_img, ptr(p),
-                            ptr(order), ptr(ws), nbytes, stream_of(imgs)))
+                            ptr(order), ptr(ws), ws.numel(), stream_of(imgs)))
     return True
 
 
@@ -133,8 +139,14 @@ def pp_fwd_tof_lm_batch(xstart, xend, tof_bin, geom, tof, imgs, p, order=None):
     nb = imgs.numel() // g.n_vox
     if p.dtype != torch.float32 or p.numel() != nb * n:
         raise ValueError("p must be float32 [B, n]")
-    check(load().pp_fwd_tof_lm_batch(ptr(xstart), ptr(xend), ptr(tof_bin), n, g.c(), t.c(n), ptr(imgs), nb, ptr(p),
-                                     ptr(order), stream_of(p)))
+    lib, gc, tc = load(), g.c(), t.c(n)
+    ws = _workspace(lib.pp_fwd_tof_lm_batch_workspace_bytes(n, gc, tc, nb) if n > 0 else 0, imgs)
+    if ws is None:
+        check(lib.pp_fwd_tof_lm_batch(ptr(xstart), ptr(xend), ptr(tof_bin), n, gc, tc, ptr(imgs), nb, ptr(p), ptr(order),
+                                      stream_of(p)))
+    else:
+        check(lib.pp_fwd_tof_lm_batch_ws(ptr(xstart), ptr(xend), ptr(tof_bin), n, gc, tc, ptr(imgs), nb, ptr(p),
+                                         ptr(order), ptr(ws), ws.numel(), stream_of(p)))
     return p
 
 

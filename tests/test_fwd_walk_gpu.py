@@ -59,3 +59,23 @@ def test_walk(gpu, name, n):
         want = oracle.fwd_tof_lm(xs, xe, o, h, dim, tof, bins, img)
         few = oracle.count_samples(xs, xe, o, h, dim, tof, bins, per_ray=True)[1] <= 160
         assert rel_l2(got[few], want[few]) <= TOL
+
+
+@pytest.mark.parametrize("name", ["odd", "tall", "one_slice", "one_column", "two"])
+@pytest.mark.parametrize("n_img", [2, 3, 4, 5, 9, 10])
+def test_batch_interleaved(gpu, name, n_img):
+    """Images interleaved two, four and eight at a time: each image's projection is pp_fwd_tof_lm's, bit for bit."""
+    n = 5003
+    dim, vox, _, _, xs, xe, bins, _ = _case(name, n, 12)
+    dev = torch.device("cuda")
+    t = lambda a: torch.from_numpy(a).to(dev)  # noqa: E731
+    G = gpu.ImageGeom(dim, vox)
+    imgs = torch.rand((n_img, *dim), generator=torch.Generator().manual_seed(1)).to(dev)
+    order = t(np.random.default_rng(2).permutation(n).astype(np.int32))
+    lib = gpu.load()
+    for T in (gpu.TofParams(28.0, 24.8, 3.0, 29), gpu.TofParams(28.0, 3.0, 3.0, 29)):
+        assert lib.pp_fwd_tof_lm_batch_workspace_bytes(n, G.c(), T.c(n), n_img) > 0
+        assert lib.pp_fwd_tof_lm_batch_workspace_bytes(n, G.c(), T.c(n), 1) == 0
+        got = gpu.fwd_tof_lm_batch(t(xs), t(xe), t(bins), G, T, imgs, order)
+        for b in range(n_img):
+            assert torch.equal(got[b], gpu.fwd_tof_lm(t(xs), t(xe), t(bins), G, T, imgs[b].contiguous(), order)), b
