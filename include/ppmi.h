@@ -220,11 +220,12 @@ int pp_back_tof_lm_batch(const float* xstart, const float* xend, const int16_t* 
                          const pp_image_t* geom, const pp_tof_t* tof, float* imgs, int32_t n_img, const float* p,
                          const int32_t* order, void* stream);
 
-/* Bytes of device memory pp_back_lm_ws needs for n events on this grid (tof NULL: non-TOF), 0 where
+/* Bytes of device memory pp_back_lm_ws needs for n events and n_img images of this grid (tof NULL: non-TOF), 0 where
  * the call is better served by pp_back, pp_back_tof_lm or their variants (many events per transaxial
  * line, or a grid the tiles do not suit; invalid arguments also give 0).  listmode 0: the rays are a
  * sinogram's or another list of whole lines.  Host only. */
-size_t pp_back_lm_workspace_bytes(int64_t n_events, const pp_image_t* geom, const pp_tof_t* tof, int32_t listmode);
+size_t pp_back_lm_workspace_bytes(int64_t n_events, const pp_image_t* geom, const pp_tof_t* tof, int32_t listmode,
+                                   int32_t n_img);
 
 /* The listmode back projections (Sec. 2.2) with a caller workspace (16-byte aligned, at least
  * pp_back_lm_workspace_bytes(n_events, geom, tof, ...) bytes, else PP_EINVAL_N): the events' planes are

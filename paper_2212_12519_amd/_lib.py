@@ -197,7 +197,7 @@ def load():
     lib.pp_lm_osem_frame_workspace_bytes.restype = ctypes.c_size_t
     lib.pp_fwd_tof_lm_batch_workspace_bytes.argtypes = [I64, G, T, I32]
     lib.pp_fwd_tof_lm_batch_workspace_bytes.restype = ctypes.c_size_t
-    lib.pp_back_lm_workspace_bytes.argtypes = [I64, G, T, I32]
+    lib.pp_back_lm_workspace_bytes.argtypes = [I64, G, T, I32, I32]
     lib.pp_back_lm_workspace_bytes.restype = ctypes.c_size_t
     lib.pp_osem_chunks.argtypes = [I64, I32]
     lib.pp_osem_chunks.restype = I64

@@ -487,11 +487,12 @@ int pp_back_tof_lm(const float* xstart, const float* xend, const int16_t* tof_bi
     return hip_status(launch_back_tof_lm(coords(xstart, xend), tof_bin, n, g, t, img, p, order, as_stream(stream)));
 }
 
-size_t pp_back_lm_workspace_bytes(int64_t n, const pp_image_t* geom, const pp_tof_t* tof, int32_t listmode) {
+size_t pp_back_lm_workspace_bytes(int64_t n, const pp_image_t* geom, const pp_tof_t* tof, int32_t listmode,
+                                   int32_t n_img) {
     GeomK g;
     TofK t;
-    if (make_geom(geom, g) != PP_OK || (tof && make_tof(tof, t) != PP_OK)) return 0;
-    return tile_workspace_bytes(n, g, tof ? &t : nullptr, listmode != 0);
+    if (n_img < 1 || make_geom(geom, g) != PP_OK || (tof && make_tof(tof, t) != PP_OK)) return 0;
+    return tile_workspace_bytes(n, g, tof ? &t : nullptr, listmode != 0, n_img);
 }
 
 int pp_back_lm_ws(const float* xstart, const float* xend, int32_t n_crystals, const int32_t* pair,
@@ -508,7 +509,7 @@ int pp_back_lm_ws(const float* xstart, const float* xend, int32_t n_crystals, co
     if (n == 0 || n_img == 0) return PP_OK;
     if (!xstart || (!pair && !xend) || !imgs || !p || !workspace) return PP_EINVAL_PTR;
     if ((reinterpret_cast<uintptr_t>(workspace) & 15u) != 0) return PP_EINVAL_PTR;
-    const size_t need = tile_bytes(n, g, tof_bin ? &t : nullptr);
+    const size_t need = tile_bytes(n, g, tof_bin ? &t : nullptr, n_img);
     if (need == 0 || workspace_bytes < need) return PP_EINVAL_N;
     return hip_status(launch_back_tiles(src, tof_bin, n, g, tof_bin ? &t : nullptr, imgs, n_img, p, order, workspace,
                                         device_cus(), as_stream(stream)));
@@ -722,7 +723,7 @@ int pp_lm_osem_subset_batched(const pp_frame_desc_t* d_slots, int32_t n_slots, c
 
 size_t pp_lm_osem_frame_workspace_bytes(int64_t n_events, int32_t n_sub, const pp_image_t* geom, const pp_tof_t* tof) {
     if (n_events <= 0 || n_sub < 1) return 0;
-    return pp_back_lm_workspace_bytes((n_events + n_sub - 1) / n_sub, geom, tof, 1);
+    return pp_back_lm_workspace_bytes((n_events + n_sub - 1) / n_sub, geom, tof, 1, 1);
 }
 
 int pp_lm_osem_frame_ws(const pp_frame_desc_t* frame, const pp_image_t* geom, const pp_tof_t* tof, void* workspace,

@@ -50,8 +50,8 @@ hipError_t launch_back_tof_lm_batch(const RaySrc& src, const int16_t* bins, int6
 // tile back projection (tiles.hip): workspace bytes for n rays, 0 where it cannot serve them (tile_bytes) or another
 // kernel is the better one (tile_workspace_bytes; listmode: events rather than a sinogram's lines); bins
 // nullptr: non-TOF (one image)
-size_t tile_bytes(int64_t n, const GeomK& g, const TofK* t);
-size_t tile_workspace_bytes(int64_t n, const GeomK& g, const TofK* t, bool listmode);
+size_t tile_bytes(int64_t n, const GeomK& g, const TofK* t, int n_img = 1);
+size_t tile_workspace_bytes(int64_t n, const GeomK& g, const TofK* t, bool listmode, int n_img);
 hipError_t launch_back_tiles(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK* t,
                              float* imgs, int n_img, const float* p, const int32_t* order, void* ws, int cus,
                              hipStream_t s);

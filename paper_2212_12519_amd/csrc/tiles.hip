@@ -131,7 +131,7 @@ constexpr int64_t kTileRaysList = 5'700'000;
 
 static size_t up256(size_t b) { return (b + 255) & ~size_t(255); }
 
-static size_t tile_layout(int64_t events, int tiles, int bound, char* base, TileWork& w) {
+static size_t tile_layout(int64_t events, int tiles, int bound, int n_img, char* base, TileWork& w) {
     size_t at = 0;
     auto take = [&](size_t bytes) {
         char* p = base + at;
@@ -145,6 +145,8 @@ static size_t tile_layout(int64_t events, int tiles, int bound, char* base, Tile
     w.unit0 = reinterpret_cast<int*>(take((size_t)tiles * 4));
     w.rec = reinterpret_cast<TileRec*>(take((size_t)events * sizeof(TileRec)));
     w.piece = reinterpret_cast<uint2*>(take((size_t)events * bound * 8));
+    w.value = n_img > 1 ? reinterpret_cast<float*>(take((size_t)events * (n_img < kTileImages ? n_img : kTileImages) * 4))
+                        : nullptr;
     w.capacity = events * bound;
     return at;
 }
@@ -152,21 +154,21 @@ static size_t tile_layout(int64_t events, int tiles, int bound, char* base, Tile
 constexpr int64_t kTileEventsMost = 40'000'000;
 
 // 0: a grid the tiles do not suit, or more events than their counts (32 bits) or 16 GB of workspace hold
-size_t tile_bytes(int64_t n, const GeomK& g, const TofK* t) {
+size_t tile_bytes(int64_t n, const GeomK& g, const TofK* t, int n_img) {
     TileGeom tg;
     if (n <= 0 || n > kTileEventsMost || !tile_geom(g, tg)) return 0;
     TileWork w;
-    const size_t bytes = tile_layout(n, tg.count(), pieces_bound(g, tg, t), nullptr, w);
+    const size_t bytes = tile_layout(n, tg.count(), pieces_bound(g, tg, t), n_img, nullptr, w);
     return w.capacity <= INT32_MAX && bytes <= (size_t(16) << 30) ? bytes : 0;
 }
 
 // Grids of more slices than a sheet holds have no other way than float atomics (12 M presorted TOF events, 160
 // slices: 28 ms), so the tiles take all they can there, of a ray list what is left below the line kernels' size.
-size_t tile_workspace_bytes(int64_t n, const GeomK& g, const TofK* t, bool listmode) {
+size_t tile_workspace_bytes(int64_t n, const GeomK& g, const TofK* t, bool listmode, int n_img) {
     const bool sheets = g.n[2] <= kSheetMaxW;
     const int64_t most = !sheets ? (listmode ? kTileEventsMost : kTileRaysList) : !listmode ? 0
                          : t ? kTileEventsTof : kTileEventsNonTof;
-    return n <= most ? tile_bytes(n, g, t) : 0;
+    return n <= most ? tile_bytes(n, g, t, n_img) : 0;
 }
 
 template <class Mode>
@@ -176,7 +178,7 @@ static hipError_t launch_tiles(const Mode& m, const RaySrc& src, int64_t n, cons
     if (!tile_geom(g, tg)) return hipErrorInvalidValue;
     TileWork w;
     const int nt = tg.count(), cnt = (int)n;
-    tile_layout(n, nt, pieces_bound(g, tg, t), static_cast<char*>(ws), w);
+    tile_layout(n, nt, pieces_bound(g, tg, t), Mode::kBatch ? (n_img > 1 ? n_img : 2) : 1, static_cast<char*>(ws), w);
     const size_t lds = tg.lds_bytes(), hist = (size_t)nt * 4;
     hipError_t e = hipFuncSetAttribute((const void*)k_tile_add<Mode>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds);

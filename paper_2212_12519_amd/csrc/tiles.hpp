@@ -79,6 +79,7 @@ struct TileWork {
     int* unit0;   // [tiles + 1] its first unit
     TileRec* rec; // [events]
     uint2* piece; // [capacity] (record, k0 | (k1 - k0) << 16 | axis << 31)
+    float* value; // [images][n] batch modes: cv times the event's value, in processing order
     int64_t capacity;
 };
 
@@ -181,7 +182,10 @@ __global__ void __launch_bounds__(kBinBlock) k_tile_bin(Mode m, RaySrc src, int6
         }
         for (int b = 0; b < n_img; ++b) {  // largest finite |value|, per image
             float c = ok ? cv : 0.0f;
-            if constexpr (Mode::kBatch) c = ok ? cv * m.value(l, b, n) : 0.0f;
+            if constexpr (Mode::kBatch) {
+                c = ok ? cv * m.value(l, b, n) : 0.0f;
+                if (q < n) w.value[b * n + q] = c;
+            }
             float a = m.mag(c, ax) * wb;
             if (!(a <= FLT_MAX)) a = 0.0f;
 #pragma unroll
@@ -328,6 +332,12 @@ __global__ void __launch_bounds__(kAddBlock) k_tile_add(Mode m, int64_t n, GeomK
                 const int q = ((j & 1 ? kAddBlock / 64 - 1 - wave : wave) + j * (kAddBlock / 64)) * 64 + lane;
                 pcs[j] = q < nr ? w.piece[first + r0 + sorted[q]] : make_uint2(0u, kNoPlanes);
             }
+            // batch: the values come from k_tile_bin's copy in processing order, of which neighbouring pieces share
+            // lines (10 M events, 8 images: 15.4 -> 13.2 ms, 0.81 -> 0.31 G L2 misses against the caller's arrays)
+            float value[kEach];
+            if constexpr (Mode::kBatch)
+#pragma unroll
+                for (int j = 0; j < kEach; ++j) value[j] = w.value[b * n + pcs[j].x];
             TileRec next = w.rec[pcs[0].x];
 #pragma unroll
             for (int j = 0; j < kEach; ++j) {
@@ -337,7 +347,7 @@ __global__ void __launch_bounds__(kAddBlock) k_tile_add(Mode m, int64_t n, GeomK
                 if (pc.y == kNoPlanes) break;
                 float cv = rec.cv;
                 if constexpr (Mode::kBatch) {
-                    cv *= m.value(rec.l, b, n);
+                    cv = value[j];
                     if (cv == 0.0f) continue;
                 }
                 const float bound = ms.mag(cv, rec.aux) * weight * scale;

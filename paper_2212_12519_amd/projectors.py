@@ -28,7 +28,7 @@ def _back_lm_tiles(xs, xe, n_crystals, pair, tof_bin, n, gc, tc, imgs, n_img, p,
     """A listmode back projection by image tiles (pp_back_lm_ws) with a workspace from torch's allocator; False,
     with nothing launched, where the library prefers its run/sheet kernel or the memory for it is not there."""
     lib = load()
-    ws = _workspace(lib.pp_back_lm_workspace_bytes(n, gc, tc, int(listmode)) if n > 0 and n_img > 0 else 0, imgs)
+    ws = _workspace(lib.pp_back_lm_workspace_bytes(n, gc, tc, int(listmode), n_img) if n > 0 else 0, imgs)
     if ws is None:
         return False
     check(lib.pp_back_lm_ws(ptr(xs), ptr(xe), n_crystals, ptr(pair), ptr(tof_bin), n, gc, tc, ptr(imgs), n_img, ptr(p),

@@ -137,7 +137,7 @@ def test_tall_grid_rule(gpu, listmode):
     dim, vox, o, h, xs, xe, _, p = _case("cut_slices", n, 8)
     geom = gpu.ImageGeom(dim, vox)
     most = 40_000_000 if listmode else 5_700_000
-    bytes_of = lambda d, k: lib.pp_back_lm_workspace_bytes(k, gpu.ImageGeom(d, vox).c(), None, int(listmode))  # noqa: E731
+    bytes_of = lambda d, k: lib.pp_back_lm_workspace_bytes(k, gpu.ImageGeom(d, vox).c(), None, int(listmode), 1)  # noqa: E731
     assert bytes_of(dim, most) > 0 and bytes_of(dim, most + 1) == 0
     assert (bytes_of((33, 20, 128), 1000) > 0) == listmode
     assert bytes_of((33, 20, 128), 7_000_001) == 0
