@@ -138,3 +138,23 @@ def test_large_back_values_not_finite(gpu):
     hit = oracle.back(xs[at:at + 1], xe[at:at + 1], o, h, dim, np.ones(1, np.float32)) != 0
     near = binary_dilation(hit, np.ones((3, 3, 3)))
     assert np.isfinite(got[~near]).all()
+
+
+@pytest.mark.parametrize("share", [0.04])
+def test_small_values_beside_large(gpu, share):
+    """A few rays of a wave with 1e-9 of their line's values: the half of the grid that only they cross."""
+    dim, vox, o, h, xs, xe, _, _ = _large("odd", 1_060_000, 10)
+    dev = torch.device("cuda")
+    t = lambda a: torch.from_numpy(a).to(dev)  # noqa: E731
+    rng = np.random.default_rng(11)
+    z = o[2] + h[2] * (dim[2] - 1) / 2
+    up = (xs[:, 2] > z + h[2]) & (xe[:, 2] > z + h[2])
+    down = (xs[:, 2] < z - h[2]) & (xe[:, 2] < z - h[2])
+    y = rng.uniform(0.5, 1.5, (xs.shape[0], 13)).astype(np.float32)
+    y *= np.where(up & (rng.random(xs.shape[0]) < share), np.float32(1e-9), down.astype(np.float32))[:, None]
+    tof = (28.0, 24.8, 3.0, 13)
+    got = gpu.back_tof_sino(t(xs), t(xe), gpu.ImageGeom(dim, vox), gpu.TofParams(*tof), t(y)).cpu().numpy()
+    want = oracle.back_tof_sino(xs, xe, o, h, dim, tofd(*tof), y)
+    first = (dim[2] + 1) // 2 + 1
+    assert want[:, :, first:].any() and rel_l2(got[:, :, first:], want[:, :, first:]) <= BACK_TOL
+    assert rel_l2(got, want) <= BACK_TOL
