@@ -35,11 +35,11 @@ HBM_PEAK_GBS = 8000.0
 
 
 # the sources the listmode step's kernels and their launch configuration are built from
-STEP_SOURCES = ("api.hip", "joseph.hpp", "launch.hpp", "presort.hip", "projectors.hip", "sheet.hpp")
+STEP_SOURCES = ("api.hip", "joseph.hpp", "launch.hpp", "line.hpp", "presort.hip", "projectors.hip", "sheet.hpp")
 
 
 # the sources of the clinical sinogram legs' kernels
-SINO_SOURCES = ("api.hip", "joseph.hpp", "launch.hpp", "projectors.hip", "sheet.hpp")
+SINO_SOURCES = ("api.hip", "back_lines.hpp", "joseph.hpp", "launch.hpp", "line.hpp", "projectors.hip", "sheet.hpp")
 
 
 def kernel_sources_sha(sources=STEP_SOURCES):
@@ -57,9 +57,9 @@ def kernel_sources_sha(sources=STEP_SOURCES):
 TRAFFIC_JSON = os.path.join(ROOT, "profiles", "tof_lm_40M_traffic.json")
 SINO_TRAFFIC_JSON = os.path.join(ROOT, "profiles", "clinical_sino_traffic.json")
 # the sinogram legs' device kernels
-SINO_KERNELS = {"nontof_fwd": "ppmi::k_fwd", "nontof_back": "ppmi::k_back_runs<ppmi::ModeNonTof>",
-                "tof_fwd": "ppmi::k_fwd_tof_sino<false>",
-                "tof_back": "ppmi::k_back_runs<ppmi::ModeTofSino<false, false> >"}
+SINO_KERNELS = {"nontof_fwd": "ppmi::k_fwd_lines", "nontof_back": "ppmi::k_back_lines<ppmi::LineBackNonTof>",
+                "tof_fwd": "ppmi::k_fwd_tof_sino_lines<3>",
+                "tof_back": "ppmi::k_back_lines<ppmi::LineBackTofSino<3> >"}
 
 
 def traffic_record(which):
