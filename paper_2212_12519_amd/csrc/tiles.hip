@@ -127,6 +127,9 @@ static int pieces_bound(const GeomK& g, const TileGeom& tg, const TofK* t) {
 // limits lie a little below the crossings (serving grid 128 x 128 x 64: 13 M and 8 M).
 constexpr int64_t kTileEventsTof = 10'000'000;
 constexpr int64_t kTileEventsNonTof = 7'000'000;
+// Batches of images: a sheet is flushed at the end of every group and image, so the crossing lies higher (two images
+// of 128 x 128 x 64: 7.5 against 9.5 ms at 15 M events, 12.5 against 11.6 at 25 M; eight: 23.5 and 36.7, 40.8 and 46.9)
+constexpr int64_t kTileEventsBatch = 20'000'000;
 constexpr int64_t kTileRaysList = 5'700'000;
 
 static size_t up256(size_t b) { return (b + 255) & ~size_t(255); }
@@ -167,7 +170,7 @@ size_t tile_bytes(int64_t n, const GeomK& g, const TofK* t, int n_img) {
 size_t tile_workspace_bytes(int64_t n, const GeomK& g, const TofK* t, bool listmode, int n_img) {
     const bool sheets = g.n[2] <= kSheetMaxW;
     const int64_t most = !sheets ? (listmode ? kTileEventsMost : kTileRaysList) : !listmode ? 0
-                         : t ? kTileEventsTof : kTileEventsNonTof;
+                         : n_img > 1 ? kTileEventsBatch : t ? kTileEventsTof : kTileEventsNonTof;
     return n <= most ? tile_bytes(n, g, t, n_img) : 0;
 }
 

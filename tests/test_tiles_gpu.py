@@ -141,6 +141,10 @@ def test_tall_grid_rule(gpu, listmode):
     assert bytes_of(dim, most) > 0 and bytes_of(dim, most + 1) == 0
     assert (bytes_of((33, 20, 128), 1000) > 0) == listmode
     assert bytes_of((33, 20, 128), 7_000_001) == 0
+    T, G = gpu.TofParams(28.0, 24.8, 3.0, 29).c(), gpu.ImageGeom((33, 20, 128), vox).c()
+    for n_img, events in ((1, 10_000_000), (2, 20_000_000)):
+        assert (lib.pp_back_lm_workspace_bytes(events, G, T, int(listmode), n_img) > 0) == listmode
+        assert lib.pp_back_lm_workspace_bytes(events + 1, G, T, int(listmode), n_img) == 0
     assert bytes_of((2000, 2000, 700), 40_000_000) == 0  # the workspace's own limit
     dev = torch.device("cuda")
     t = lambda a: torch.from_numpy(a).to(dev)  # noqa: E731
