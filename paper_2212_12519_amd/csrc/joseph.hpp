@@ -395,22 +395,17 @@ __device__ __forceinline__ unsigned inner_at(const RayK& r, double kd, unsigned 
     return __umul24((unsigned)(int)U, (unsigned)r.su) + plane + (unsigned)(int)W;
 }
 
-// The sample from the two columns' pairs of slices
+// The sample from the two columns' pairs of slices (not a0 + fw (a1 - a0): an infinite voxel stays infinite); spelled
+// out, so that every kernel rounds it alike
 __device__ __forceinline__ float inner_value(float a0, float a1, float c0, float c1, float fu, float fw) {
-    const float va = fmaf(fw, a1 - a0, a0), vc = fmaf(fw, c1 - c0, c0);
-    return fmaf(fu, vc - va, va);
-}
-
-// The sample of an edge plane, zero padding; spelled out, so that every kernel rounds it alike
-__device__ __forceinline__ float edge_value(const Stencil& st, float v00, float v01, float v10, float v11) {
-    const float gu = 1.0f - st.fu, gw = 1.0f - st.fw;
-    return fmaf(gu, fmaf(gw, v00, st.fw * v01), st.fu * fmaf(gw, v10, st.fw * v11));
+    const float gu = 1.0f - fu, gw = 1.0f - fw;
+    return fmaf(gu, fmaf(gw, a0, fw * a1), fu * fmaf(gw, c0, fw * c1));
 }
 
 __device__ __forceinline__ float edge_gather(__amdgpu_buffer_rsrc_t ib, const RayK& r, const Stencil& st, int base) {
     float v00, v01, v10, v11;
     stencil_load(ib, r, st, base, v00, v01, v10, v11);
-    return edge_value(st, v00, v01, v10, v11);
+    return inner_value(v00, v01, v10, v11, st.fu, st.fw);
 }
 
 // A forward sum over the planes of a ray: add(k, v) with the interpolated value of every plane sample.  Planes inside

@@ -119,7 +119,8 @@ __device__ __forceinline__ void line_walk(const float* sheet, int zs, const RayK
     auto at = [&](double Z) {
         const int i = (int)Z;
         const float a = sheet[i], b = sheet[i + 1];
-        return fmaf((float)__builtin_amdgcn_fract(Z), b - a, a);
+        const float fw = (float)__builtin_amdgcn_fract(Z);
+        return fmaf(fw, b, (1.0f - fw) * a);  // not a + fw (b - a): an infinite voxel stays infinite
     };
     int k = r.k_lo;
     if (Four)

@@ -335,7 +335,7 @@ __global__ void __launch_bounds__(kBlock) k_fwd_tof_lm_mixed(RaySrc src, const i
             load_images<B>(ib, st.i1ok && st.j1ok ? at + su + sw : 0xFFFFFF00u, v11);
 #pragma unroll
             for (int q = 0; q < B; ++q)
-                acc[q] = fmaf(w, edge_value(st, v00[q], v01[q], v10[q], v11[q]), acc[q]);
+                acc[q] = fmaf(w, inner_value(v00[q], v01[q], v10[q], v11[q], st.fu, st.fw), acc[q]);
         });
         unsigned plane = (unsigned)(ka * r.sp);
         double kd = (double)ka;

@@ -79,3 +79,23 @@ def test_batch_interleaved(gpu, name, n_img):
         got = gpu.fwd_tof_lm_batch(t(xs), t(xe), t(bins), G, T, imgs, order)
         for b in range(n_img):
             assert torch.equal(got[b], gpu.fwd_tof_lm(t(xs), t(xe), t(bins), G, T, imgs[b].contiguous(), order)), b
+
+
+@pytest.mark.parametrize("n", [20_011, 140_003])
+def test_infinite_voxel(gpu, n):
+    """A ray through an infinite voxel is infinite, not a NaN, and no other ray is touched."""
+    dim, vox, o, h, xs, xe, bins, img = _case("odd", n, 13)
+    img[18, 20, 14] = np.inf
+    keep = np.isfinite(xs).all(1) & np.isfinite(xe).all(1) & (np.abs(xe - xs) > 1e-3).all(1)  # no exact weights of 0
+    xs, xe, bins = xs[keep], xe[keep], bins[keep]
+    dev = torch.device("cuda")
+    t = lambda a: torch.from_numpy(a).to(dev)  # noqa: E731
+    want = oracle.fwd(xs, xe, o, h, dim, img)
+    got = gpu.fwd(t(xs), t(xe), gpu.ImageGeom(dim, vox), t(img)).cpu().numpy()
+    assert np.isinf(want).any() and not np.isnan(got).any() and np.array_equal(np.isinf(got), np.isinf(want))
+    imgs = t(np.stack([img, np.ones_like(img)]))
+    T = gpu.TofParams(28.0, 24.8, 3.0, 29)
+    got = gpu.fwd_tof_lm_batch(t(xs), t(xe), t(bins), gpu.ImageGeom(dim, vox), T, imgs).cpu().numpy()
+    want = oracle.fwd_tof_lm(xs, xe, o, h, dim, tofd(28.0, 24.8, 3.0, 29), bins, img)
+    assert np.isinf(got[0][np.isinf(want) & ~np.isnan(got[0])]).all() and np.isfinite(got[1]).all()
+    assert not np.isfinite(got[0][np.isinf(want)]).any()  # a plane at the window's end may weigh the voxel by 0: NaN
