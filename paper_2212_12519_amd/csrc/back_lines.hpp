@@ -65,8 +65,10 @@ struct LineBackTofSino {
             const double Ba = fma((double)k0, dB, B0), Bb = fma((double)k1, dB, B0);
             const int first = __ffsll((long long)__ballot(on)) - 1;
             const double Ba0 = __shfl(Ba, first, 64), Bb0 = __shfl(Bb, first, 64);
-            const int dir = __builtin_amdgcn_readfirstlane(Bb0 > Ba0 ? 1 : -1);
-            const bool near = fabs(Ba - Ba0) < 0.49 && fabs(Bb - Bb0) < 0.49 && fabs(Ba0) < 4096.0 && fabs(Bb0) < 4096.0;
+            // the window moves one way only: a line's rays in both directions (bitwise the same U0 and dU) walk alone
+            const int dir = __builtin_amdgcn_readfirstlane(__shfl(dB, first, 64) > 0.0 ? 1 : -1);
+            const bool near = (dB > 0.0) == (dir > 0) && fabs(Ba - Ba0) < 0.49 && fabs(Bb - Bb0) < 0.49 &&
+                              fabs(Ba0) < 4096.0 && fabs(Bb0) < 4096.0;
             if (__ballot(on && !near) == 0ull) {
                 if (!on) return;
                 // cur: the lowest bin a lane lies in (wave-uniform; the others lie in cur or cur + 1)

@@ -1,0 +1,60 @@
+"""The TOF sinogram projections through line sheets where the wave's window of bins could go wrong, against the FP64
+oracle: rays in both directions on one line.
+
+Lists long enough for the line kernels (512 rays a line, more than 2^20 rays).  Tolerances as in test_lines_gpu.py: a
+projection sums few samples of a dozen float32 roundings each, 5e-6 in relative L2; a back projection 1e-4."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from helpers import f32, rel_l2, tofd
+
+pytestmark = pytest.mark.gpu
+
+TOL, BACK_TOL = 5e-6, 1e-4
+LINES, RAYS = 2100, 512
+
+
+def _grid(dim, vox):
+    return [f32(-(d - 1) / 2 * v) for d, v in zip(dim, vox)], [f32(v) for v in vox]
+
+
+def _both_ways(name, seed):
+    """LINES lines of RAYS rays each that share U0 and dU bit for bit in either direction: along axis 0 through a grid of
+    four planes, or at 45 degrees across a grid's corner (coordinates that are exact in float32).  Every chord is
+    shorter than half a bin of 28 mm."""
+    rng = np.random.default_rng(seed)
+    if name == "slab":
+        dim, vox = (4, 40, 33), (3.5, 4.0, 2.5)
+        y = rng.integers(-300, 301, LINES) * 0.25
+        a = np.column_stack([np.full(LINES, -60.0), y])
+        b = np.column_stack([np.full(LINES, 60.0), y])
+    else:
+        dim, vox = (24, 24, 33), (4.0, 4.0, 2.5)
+        c, m = rng.integers(80, 92, LINES) * 1.0, 48.0 - rng.integers(0, 32, LINES) * 0.25
+        a = np.column_stack([m - 64.0, m - c - 64.0])
+        b = np.column_stack([m + 64.0, m - c + 64.0])
+    a, b = a.repeat(RAYS, 0), b.repeat(RAYS, 0)
+    z = rng.uniform(-1.1, 1.1, (a.shape[0], 2)) * 0.5 * dim[2] * vox[2]
+    xs, xe = np.column_stack([a, z[:, 0]]), np.column_stack([b, z[:, 1]])
+    turn = rng.random(xs.shape[0]) < 0.5
+    xs[turn], xe[turn] = xe[turn].copy(), xs[turn].copy()
+    return dim, vox, xs.astype(np.float32), xe.astype(np.float32), rng
+
+
+@pytest.mark.parametrize("name", ["slab", "corner"])
+@pytest.mark.parametrize("offset", [-16.8, -2.0, 0.0, 13.0, 16.8])
+def test_both_directions_of_a_line(gpu, name, offset):
+    dim, vox, xs, xe, rng = _both_ways(name, 21)
+    o, h = _grid(dim, vox)
+    tof = (28.0, 24.8, 3.0, 9)
+    T, t64, G = gpu.TofParams(*tof, center_offset=offset), tofd(*tof, center_offset=offset), gpu.ImageGeom(dim, vox)
+    dev = torch.device("cuda")
+    t = lambda a: torch.from_numpy(a).to(dev)  # noqa: E731
+    img = rng.uniform(0.5, 2.0, dim).astype(np.float32)
+    got = gpu.fwd_tof_sino(t(xs), t(xe), G, T, t(img)).cpu().numpy()
+    assert rel_l2(got, oracle.fwd_tof_sino(xs, xe, o, h, dim, t64, img)) <= TOL
+    y = rng.uniform(0.0, 2.0, (xs.shape[0], tof[3])).astype(np.float32)
+    got = gpu.back_tof_sino(t(xs), t(xe), G, T, t(y)).cpu().numpy()
+    assert rel_l2(got, oracle.back_tof_sino(xs, xe, o, h, dim, t64, y)) <= BACK_TOL
