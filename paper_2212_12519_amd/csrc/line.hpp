@@ -66,7 +66,8 @@ __device__ __forceinline__ void line_trim(RayK& r) {
 // The sheet of line (p, U0, dU) over all planes (every thread of the workgroup; zeros where a column lies
 // outside the grid).  The planes' column offsets and weights are worked out once; a thread keeps its slice and
 // takes every rows-th plane, four planes' loads in flight together: with one at a time the load's latency, not
-// the rays' samples, was most of the kernel's time.
+// the rays' samples, was most of the kernel's time.  *odd: an entry is infinite, a NaN or so large that a difference
+// of two may be infinite.
 struct LinePlane {
     unsigned a, b;  // byte offsets of the two columns; out of the image's range outside the grid
     float fu;
@@ -74,7 +75,7 @@ struct LinePlane {
 constexpr unsigned kLineOutside = 0xC0000000u;  // beyond every grid whose sheet fits the LDS
 
 __device__ __forceinline__ void line_load(float* sheet, LinePlane* planes, __amdgpu_buffer_rsrc_t ib, const GeomK& g, int p,
-                                 double U0, double dU) {
+                                 double U0, double dU, int* odd) {
     const int np = g.n[p], nu = g.n[1 - p], nw = g.n[2], zs = line_stride(g);
     const int sp = g.stride[p], su = g.stride[1 - p];
     const int T = blockDim.x, lanes = min(nw, T), rows = T / lanes;
@@ -85,6 +86,7 @@ __device__ __forceinline__ void line_load(float* sheet, LinePlane* planes, __amd
         planes[k] = {(unsigned)i0 < (unsigned)nu ? at : kLineOutside,
                      (unsigned)(i0 + 1) < (unsigned)nu ? at + (unsigned)su * 4u : kLineOutside, (float)(U - fi)};
     }
+    if (threadIdx.x == 0) *odd = 0;
     __syncthreads();
     const int kr = (int)threadIdx.x / lanes;
     constexpr int kBatch = 4;
@@ -102,7 +104,9 @@ __device__ __forceinline__ void line_load(float* sheet, LinePlane* planes, __amd
 #pragma unroll
             for (int u = 0; u < kBatch; ++u) {
                 const int k = k0 + u * rows;
-                if (k < np) sheet[k * zs + j + 1] = fmaf(fu[u], b[u], (1.0f - fu[u]) * a[u]);
+                const float v = fmaf(fu[u], b[u], (1.0f - fu[u]) * a[u]);
+                if (k < np) sheet[k * zs + j + 1] = v;
+                if (!(fabsf(v) <= 1e38f)) *odd = 1;
             }
         }
     }
@@ -178,7 +182,7 @@ struct LineShared {
     unsigned long long heads[kLineMaxBlock / 64];
     double last[3 * (kLineMaxBlock / 64)];
     double line[2];
-    int p;
+    int p, odd;
 };
 
 // Walks `groups` groups of blockDim.x rays from position `first` on, but those with their bit set in `left`.  setup(i, r) prepares the ray at position i
@@ -222,7 +226,7 @@ __device__ __forceinline__ void line_groups(const GeomK& g, __amdgpu_buffer_rsrc
                 const double U0 = sh.line[0], dU = sh.line[1];
                 const bool same = p >= 0 && p == cur_p && U0 == cur_U && dU == cur_d;
                 if (p >= 0 && !same && e - h >= min_run) {
-                    line_load(sheet, planes, ib, g, p, U0, dU);
+                    line_load(sheet, planes, ib, g, p, U0, dU, &sh.odd);
                     cur_p = p, cur_U = U0, cur_d = dU;
                 }
                 __syncthreads();

@@ -483,7 +483,7 @@ __global__ void __launch_bounds__(kSinoBlock, 4) k_fwd_tof_sino_lines(RaySrc src
             const double B0 = fma(r.s0, t.inv_bw, t.B0), dB = r.ds * t.inv_bw;
             const float ell = r.ell;
             float w[2 * R + 1];
-            if (sheet) {
+            if (sheet && !sh.odd) {  // a sheet with an infinity: a window per ray, which keeps it to its bins
                 const int k0 = __builtin_amdgcn_readfirstlane(wave_min(on ? r.k_lo : INT_MAX));
                 const int k1 = __builtin_amdgcn_readfirstlane(wave_max(on ? r.k_hi : INT_MIN));
                 // the lanes' positions in bins at both ends (linear between): how far they lie apart there
@@ -584,6 +584,12 @@ __global__ void __launch_bounds__(kSinoBlock, 4) k_fwd_tof_sino_lines(RaySrc src
                     else advance();
                 }
                 tof_edge_weights<R>((float)(B - fb), t, w);
+                if (__ballot(!(fabsf(v) <= FLT_MAX))) {  // only into the bins that the sample reaches: no 0 * inf
+#pragma unroll
+                    for (int i = 0; i <= 2 * R; ++i)
+                        if (w[i] != 0.0f) acc[i] = fmaf(w[i], v, acc[i]);
+                    return;
+                }
 #pragma unroll
                 for (int i = 0; i <= 2 * R; ++i) acc[i] = fmaf(w[i], v, acc[i]);
             };

@@ -1,5 +1,5 @@
 """The TOF sinogram projections through line sheets where the wave's window of bins could go wrong, against the FP64
-oracle: rays in both directions on one line.
+oracle: rays in both directions on one line, infinite voxels.
 
 Lists long enough for the line kernels (512 rays a line, more than 2^20 rays).  Tolerances as in test_lines_gpu.py: a
 projection sums few samples of a dozen float32 roundings each, 5e-6 in relative L2; a back projection 1e-4."""
@@ -58,3 +58,55 @@ def test_both_directions_of_a_line(gpu, name, offset):
     y = rng.uniform(0.0, 2.0, (xs.shape[0], tof[3])).astype(np.float32)
     got = gpu.back_tof_sino(t(xs), t(xe), G, T, t(y)).cpu().numpy()
     assert rel_l2(got, oracle.back_tof_sino(xs, xe, o, h, dim, t64, y)) <= BACK_TOL
+
+
+def _lines(dim, vox, seed, lines=LINES):
+    """Random lines of RAYS rays each, all of a line in one direction, heights at random."""
+    rng = np.random.default_rng(seed)
+    half = 0.5 * np.asarray(dim) * np.asarray(vox)
+    a, off = rng.uniform(0.0, 2.0 * np.pi, lines), rng.uniform(-0.8, 0.8, lines) * min(half[0], half[1])
+    d, nrm = np.column_stack([np.cos(a), np.sin(a)]), np.column_stack([-np.sin(a), np.cos(a)])
+    mid, reach = off[:, None] * nrm, 1.6 * max(half[0], half[1]) * d
+    ends = [e.astype(np.float32).repeat(RAYS, 0) for e in (mid - reach, mid + reach)]
+    z = rng.uniform(-0.9, 0.9, (lines * RAYS, 2)) * half[2]
+    return [np.column_stack([e, z[:, i]]).astype(np.float32) for i, e in enumerate(ends)], rng
+
+
+@pytest.mark.parametrize("lines", [LINES, 7])
+def test_infinite_voxel(gpu, lines):
+    """A ray's bins that the infinite voxel reaches are infinite, no value is a NaN, and the others are as without it,
+    through line sheets and (the short list) by gathers."""
+    dim, vox, tof = (37, 41, 15), (4.0, 3.5, 5.0), (28.0, 24.8, 3.0, 13)
+    (xs, xe), rng = _lines(dim, vox, 22, lines)
+    o, h = _grid(dim, vox)
+    dev = torch.device("cuda")
+    t = lambda a: torch.from_numpy(a).to(dev)  # noqa: E731
+    img = rng.uniform(0.5, 2.0, dim).astype(np.float32)
+    at = (18, 20, 7)
+    img[at] = 0.0
+    one = np.zeros(dim, np.float32)
+    one[at] = 1.0
+    want = oracle.fwd_tof_sino(xs, xe, o, h, dim, tofd(*tof), img)
+    reached = oracle.fwd_tof_sino(xs, xe, o, h, dim, tofd(*tof), one)
+    clear = oracle.fwd_tof_sino(xs, xe, o, h, dim, tofd(28.0, 24.8, 3.0001, 13), one) == 0.0
+    img[at] = np.inf
+    got = gpu.fwd_tof_sino(t(xs), t(xe), gpu.ImageGeom(dim, vox), gpu.TofParams(*tof), t(img)).cpu().numpy()
+    assert (reached > 1e-5).any() and not np.isnan(got).any()
+    assert np.isinf(got[reached > 1e-5]).all() and np.isfinite(got[clear]).all()
+    assert rel_l2(got[clear], want[clear]) <= TOL
+
+
+def test_infinite_voxel_nontof(gpu):
+    """The same without TOF, a list long enough for its line kernel: rays that the voxel reaches are infinite, no other."""
+    dim, vox = (19, 17, 9), (4.0, 3.5, 5.0)
+    (xs, xe), rng = _lines(dim, vox, 23, 11_400)
+    o, h = _grid(dim, vox)
+    dev = torch.device("cuda")
+    t = lambda a: torch.from_numpy(a).to(dev)  # noqa: E731
+    img = rng.uniform(0.5, 2.0, dim).astype(np.float32)
+    img[9, 8, 4] = np.inf
+    one = np.where(np.isinf(img), np.float32(1.0), np.float32(0.0))
+    reached = oracle.fwd(xs, xe, o, h, dim, one)
+    got = gpu.fwd(t(xs), t(xe), gpu.ImageGeom(dim, vox), t(img)).cpu().numpy()
+    assert (reached > 1e-5).any() and not np.isnan(got).any()
+    assert np.isinf(got[reached > 1e-5]).all() and np.isfinite(got[reached == 0.0]).all()
