@@ -145,14 +145,16 @@ void fit_tof_edges(double sig, double ns, double bw, TofEdgeK& e) {
     static_assert(kEdgeDegree == 7, "tof_edge_weights is written for degree 7");
     auto phi = [&](double x) { return 0.5 * std::erf(k * std::fmin(std::fmax(x, -X), X)); };
     e.R = R;
-    e.sat = (float)phi(X);
     e.t_max = (float)(X - (R - 0.5));
     for (int m = 0; m < R; ++m) {
         double c[kEdgeDegree + 1];
         cheb_powers([&](double s) { return 0.5 * std::erf(k * (m + 0.5 + 0.5 * s)); }, kEdgeDegree, c);
         for (int i = 0; i <= kEdgeDegree; ++i) e.c[m][i] = (float)std::ldexp(c[i], i);  // s = 2 t
     }
-    double err = 0.0;
+    // beyond the truncation as the clipped outer polynomial gives it, not as Phi(X) rounds: the difference of the two, the
+    // weight of a bin out of reach, is then 0 and not some -3e-8
+    e.sat = tof_edge_host(e.t_max, R - 1, false, e);
+    double err = std::fabs(e.sat - phi(X));
     for (int m = 0; m < R; ++m)
         for (int i = 0; i <= 256; ++i) {
             const float g = (float)(i / 256.0 - 0.5);

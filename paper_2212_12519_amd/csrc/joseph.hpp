@@ -76,7 +76,7 @@ constexpr int kEdgeMaxR = 5;
 constexpr int kEdgeDegree = 7;
 struct TofEdgeK {
     int R;         // 0: no fit within the error bound, or more than kEdgeMaxR edges on a side
-    float sat;     // Phi beyond the truncation
+    float sat;     // Phi beyond the truncation, as the outermost polynomial gives it at t_max
     float t_max;   // the outermost edge's argument is clipped to t_max
     double B0, inv_bw;  // position in bins, B0 + s inv_bw: the nearest integer is the bin, the remainder g
     float c[kEdgeMaxR][kEdgeDegree + 1];  // Phi(m + 1/2 + t) = sum_i c[m][i] t^i
@@ -566,8 +566,9 @@ __device__ __forceinline__ void tof_edge_weights(float g, const TofEdgeK& t, flo
         w[R - m] = pos[m] - pos[m - 1];
         w[R + m] = neg[m] - neg[m - 1];
     }
-    w[0] = t.sat - pos[R - 1];
-    w[2 * R] = t.sat - neg[R - 1];
+    // not below 0 (just inside the truncation the polynomial may round above its end); the clamp to [0, 1] is free
+    w[0] = __builtin_amdgcn_fmed3f(t.sat - pos[R - 1], 0.0f, 1.0f);
+    w[2 * R] = __builtin_amdgcn_fmed3f(t.sat - neg[R - 1], 0.0f, 1.0f);
 }
 
 // Tabulated kernel (the lookup-table alternative of Sec. 4, which also admits non-Gaussian

@@ -1,5 +1,5 @@
 """The TOF sinogram projections through line sheets where the wave's window of bins could go wrong, against the FP64
-oracle: rays in both directions on one line, infinite voxels.
+oracle: rays in both directions on one line, infinite voxels, bins beyond the truncation.
 
 Lists long enough for the line kernels (512 rays a line, more than 2^20 rays).  Tolerances as in test_lines_gpu.py: a
 projection sums few samples of a dozen float32 roundings each, 5e-6 in relative L2; a back projection 1e-4."""
@@ -110,3 +110,24 @@ def test_infinite_voxel_nontof(gpu):
     got = gpu.fwd(t(xs), t(xe), gpu.ImageGeom(dim, vox), t(img)).cpu().numpy()
     assert (reached > 1e-5).any() and not np.isnan(got).any()
     assert np.isinf(got[reached > 1e-5]).all() and np.isfinite(got[reached == 0.0]).all()
+
+
+# truncations just above and just below an edge of a bin (3.08 and 4.96 bins), and the one of 58.5 mm FWHM in 28 mm bins
+@pytest.mark.parametrize("tof", [(12.0, 29.0 / 2.355, 3.0, 31), (15.0, 24.8, 3.0, 17), (28.0, 58.5 / 2.355, 3.0, 29)],
+                         ids=lambda t: str(t[0]))
+@pytest.mark.parametrize("lines", [600, 7])
+def test_bins_beyond_the_truncation(gpu, tof, lines):
+    """Of an image without negative voxels no bin is negative, and bins that no sample's truncated Gaussian reaches (nor
+    one truncated 1e-4 further out) are exactly 0."""
+    dim, vox = (37, 41, 15), (4.0, 3.5, 5.0)
+    (xs, xe), rng = _lines(dim, vox, 24, lines)
+    o, h = _grid(dim, vox)
+    dev = torch.device("cuda")
+    t = lambda a: torch.from_numpy(a).to(dev)  # noqa: E731
+    img = rng.uniform(0.5, 2.0, dim).astype(np.float32)
+    img[:, 12:] = 0.0
+    got = gpu.fwd_tof_sino(t(xs), t(xe), gpu.ImageGeom(dim, vox), gpu.TofParams(*tof), t(img)).cpu().numpy()
+    out = oracle.fwd_tof_sino(xs, xe, o, h, dim, tofd(tof[0], tof[1], tof[2] * 1.0001, tof[3]), img) == 0.0
+    assert out.any() and got[out].any() == False  # noqa: E712
+    assert got.min() >= 0.0
+    assert rel_l2(got, oracle.fwd_tof_sino(xs, xe, o, h, dim, tofd(*tof), img)) <= TOL
