@@ -16,9 +16,32 @@
 
 namespace ppmi {
 
-// The first run of a sheet is scaled below this; later ones of its line are added up to kSheetCap (precision and
-// flushes as in sheet.hpp: a ray of 512 of one size keeps 20 bits)
-constexpr int kLineFirstBits = 28;
+// A sheet's fixed point is as fine as its first run allows (the run's bound between half of kSheetCap and kSheetCap) and
+// is coarsened, by at most kLineCoarse bits in all, for later runs of the line that do not fit; a run that still does
+// not is preceded by a flush.  Values are left to the direct scatter below kSheetBits + what coarsening may still take:
+// the bits that sheet.hpp keeps at least.  The beginning of a line that goes on in the next group is scaled with room
+// for that group.  (A first run scaled to 28 bits, without coarsening, gave TOF sinograms with values over three decades
+// 2.9e-7 against float64 where k_back_runs gives 1.7e-7; now 1.2 to 1.6e-7.  335 M LORs: 22.9 -> 23.2 ms.)
+constexpr int kLineCoarse = 3;
+
+// Every word of the sheet divided by 2^sft and rounded, the remainder carried into the thread's next word (every thread
+// of the workgroup; the caller synchronises before and after).  Entries stay within kSheetCap, so 32 bits hold the sums.
+__device__ inline void line_coarsen(int* words, int count, int sft) {
+    int rem = 0;
+    const int half = 1 << (sft - 1);
+    auto one = [&](int v) {
+        const int t = v + rem, c = (t + half) >> sft;
+        rem = t - (c << sft);
+        return c;
+    };
+    int4* const quads = reinterpret_cast<int4*>(words);
+    for (int e = threadIdx.x; e < count / 4; e += blockDim.x) {
+        int4 v = quads[e];
+        v.x = one(v.x), v.y = one(v.y), v.z = one(v.z), v.w = one(v.w);
+        quads[e] = v;
+    }
+    for (int e = count / 4 * 4 + (int)threadIdx.x; e < count; e += blockDim.x) words[e] = one(words[e]);
+}
 
 struct LineBackNonTof {
     const float* __restrict__ p;
@@ -153,30 +176,32 @@ template <class Mode>
 __global__ void __launch_bounds__(kLineBlock, 4) k_back_lines(Mode m, RaySrc src, int64_t n, GeomK g,
                                                               float* __restrict__ img, int groups) {
     constexpr int T = kLineBlock;
-    extern __shared__ int line_sheet[];
+    extern __shared__ __attribute__((aligned(16))) int line_sheet[];
     __shared__ LineShared sh;
-    __shared__ unsigned left;
+    __shared__ unsigned left, on;  // groups left to k_back_runs; groups whose last line goes on after them
     __shared__ float part[T / 64];
     typedef __attribute__((address_space(3))) int lds_int;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, zs = line_stride(g), nw = g.n[2];
     const int words = line_words(g);
     int* const sheet = line_sheet + 1;
     LinePlane* const planes = reinterpret_cast<LinePlane*>(line_sheet + words);
-    if (tid == 0) left = 0;
+    if (tid == 0) left = on = 0;
     __syncthreads();
     const int64_t first = (int64_t)blockIdx.x * groups * T;
     if (tid < groups) {
         const int64_t i0 = first + (int64_t)tid * T;
         if (i0 < n && !line_group(src, i0, n, T)) atomicOr(&left, 1u << tid);
+        if (line_goes_on(src, i0 + T, n)) atomicOr(&on, 1u << tid);
     }
     __syncthreads();
-    const unsigned skip = left;
+    const unsigned skip = left, follow = on;
     const int64_t here = (n - first + T - 1) / T;  // groups with rays
     if (__popc(skip) >= (here < groups ? here : groups)) return;
     for (int e = tid; e < words; e += T) line_sheet[e] = 0;
     int cur_p = -1;  // the sheet's line, its scale and the bounds added to it (block-uniform)
     double cur_U = 0.0, cur_d = 0.0;
     float scale = 1.0f, used = 0.0f;
+    int coarse = 0;  // bits that the fixed point has been coarsened by
     // the sheet into the image's columns of its line, and cleared (every thread; synchronises before and after)
     auto flush = [&]() {
         const int np = g.n[cur_p], nu = g.n[1 - cur_p], sp = g.stride[cur_p], su = g.stride[1 - cur_p];
@@ -240,23 +265,40 @@ __global__ void __launch_bounds__(kLineBlock, 4) k_back_lines(Mode m, RaySrc src
                 for (int w = 0; w < T / 64; ++w) sum += part[w];
                 sum *= 1.0f + 0x1p-12f;
                 const bool same = p >= 0 && p == cur_p && U0 == cur_U && dU == cur_d;
-                const bool take = p >= 0 && sum > 0.0f && sum <= 1e37f && (same || e - h >= kLineMinRun);
+                // the beginning of a line that goes on in the next group, however short
+                const bool goes_on = e == T && (follow >> grp & 1) && grp + 1 < groups && !(skip >> (grp + 1) & 1);
+                const bool take = p >= 0 && sum > 0.0f && sum <= 1e37f && (same || goes_on || e - h >= kLineMinRun);
+                if (take && same && used + sum * scale > kSheetCap) {
+                    int sft = 1;
+                    while (sft <= kLineCoarse && ldexpf(used + sum * scale, -sft) + 1.0f > kSheetCap) ++sft;
+                    if (coarse + sft <= kLineCoarse && scale >= 0x1p-120f) {
+                        line_coarsen(line_sheet, words, sft);
+                        __syncthreads();
+                        coarse += sft;
+                        scale = ldexpf(scale, -sft);
+                        used = ldexpf(used, -sft) + 1.0f;  // each entry's rounding adds at most 1/2
+                    }
+                }
                 if (take && !(same && used + sum * scale <= kSheetCap)) {
                     if (cur_p >= 0) flush();
                     cur_p = p, cur_U = U0, cur_d = dU;
                     int ex = 0;
                     frexpf(sum, &ex);  // sum < 2^ex
-                    scale = ldexpf(1.0f, min(max(kLineFirstBits - ex, -126), 126));
+                    // room for another group of the line
+                    const int room = !goes_on ? 0 : e - h == T ? 1 : 2 * (e - h) >= T ? 2 : 3;
+                    scale = ldexpf(1.0f, min(max(31 - room - ex, -126), 126));
+                    if (sum * scale > kSheetCap) scale *= 0.5f;
                     used = 0.0f;
+                    coarse = 0;
                 }
                 if (take) {
                     used += sum * scale;
-                    // a ray of far smaller values than the run's (fewer than kSheetBits bits) is left to the direct scatter
-                    const bool on = mine && bound * scale >= (float)(1 << kSheetBits);
-                    if (__ballot(on)) {
+                    // a ray of far smaller values than the run's is left to the direct scatter
+                    const bool in = mine && bound * scale >= (float)(1 << (kSheetBits + kLineCoarse - coarse));
+                    if (__ballot(in)) {
                         const double dZ = r.dW + (double)zs, Z0 = r.W0 + 1.0;
                         float res = 0.0f;
-                        m.walk(r, l, cv * scale, on, true, [&](int k, float v) {
+                        m.walk(r, l, cv * scale, in, true, [&](int k, float v) {
                             const double Z = fma((double)k, dZ, Z0);
                             lds_int* const at = (lds_int*)sheet + (int)Z;
                             const float fw = (float)__builtin_amdgcn_fract(Z);
@@ -268,7 +310,7 @@ __global__ void __launch_bounds__(kLineBlock, 4) k_back_lines(Mode m, RaySrc src
                             __hip_atomic_fetch_add(at, q0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                             __hip_atomic_fetch_add(at + 1, (int)qt - q0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                         });
-                        todo = todo && !on;
+                        todo = todo && !in;
                     }
                 }
                 h = e;

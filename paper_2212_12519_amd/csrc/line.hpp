@@ -45,6 +45,13 @@ __device__ inline bool line_group(const RaySrc& src, int64_t i0, int64_t n, int 
     return same(0) || same(2);
 }
 
+// Whether ray i lies on the line of the one before it, by their transaxial end points
+__device__ inline bool line_goes_on(const RaySrc& src, int64_t i, int64_t n) {
+    const float *s0, *e0, *s1, *e1;
+    if (i >= n || !src.ends(i - 1, s0, e0) || !src.ends(i, s1, e1)) return false;
+    return s0[0] == s1[0] && s0[1] == s1[1] && e0[0] == e1[0] && e0[1] == e1[1];
+}
+
 // Rows of the sheet: planes 0 .. n_p - 1, nw + 2 entries each (slices -1 .. nw)
 __host__ __device__ inline int line_stride(const GeomK& g) { return g.n[2] + 2; }
 __host__ __device__ inline int line_planes(const GeomK& g) { return g.n[0] > g.n[1] ? g.n[0] : g.n[1]; }
