@@ -665,6 +665,20 @@ static int line_groups_of(int64_t n, int T, int rays) {
 }
 
 constexpr int kLineMaxWords = 20 * 1024;  // largest sheet (two workgroups of a smaller one share a CU's LDS)
+constexpr int64_t kCuLds = 160 * 1024;
+constexpr int64_t kLineStaticLds = sizeof(LineShared) + 256;  // what the line kernels hold beside the sheet and the planes
+
+// Dynamic LDS of k_fwd_lines and k_back_lines (64 bits: the extents of a long flat grid overflow an int)
+static int64_t line_lds_bytes(const GeomK& g) {
+    const int64_t planes = line_planes(g);
+    return (planes * line_stride(g) + 2 + 3 * planes) * (int64_t)sizeof(float);
+}
+
+// Whether a CU's LDS holds the grid's sheet with its planes' records
+static bool lines_fit(const GeomK& g) {
+    return (int64_t)line_planes(g) * line_stride(g) + 2 <= kLineMaxWords && line_lds_bytes(g) + kLineStaticLds <= kCuLds;
+}
+
 // Fewest rays the non-TOF line kernel is launched for: below, the second launch and the look at the groups are felt
 // where the lines turn out short (561,600 rays of 39 a line: 62 us by one kernel, 79 by two)
 constexpr int64_t kLineRays = 11 << 19;
@@ -678,9 +692,9 @@ static bool split_rays(int64_t n) { return n <= (int64_t)device_cus() * (kBlock 
 
 hipError_t launch_fwd(const RaySrc& src, int64_t n, const GeomK& g, const float* img, float* p,
                       const int32_t* order, hipStream_t s) {
-    if (!order && n >= kLineRays && line_words(g) <= kLineMaxWords && line_plane_words(g) <= kLineMaxWords) {
+    if (!order && n >= kLineRays && lines_fit(g)) {
         constexpr int T = kLineBlock;
-        const size_t lds = (size_t)(line_words(g) + line_plane_words(g)) * sizeof(float);
+        const size_t lds = (size_t)line_lds_bytes(g);
         const hipError_t e = hipFuncSetAttribute((const void*)k_fwd_lines, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  (int)lds);
         if (e != hipSuccess) return e;
@@ -728,7 +742,7 @@ static hipError_t launch_runs(const Mode& m, const RaySrc& src, int64_t n, const
 template <class LineMode, class Mode>
 static hipError_t launch_back_lines(const LineMode& lm, const Mode& m, const RaySrc& src, int64_t n, const GeomK& g,
                                     float* img, hipStream_t s) {
-    const size_t lds = (size_t)(line_words(g) + line_plane_words(g)) * sizeof(float);
+    const size_t lds = (size_t)line_lds_bytes(g);
     hipError_t e = hipFuncSetAttribute((const void*)k_back_lines<LineMode>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds);
     if (e != hipSuccess) return e;
@@ -740,14 +754,10 @@ static hipError_t launch_back_lines(const LineMode& lm, const Mode& m, const Ray
     return launch_runs<true>(m, src, n, g, img, nullptr, s);
 }
 
-static bool back_lines_fit(const GeomK& g) {
-    return line_words(g) <= kLineMaxWords && line_plane_words(g) <= kLineMaxWords;
-}
-
 hipError_t launch_back(const RaySrc& src, int64_t n, const GeomK& g, float* img, const float* p,
                        const int32_t* order, hipStream_t s) {
     ModeNonTof m{p};
-    if (!order && n >= kLineRays && back_lines_fit(g))
+    if (!order && n >= kLineRays && lines_fit(g))
         return launch_back_lines(LineBackNonTof{p}, m, src, n, g, img, s);
     return launch_runs(m, src, n, g, img, order, s);
 }
@@ -884,8 +894,10 @@ static int sino_block(int nb) { return nb <= 64 ? 256 : 64; }  // LDS tile <= 64
 // Threads of a k_fwd_tof_sino_lines workgroup: as many as leave two workgroups room in a CU's LDS, fewer where n would
 // leave CUs idle; 0 if the grid's sheet does not fit
 static int sino_lines_block(const GeomK& g, int64_t n) {
-    const int words = (80 * 1024 - (int)sizeof(LineShared) - 64) / 4 - line_words(g);
-    if (words < 8 * 64 || words < line_plane_words(g)) return 0;
+    const int64_t room = (80 * 1024 - (int)sizeof(LineShared) - 64) / 4 - ((int64_t)line_planes(g) * line_stride(g) + 2);
+    if (room < 8 * 64) return 0;
+    const int words = (int)room;
+    if (words < line_plane_words(g)) return 0;
     int rays = words / 8 / 64 * 64;
     rays = rays > kSinoBlock ? kSinoBlock : rays;
     while (rays > 64 && n < (int64_t)rays * 2 * device_cus()) rays = (rays / 2 + 63) / 64 * 64;
@@ -927,7 +939,7 @@ hipError_t launch_fwd_tof_sino(const RaySrc& src, int64_t n, const GeomK& g, con
 
 hipError_t launch_back_tof_sino(const RaySrc& src, int64_t n, const GeomK& g, const TofK& t, const TofEdgeK* te,
                                 float* img, const float* p, hipStream_t s) {
-    if (te && te->R && n >= kLineRaysTof && back_lines_fit(g)) {
+    if (te && te->R && n >= kLineRaysTof && lines_fit(g)) {
         const ModeTofSino<false> m{p, t};
         switch (te->R) {
             case 1: return launch_back_lines(LineBackTofSino<1>{p, *te, t.nb}, m, src, n, g, img, s);
