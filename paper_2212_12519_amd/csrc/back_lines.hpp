@@ -44,6 +44,7 @@ __device__ inline void line_coarsen(int* words, int count, int sft) {
 }
 
 struct LineBackNonTof {
+    static constexpr bool kRegular = true;  // the lists it takes (back_lines_group)
     const float* __restrict__ p;
     __device__ bool value(int64_t l, const RayK& r, float& cv, float& bound) const {
         const float pl = p[l];
@@ -65,6 +66,7 @@ struct LineBackNonTof {
 // (k_fwd_tof_sino_lines), the next bin's value loaded ahead.
 template <int R>
 struct LineBackTofSino {
+    static constexpr bool kRegular = false;
     const float* __restrict__ p;  // [n][nb]
     TofEdgeK t;
     int nb;
@@ -171,7 +173,7 @@ __device__ __forceinline__ RayK ray_of_lane(const RayK& r, int j) {
     return o;
 }
 
-// The groups of kLineBlock rays that line_group takes (the others: k_back_runs)
+// The groups of kLineBlock rays that back_lines_group takes (the others: k_back_runs)
 template <class Mode>
 __global__ void __launch_bounds__(kLineBlock, 4) k_back_lines(Mode m, RaySrc src, int64_t n, GeomK g,
                                                               float* __restrict__ img, int groups) {
@@ -188,10 +190,14 @@ __global__ void __launch_bounds__(kLineBlock, 4) k_back_lines(Mode m, RaySrc src
     if (tid == 0) left = on = 0;
     __syncthreads();
     const int64_t first = (int64_t)blockIdx.x * groups * T;
-    if (tid < groups) {
-        const int64_t i0 = first + (int64_t)tid * T;
-        if (i0 < n && !line_group(src, i0, n, T)) atomicOr(&left, 1u << tid);
-        if (line_goes_on(src, i0 + T, n)) atomicOr(&on, 1u << tid);
+    {
+        const int at = tid / kLineLanes;  // groups <= T / kLineLanes
+        const int64_t ia = first + (int64_t)at * T;
+        const bool some = at < groups && ia < n, take = back_lines_group(src, some ? ia : 0, n, Mode::kRegular);
+        if (some && tid % kLineLanes == 0) {
+            if (!take) atomicOr(&left, 1u << at);
+            if (line_goes_on(src, ia + T, n)) atomicOr(&on, 1u << at);
+        }
     }
     __syncthreads();
     const unsigned skip = left, follow = on;
@@ -245,77 +251,80 @@ __global__ void __launch_bounds__(kLineBlock, 4) k_back_lines(Mode m, RaySrc src
         bound *= 1.0f + 0x1p-8f;  // margin for the rounding of the bounds
         const int lp = (r.p == 0 || r.p == 1) ? r.p : -1;
         const int runs = line_runs(lp, r.U0, r.dU, sh.heads, sh.last);
-        if (runs * kLineHeads <= T) {
-            for (int h = 0; h < T;) {  // block-uniform
-                const int e = line_next(sh.heads, h);
-                const bool mine = todo && tid >= h && tid < e && lp >= 0 && bound <= FLT_MAX;
-                float b = mine ? bound : 0.0f;
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) b += __shfl_xor(b, off, 64);
-                if (lane == 0) part[wave] = b;
-                if (tid == h) {
-                    sh.p = lp;
-                    sh.line[0] = r.U0;
-                    sh.line[1] = r.dU;
-                }
-                __syncthreads();
-                const int p = sh.p;
-                const double U0 = sh.line[0], dU = sh.line[1];
-                float sum = 0.0f;
-                for (int w = 0; w < T / 64; ++w) sum += part[w];
-                sum *= 1.0f + 0x1p-12f;
-                const bool same = p >= 0 && p == cur_p && U0 == cur_U && dU == cur_d;
-                // the beginning of a line that goes on in the next group, however short
-                const bool goes_on = e == T && (follow >> grp & 1) && grp + 1 < groups && !(skip >> (grp + 1) & 1);
-                const bool take = p >= 0 && sum > 0.0f && sum <= 1e37f && (same || goes_on || e - h >= kLineMinRun);
-                if (take && same && used + sum * scale > kSheetCap) {
-                    int sft = 1;
-                    while (sft <= kLineCoarse && ldexpf(used + sum * scale, -sft) + 1.0f > kSheetCap) ++sft;
-                    if (coarse + sft <= kLineCoarse && scale >= 0x1p-120f) {
-                        line_coarsen(line_sheet, words, sft);
-                        __syncthreads();
-                        coarse += sft;
-                        scale = ldexpf(scale, -sft);
-                        used = ldexpf(used, -sft) + 1.0f;  // each entry's rounding adds at most 1/2
-                    }
-                }
-                if (take && !(same && used + sum * scale <= kSheetCap)) {
-                    if (cur_p >= 0) flush();
-                    cur_p = p, cur_U = U0, cur_d = dU;
-                    int ex = 0;
-                    frexpf(sum, &ex);  // sum < 2^ex
-                    // room for another group of the line
-                    const int room = !goes_on ? 0 : e - h == T ? 1 : 2 * (e - h) >= T ? 2 : 3;
-                    scale = ldexpf(1.0f, min(max(31 - room - ex, -126), 126));
-                    if (sum * scale > kSheetCap) scale *= 0.5f;
-                    used = 0.0f;
-                    coarse = 0;
-                }
-                if (take) {
-                    used += sum * scale;
-                    // a ray of far smaller values than the run's is left to the direct scatter
-                    const bool in = mine && bound * scale >= (float)(1 << (kSheetBits + kLineCoarse - coarse));
-                    if (__ballot(in)) {
-                        const double dZ = r.dW + (double)zs, Z0 = r.W0 + 1.0;
-                        float res = 0.0f;
-                        m.walk(r, l, cv * scale, in, true, [&](int k, float v) {
-                            const double Z = fma((double)k, dZ, Z0);
-                            lds_int* const at = (lds_int*)sheet + (int)Z;
-                            const float fw = (float)__builtin_amdgcn_fract(Z);
-                            // the value with the carried remainder, rounded; the first entry gets its own share rounded, the
-                            // second the rest
-                            const float tv = v + res, qt = rintf(tv);
-                            res = tv - qt;
-                            const int q0 = round_half_up(fmaf(-fw, v, v));
-                            __hip_atomic_fetch_add(at, q0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                            __hip_atomic_fetch_add(at + 1, (int)qt - q0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        });
-                        todo = todo && !in;
-                    }
-                }
+        for (int h = 0; h < T;) {  // block-uniform
+            const int e = line_next(sh.heads, h);
+            // among many runs the short ones between the group's first and last are left to the scatter unseen
+            if (runs * kLineHeads > T && h > 0 && e < T && e - h < kLineMinRun) {
                 h = e;
-                __syncthreads();  // before part[] and the line are written again
+                continue;
             }
+            const bool mine = todo && tid >= h && tid < e && lp >= 0 && bound <= FLT_MAX;
+            float b = mine ? bound : 0.0f;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) b += __shfl_xor(b, off, 64);
+            if (lane == 0) part[wave] = b;
+            if (tid == h) {
+                sh.p = lp;
+                sh.line[0] = r.U0;
+                sh.line[1] = r.dU;
+            }
+            __syncthreads();
+            const int p = sh.p;
+            const double U0 = sh.line[0], dU = sh.line[1];
+            float sum = 0.0f;
+            for (int w = 0; w < T / 64; ++w) sum += part[w];
+            sum *= 1.0f + 0x1p-12f;
+            const bool same = p >= 0 && p == cur_p && U0 == cur_U && dU == cur_d;
+            // the beginning of a line that goes on in the next group, however short
+            const bool goes_on = e == T && (follow >> grp & 1) && grp + 1 < groups && !(skip >> (grp + 1) & 1);
+            const bool take = p >= 0 && sum > 0.0f && sum <= 1e37f && (same || goes_on || e - h >= kLineMinRun);
+            if (take && same && used + sum * scale > kSheetCap) {
+                int sft = 1;
+                while (sft <= kLineCoarse && ldexpf(used + sum * scale, -sft) + 1.0f > kSheetCap) ++sft;
+                if (coarse + sft <= kLineCoarse && scale >= 0x1p-120f) {
+                    line_coarsen(line_sheet, words, sft);
+                    __syncthreads();
+                    coarse += sft;
+                    scale = ldexpf(scale, -sft);
+                    used = ldexpf(used, -sft) + 1.0f;  // each entry's rounding adds at most 1/2
+                }
+            }
+            if (take && !(same && used + sum * scale <= kSheetCap)) {
+                if (cur_p >= 0) flush();
+                cur_p = p, cur_U = U0, cur_d = dU;
+                int ex = 0;
+                frexpf(sum, &ex);  // sum < 2^ex
+                // room for another group of the line
+                const int room = !goes_on ? 0 : e - h == T ? 1 : 2 * (e - h) >= T ? 2 : 3;
+                scale = ldexpf(1.0f, min(max(31 - room - ex, -126), 126));
+                if (sum * scale > kSheetCap) scale *= 0.5f;
+                used = 0.0f;
+                coarse = 0;
+            }
+            if (take) {
+                used += sum * scale;
+                // a ray of far smaller values than the run's is left to the direct scatter
+                const bool in = mine && bound * scale >= (float)(1 << (kSheetBits + kLineCoarse - coarse));
+                if (__ballot(in)) {
+                    const double dZ = r.dW + (double)zs, Z0 = r.W0 + 1.0;
+                    float res = 0.0f;
+                    m.walk(r, l, cv * scale, in, true, [&](int k, float v) {
+                        const double Z = fma((double)k, dZ, Z0);
+                        lds_int* const at = (lds_int*)sheet + (int)Z;
+                        const float fw = (float)__builtin_amdgcn_fract(Z);
+                        // the value with the carried remainder, rounded; the first entry gets its own share rounded, the
+                        // second the rest
+                        const float tv = v + res, qt = rintf(tv);
+                        res = tv - qt;
+                        const int q0 = round_half_up(fmaf(-fw, v, v));
+                        __hip_atomic_fetch_add(at, q0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        __hip_atomic_fetch_add(at + 1, (int)qt - q0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    });
+                    todo = todo && !in;
+                }
+            }
+            h = e;
+            __syncthreads();  // before part[] and the line are written again
         }
         // Rays left out of their run's sheet (values of 1e-6 of the run's sum, as at a body's rim): the lanes of the
         // wave take a ray's planes.  With the wave's combined scatter for one such ray the clinical sinogram of a

@@ -45,6 +45,66 @@ __device__ inline bool line_group(const RaySrc& src, int64_t i0, int64_t n, int 
     return same(0) || same(2);
 }
 
+// The rule of k_back_lines for a group of kLineBlock rays, by the transaxial end points at its sixteen points:
+// - its first or its last nine points lie on one line that is longer than kLineLong rays (shorter ones change sheets
+//   too often: TOF lines of 480 rays 1.9 ms by k_back_runs, 2.2 by lines; of 600 rays 2.5 and 1.8 ms);
+// - at most kLineOther of the fifteen stretches between the points begin and end on different lines, so that no more than
+//   some 70 rays lie in short runs, which k_back_lines would scatter one by one (a line of 340 rays and 22 of 8 in
+//   turn: 57 ms where k_back_runs takes 15).  The stretches' lengths have no common divisor: a list that returns to a
+//   line every so many rays is not taken for one that stays on it;
+// - regular: the rays' mid points move by the same step from ray to ray, as in a sinogram, whose neighbours meet in few
+//   entries of the sheet.  Without TOF those meetings bound the kernel (40 M presorted events 11.8 ms by k_back_runs, 18.8
+//   by lines; lines of 1200 rays of random slices 1.25 and 1.63 ms); with TOF the lines are the faster all the same
+//   (lines of 1200 presorted rays 1.9 and 0.7 ms).
+// Called by whole waves, kLineLanes neighbouring lanes for a group, all of which get its answer.
+constexpr int kLineLanes = 16, kLineOther = 2, kLineRegular = 11, kLineLong = 545;
+
+// The points 0 .. 15 of a group: rays 0, 31, 68, 97, 138, 173, 206, 242, 274, 312, 342, 381, 409, 443, 478, 511
+__device__ __forceinline__ int line_point(int q) { return 34 * q + (int)(0x6766c7b797870525ull >> (4 * q) & 15) - 5; }
+
+__device__ inline bool back_lines_group(const RaySrc& src, int64_t i0, int64_t n, bool regular) {
+    static_assert(kLineBlock == 512, "the points");
+    const int lane = (int)threadIdx.x & 63, q = lane & (kLineLanes - 1);
+    const int64_t i = min(i0 + line_point(q), n - 1);
+    const float *s, *e;
+    const bool ok = src.ends(i, s, e);
+    float ax = 0.0f, ay = 0.0f, bx = 0.0f, by = 0.0f, step = 0.0f;
+    if (ok) ax = s[0], ay = s[1], bx = e[0], by = e[1];
+    const int group = lane & ~(kLineLanes - 1);
+    auto like = [&](int from) {  // this lane's ray lies on the line of lane `from`'s (every lane shuffles: no short circuit)
+        const float sx = __shfl(ax, from, 64), sy = __shfl(ay, from, 64), ex = __shfl(bx, from, 64), ey = __shfl(by, from, 64);
+        return sx == ax && sy == ay && ex == bx && ey == by;
+    };
+    auto of_group = [&](bool b) { return (unsigned)(__ballot(b) >> group) & 0xffffu; };
+    const bool bad = of_group(!ok) != 0;
+    const int other = __popc(of_group(!like(min(lane + 1, group + 15))));
+    const unsigned first = of_group(like(group)), last = of_group(like(group + 15));
+    // how long the group's first line is up to its last point here, and its last line from its first one
+    const int lead = __ffs((int)~first) - 1, trail = __clz((int)~(last << 16));
+    const int64_t far = q == 0 ? i0 + line_point(lead - 1) - kLineLong : i0 + line_point(kLineLanes - trail) + kLineLong;
+    bool on = false;
+    if ((q == 0 || q == 15) && far >= 0 && far < n && src.ends(far, s, e)) on = s[0] == ax && s[1] == ay && e[0] == bx && e[1] == by;
+    const unsigned out = of_group(on);
+    const bool head = lead >= 9 && out & 1, tail = trail >= 9 && out >> 15;
+    bool take = !bad && other <= kLineOther && (head || tail);
+    if (regular) {
+        // from this ray to the next, or the list's last one's from the one before it
+        const int64_t by1 = i + 1 < n ? 1 : -1;
+        if (src.ends(max(i + by1, (int64_t)0), s, e)) {
+            const float z = s[2] + e[2];
+            if (src.ends(i, s, e)) step = (z - (s[2] + e[2])) * (float)by1;
+        }
+        auto steps = [&](int from) {  // how many of the steps are lane `from`'s
+            const float d = __shfl(step, group + from, 64);
+            const int like_it = __popc(of_group(fabsf(step - d) <= 0.02f * fabsf(d)));
+            return d != 0.0f ? like_it : 0;
+        };
+        const int a = steps(2), b = steps(9);
+        take = take && max(a, b) >= kLineRegular;
+    }
+    return take;
+}
+
 // Whether ray i lies on the line of the one before it, by their transaxial end points
 __device__ inline bool line_goes_on(const RaySrc& src, int64_t i, int64_t n) {
     const float *s0, *e0, *s1, *e1;

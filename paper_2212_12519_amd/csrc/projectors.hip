@@ -717,7 +717,8 @@ hipError_t launch_fwd(const RaySrc& src, int64_t n, const GeomK& g, const float*
 // list without an order.
 template <bool Left = false, class Mode>
 static hipError_t launch_runs(const Mode& m, const RaySrc& src, int64_t n, const GeomK& g, float* img,
-                              const int32_t* order, hipStream_t s, int n_img = 1, int64_t img_stride = 0) {
+                              const int32_t* order, hipStream_t s, int n_img = 1, int64_t img_stride = 0,
+                              bool regular = false) {
     const int nw = (g.n[2] <= kSheetMaxW) ? g.n[2] : 0;
     const size_t lds = SheetLayout::bytes(nw, g);
     const void* k;
@@ -729,16 +730,20 @@ static hipError_t launch_runs(const Mode& m, const RaySrc& src, int64_t n, const
     const int cus = device_cus();
     int64_t groups = (n + (int64_t)kSheetBlock * 4 * cus - 1) / ((int64_t)kSheetBlock * 4 * cus);
     groups = groups < 1 ? 1 : (groups > kSheetGroups ? kSheetGroups : groups);
+    if (Left && n > (int64_t)kSheetGroups * kSheetBlock * 16 * cus)
+        groups = n > (int64_t)kLeftGroups * kSheetBlock * 16 * cus ? kLeftGroups : kLeftGroups / 2;
     const dim3 grid(grid_for(n, kSheetBlock * groups));
     if constexpr (Left)
-        hipLaunchKernelGGL(k_back_runs_left<Mode>, grid, dim3(kSheetBlock), lds, s, m, src, n, g, img, nw, (int)groups);
+        hipLaunchKernelGGL(k_back_runs_left<Mode>, grid, dim3(kSheetBlock), lds, s, m, src, n, g, img, nw, (int)groups,
+                           regular);
     else
         hipLaunchKernelGGL(k_back_runs<Mode>, grid, dim3(kSheetBlock), lds, s, m, src, n, g, img, order, nw, (int)groups,
                            n_img, img_stride);
     return hipGetLastError();
 }
 
-// The groups of rays with long runs by k_back_lines, the others by the run/sheet kernel
+// The groups of rays with long runs by k_back_lines, the others by the run/sheet kernel (first: their sums meet a small
+// image, where a float addition rounds less)
 template <class LineMode, class Mode>
 static hipError_t launch_back_lines(const LineMode& lm, const Mode& m, const RaySrc& src, int64_t n, const GeomK& g,
                                     float* img, hipStream_t s) {
@@ -746,12 +751,12 @@ static hipError_t launch_back_lines(const LineMode& lm, const Mode& m, const Ray
     hipError_t e = hipFuncSetAttribute((const void*)k_back_lines<LineMode>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds);
     if (e != hipSuccess) return e;
+    e = launch_runs<true>(m, src, n, g, img, nullptr, s, 1, 0, LineMode::kRegular);
+    if (e != hipSuccess) return e;
     const int groups = line_groups_of(n, kLineBlock, 16384);
     hipLaunchKernelGGL(k_back_lines<LineMode>, dim3(grid_for(n, kLineBlock * groups)), dim3(kLineBlock), lds, s, lm, src, n,
                        g, img, groups);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_runs<true>(m, src, n, g, img, nullptr, s);
+    return hipGetLastError();
 }
 
 hipError_t launch_back(const RaySrc& src, int64_t n, const GeomK& g, float* img, const float* p,

@@ -349,7 +349,9 @@ __device__ __forceinline__ void sheet_flush(float* __restrict__ img, int* col, c
 // order.  The sheet of the current line (one column per absolute plane, so lines
 // need n_p <= 256) persists across groups; it is flushed when a run of another
 // line starts, when the line's values outgrow its fixed-point range, and at the end.
-template <class Mode>
+// Own: which rays add to the image directly is decided by their own bounds, not by differences of the groups' prefix
+// sums, whose rounding can put rays of 1e-9 of their run's values into the sheet (not for batches).
+template <bool Own = false, class Mode>
 __device__ void back_runs_chunk(const Mode& m, RaySrc src, int64_t n,
                                 const GeomK& g, float* __restrict__ img, const int32_t* __restrict__ order,
                                 int nw_lds, int groups, int64_t chunk0, double* smem, int n_img = 1,
@@ -362,9 +364,10 @@ __device__ void back_runs_chunk(const Mode& m, RaySrc src, int64_t n,
     double* U0 = ds + B;
     double* dU = U0 + B;
     float* cvs = reinterpret_cast<float*>(dU + B);
-    // k_lo | k_hi << 8 | p << 16 (the plane range is read for sheet rays only, whose planes are < 256)
+    // k_lo | k_hi << 8 | p << 16 (the plane range is read for sheet rays only, whose planes are < 256) and, for Own, the
+    // ray's bound of |an added value| << 18, in 13 bits (a float's exponent and 5 bits of its mantissa)
     int* lohi = reinterpret_cast<int*>(cvs + B);
-    auto pax = [&](int e) { return lohi[e] >> 16; };
+    auto pax = [&](int e) { return Own ? (lohi[e] >> 16) & 3 : lohi[e] >> 16; };
     int* start = lohi + B;
     int* cnt = start + B;
     int* masks = cnt + B;  // 8 words: run-boundary ballots of the 4 waves
@@ -417,6 +420,7 @@ __device__ void back_runs_chunk(const Mode& m, RaySrc src, int64_t n,
         // inclusive prefix sum, in ray order, of the valid rays' bounds of |an added value| (a run's
         // bound is the difference of two of them)
         float pm = ok ? m.mag(cv, ax) * wb : 0.0f;
+        const int own = Own ? (int)((__float_as_uint(pm) >> 18 & 0x1fffu) << 18) : 0;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
             const float o = __shfl_up(pm, off, 64);
@@ -443,7 +447,7 @@ __device__ void back_runs_chunk(const Mode& m, RaySrc src, int64_t n,
             dU[cp] = r.dU;
             cvs[cp] = cv;
             aux[cp] = ax;
-            lohi[cp] = (r.k_lo & 0xff) | ((r.k_hi & 0xff) << 8) | (r.p << 16);
+            lohi[cp] = (r.k_lo & 0xff) | ((r.k_hi & 0xff) << 8) | (r.p << 16) | own;
         }
         __syncthreads();
         // runs over the compacted entries (thread t examines entry t): maximal stretches with
@@ -649,7 +653,8 @@ __device__ void back_runs_chunk(const Mode& m, RaySrc src, int64_t n,
                     // a ray whose values would keep fewer than kSheetBits bits in the sheet's fixed point
                     // (far smaller values than the run's others) adds them to the image directly, with the
                     // direct path's float atomics
-                    const bool direct = cur.mg * sh_scale < (float)(1 << kSheetBits);
+                    const float mg = Own ? __uint_as_float((unsigned)cur.lh & 0x7ffc0000u) : cur.mg;
+                    const bool direct = mg * sh_scale < (float)(1 << kSheetBits);
                     if (klo <= khi) {
                         t_klo = min(t_klo, klo);
                         t_khi = max(t_khi, khi);
@@ -734,25 +739,39 @@ __global__ void __launch_bounds__(kSheetBlock) k_back_runs(Mode m, RaySrc src, i
     back_runs_chunk(m, src, n, g, img, order, nw_lds, groups, chunk0, smem, n_img, img_stride);
 }
 
-// The groups of kLineBlock rays that k_back_lines leaves (line_group), stretch by stretch of a workgroup's chunk
+// The groups of kLineBlock rays that k_back_lines leaves (back_lines_group), stretch by stretch of a workgroup's
+// `groups` times 256 rays: enough of them, where there are many, that the look at the groups, which nothing else of so few
+// resident workgroups hides, is not felt.
+constexpr int kLeftGroups = 32;
+
 template <class Mode>
 __global__ void __launch_bounds__(kSheetBlock) k_back_runs_left(Mode m, RaySrc src, int64_t n, GeomK g,
-                                                               float* __restrict__ img, int nw_lds, int groups) {
+                                                               float* __restrict__ img, int nw_lds, int groups,
+                                                               bool regular) {
     extern __shared__ double smem[];
     const int64_t chunk0 = (int64_t)blockIdx.x * groups * kSheetBlock;
     unsigned* const word = reinterpret_cast<unsigned*>(smem);
     if (threadIdx.x == 0) *word = 0;
     __syncthreads();
-    if ((int)threadIdx.x < groups) {  // bit q: the q-th 256 rays of the chunk
-        const int64_t i = chunk0 + (int64_t)threadIdx.x * kSheetBlock;
-        if (i < n && !line_group(src, i / kLineBlock * kLineBlock, n, kLineBlock)) atomicOr(word, 1u << threadIdx.x);
+    {  // bit q: the q-th 256 rays; kLineLanes lanes look at two of them, the halves of a group
+        constexpr int kHalves = kLineBlock / kSheetBlock;
+        static_assert(kLeftGroups / kHalves * kLineLanes <= kSheetBlock && kHalves == 2, "lanes for every group");
+        const int q = (int)threadIdx.x / kLineLanes * kHalves;
+        const int64_t i = (chunk0 / kLineBlock + q / kHalves) * kLineBlock;
+        const bool some = i < n, take = back_lines_group(src, some ? i : 0, n, regular);
+        if (some && !take && threadIdx.x % kLineLanes == 0) {
+            const int64_t b = i / kSheetBlock - chunk0 / kSheetBlock;  // -1: the chunk begins at the group's second half
+            for (int64_t h = b < 0 ? 0 : b; h < b + kHalves && h < groups; ++h)
+                if (i + (h - b) * kSheetBlock < n) atomicOr(word, 1u << h);
+        }
     }
     __syncthreads();
     unsigned left = __builtin_amdgcn_readfirstlane(*word);
     __syncthreads();
     while (left) {
-        const int q = __ffs((int)left) - 1, len = __ffs((int)~(left >> q)) - 1;
-        back_runs_chunk(m, src, n, g, img, nullptr, nw_lds, len, chunk0 + (int64_t)q * kSheetBlock, smem);
+        const int q = __ffs((int)left) - 1, run = __ffs((int)~(left >> q)) - 1;
+        const int len = run < 0 || run > kSheetGroups ? kSheetGroups : run;
+        back_runs_chunk<true>(m, src, n, g, img, nullptr, nw_lds, len, chunk0 + (int64_t)q * kSheetBlock, smem);
         left &= ~(((1u << len) - 1u) << q);
     }
 }
