@@ -410,30 +410,54 @@ __device__ __forceinline__ float edge_gather(__amdgpu_buffer_rsrc_t ib, const Ra
 
 // A forward sum over the planes of a ray: add(k, v) with the interpolated value of every plane sample.  Planes inside
 // (inner_planes) need neither their neighbours' bounds nor a choice of how to read them, half of the arithmetic
-// (4.24 -> 2.85 G vector instructions for 40 M presorted TOF events, 8.06 -> 6.8 ms; 10 M non-TOF events 2.54 -> 2.06 ms),
-// and are read kWalk at a time, so that a wave waits for memory once in kWalk samples (777,777 TOF events: 569 -> 517 us);
+// (4.24 -> 2.85 G vector instructions for 40 M presorted TOF events, 8.06 -> 6.8 ms; 10 M non-TOF events 2.54 -> 2.1 ms),
+// and are read Walk at a time, so that a wave waits for memory once in Walk samples (777,777 TOF events: 569 -> 517 us);
 // past the last plane the loads are sent beyond the buffer's end, which reads 0.  Of Parts lanes that share a ray,
 // lane `part` adds its share of the planes.
+// Ascend, for sums over whole chords: the planes in rising order, and all of them with their bounds (the same values in
+// the same order) where the walk is no gain for the wave: chords of fewer than 40 planes (thin grid, 1 M presorted rays: 104
+// us so, 123 with the walk); more than an eighth of them at the grid's faces in some lane, so that the lanes would wait for
+// each other three times (a sinogram's 652,800 oblique LORs in 71 slices: 122 us with every wave walking, 92 us).
 constexpr int kWalk = 4;
+constexpr int kPlainMost = 5;  // eighths of planes
 
-template <int Parts = 1, class Add>
+template <int Parts = 1, int Walk = kWalk, bool Ascend = false, class Add>
 __device__ __forceinline__ void ray_walk(__amdgpu_buffer_rsrc_t ib, const RayK& r, Add&& add, int part = 0) {
     int ka, kb;
-    inner_planes(r, ka, kb);
     auto edge = [&](int k) {
         const Stencil st = stencil_at(r, k);
         add((double)k, edge_gather(ib, r, st, st.base));
     };
-    edge_planes<Parts>(r, ka, kb, edge, part);
-    ka += part * kWalk;
+    if constexpr (Ascend && Parts == 1) {
+        const int total = r.k_hi - r.k_lo + 1;
+        int most = 0;  // the wave's largest total, in eighths of planes
+#pragma unroll
+        for (int bit = 32; bit > 0; bit >>= 1)
+            if (__ballot((total >> 3) >= (most | bit))) most |= bit;
+        bool plain = most < kPlainMost;
+        if (!plain) {
+            inner_planes(r, ka, kb);
+            plain = __ballot(total - max(kb - ka + 1, 0) > most) != 0ull;
+        }
+        if (plain) {
+            for (int k = r.k_lo; k <= r.k_hi; ++k) edge(k);
+            return;
+        }
+        if (ka > kb) ka = r.k_hi + 1, kb = r.k_hi;
+        for (int k = r.k_lo; k < ka; ++k) edge(k);
+    } else {
+        inner_planes(r, ka, kb);
+        edge_planes<Parts>(r, ka, kb, edge, part);
+    }
+    ka += part * Walk;
     unsigned plane = (unsigned)(ka * r.sp);
     double kd = (double)ka;
-    for (int k = ka; k <= kb; k += Parts * kWalk) {
-        uint2 a[kWalk], c[kWalk];
-        float fu[kWalk], fw[kWalk];
+    for (int k = ka; k <= kb; k += Parts * Walk) {
+        uint2 a[Walk], c[Walk];
+        float fu[Walk], fw[Walk];
         double ks = kd;
 #pragma unroll
-        for (int q = 0; q < kWalk; ++q, ks += 1.0, plane += (unsigned)r.sp) {
+        for (int q = 0; q < Walk; ++q, ks += 1.0, plane += (unsigned)r.sp) {
             unsigned off = inner_at(r, ks, plane, fu[q], fw[q]) * 4u, off1 = off + (unsigned)r.su * 4u;
             if (q > 0 && k + q > kb) off = off1 = 0xFFFFFFF0u;
             const auto va = __builtin_amdgcn_raw_buffer_load_b64(ib, off, 0, 0);
@@ -441,12 +465,14 @@ __device__ __forceinline__ void ray_walk(__amdgpu_buffer_rsrc_t ib, const RayK& 
             a[q] = make_uint2(va[0], va[1]), c[q] = make_uint2(vc[0], vc[1]);
         }
 #pragma unroll
-        for (int q = 0; q < kWalk; ++q, kd += 1.0) {
+        for (int q = 0; q < Walk; ++q, kd += 1.0) {
             add(kd, inner_value(__uint_as_float(a[q].x), __uint_as_float(a[q].y), __uint_as_float(c[q].x),
                                 __uint_as_float(c[q].y), fu[q], fw[q]));
         }
-        if (Parts > 1) kd += (Parts - 1) * kWalk, plane += (unsigned)(r.sp * ((Parts - 1) * kWalk));
+        if (Parts > 1) kd += (Parts - 1) * Walk, plane += (unsigned)(r.sp * ((Parts - 1) * Walk));
     }
+    if constexpr (Ascend && Parts == 1)
+        for (int k = kb + 1; k <= r.k_hi; ++k) edge(k);
 }
 
 // stencil_gather of the image that starts `img_off` voxels into the buffer (same arithmetic)

@@ -23,81 +23,90 @@ constexpr int kLineBlock = 512;  // rays of a group of k_fwd_lines and k_back_li
 constexpr int kLineMinRun = 96, kLineMinRunTof = 224;
 constexpr int kLineHeads = 32;  // a group with more runs than its rays / kLineHeads gathers them all
 
-// Whether the runs of a group of T rays are long enough for the group's waves to share sheets: the first or the last
-// 9/16 of the group lie on one line, by the transaxial end points of the first and last ray of either stretch.
-// (Much shorter runs would be walked one after the other by a few of the waves.  A group of a long list that
-// holds a line's end fails this with probability 1/8; with half a group asked, lists of 268 rays a line had
-// a few groups taken and took a tenth longer.)
-__device__ inline bool line_group(const RaySrc& src, int64_t i0, int64_t n, int T) {
-    const int at[4] = {0, T * 9 / 16, T - 1 - T * 9 / 16, T - 1};
-    const float *s[4], *e[4];
-    bool ok = true;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int64_t i = i0 + at[q];
-        ok &= src.ends(i < n ? i : n - 1, s[q], e[q]);
-    }
-    if (!ok) return false;
-    float2 a[4], b[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) a[q] = make_float2(s[q][0], s[q][1]), b[q] = make_float2(e[q][0], e[q][1]);
-    auto same = [&](int q) { return a[q].x == a[q + 1].x && a[q].y == a[q + 1].y && b[q].x == b[q + 1].x && b[q].y == b[q + 1].y; };
-    return same(0) || same(2);
-}
+// What a group of kLineBlock rays looks like at its sixteen points, by their transaxial end points: how many of the fifteen
+// stretches between them begin and end on different lines, and how many points lie on the line of the first and of
+// the last one without a break.  The stretches' lengths have no common divisor: a list that returns to a line every so
+// many rays is not taken for one that stays on it.
+constexpr int kLineLanes = 16;
 
-// The rule of k_back_lines for a group of kLineBlock rays, by the transaxial end points at its sixteen points:
-// - its first or its last nine points lie on one line that is longer than kLineLong rays (shorter ones change sheets
-//   too often: TOF lines of 480 rays 1.9 ms by k_back_runs, 2.2 by lines; of 600 rays 2.5 and 1.8 ms);
-// - at most kLineOther of the fifteen stretches between the points begin and end on different lines, so that no more than
-//   some 70 rays lie in short runs, which k_back_lines would scatter one by one (a line of 340 rays and 22 of 8 in
-//   turn: 57 ms where k_back_runs takes 15).  The stretches' lengths have no common divisor: a list that returns to a
-//   line every so many rays is not taken for one that stays on it;
-// - regular: the rays' mid points move by the same step from ray to ray, as in a sinogram, whose neighbours meet in few
-//   entries of the sheet.  Without TOF those meetings bound the kernel (40 M presorted events 11.8 ms by k_back_runs, 18.8
-//   by lines; lines of 1200 rays of random slices 1.25 and 1.63 ms); with TOF the lines are the faster all the same
-//   (lines of 1200 presorted rays 1.9 and 0.7 ms).
-// Called by whole waves, kLineLanes neighbouring lanes for a group, all of which get its answer.
-constexpr int kLineLanes = 16, kLineOther = 2, kLineRegular = 11, kLineLong = 545;
+struct LineProbe {
+    bool ok;                 // every point's ends are known
+    int other, lead, trail;
+    float ax, ay, bx, by;    // this lane's point's ends
+};
 
 // The points 0 .. 15 of a group: rays 0, 31, 68, 97, 138, 173, 206, 242, 274, 312, 342, 381, 409, 443, 478, 511
 __device__ __forceinline__ int line_point(int q) { return 34 * q + (int)(0x6766c7b797870525ull >> (4 * q) & 15) - 5; }
 
-__device__ inline bool back_lines_group(const RaySrc& src, int64_t i0, int64_t n, bool regular) {
+// The bits of b in this lane's group of kLineLanes (called by whole waves)
+__device__ __forceinline__ unsigned line_bits(bool b) {
+    return (unsigned)(__ballot(b) >> (threadIdx.x & 63 & ~(kLineLanes - 1))) & 0xffffu;
+}
+
+// Called by whole waves, kLineLanes neighbouring lanes for a group, all of which get its answer.
+__device__ inline LineProbe line_probe(const RaySrc& src, int64_t i0, int64_t n) {
     static_assert(kLineBlock == 512, "the points");
-    const int lane = (int)threadIdx.x & 63, q = lane & (kLineLanes - 1);
-    const int64_t i = min(i0 + line_point(q), n - 1);
+    const int lane = (int)threadIdx.x & 63, group = lane & ~(kLineLanes - 1);
     const float *s, *e;
-    const bool ok = src.ends(i, s, e);
-    float ax = 0.0f, ay = 0.0f, bx = 0.0f, by = 0.0f, step = 0.0f;
-    if (ok) ax = s[0], ay = s[1], bx = e[0], by = e[1];
-    const int group = lane & ~(kLineLanes - 1);
+    const bool ok = src.ends(min(i0 + line_point(lane - group), n - 1), s, e);
+    LineProbe p{false, 0, 0, 0, 0.0f, 0.0f, 0.0f, 0.0f};
+    if (ok) p.ax = s[0], p.ay = s[1], p.bx = e[0], p.by = e[1];
     auto like = [&](int from) {  // this lane's ray lies on the line of lane `from`'s (every lane shuffles: no short circuit)
-        const float sx = __shfl(ax, from, 64), sy = __shfl(ay, from, 64), ex = __shfl(bx, from, 64), ey = __shfl(by, from, 64);
-        return sx == ax && sy == ay && ex == bx && ey == by;
+        const float sx = __shfl(p.ax, from, 64), sy = __shfl(p.ay, from, 64);
+        const float ex = __shfl(p.bx, from, 64), ey = __shfl(p.by, from, 64);
+        return sx == p.ax && sy == p.ay && ex == p.bx && ey == p.by;
     };
-    auto of_group = [&](bool b) { return (unsigned)(__ballot(b) >> group) & 0xffffu; };
-    const bool bad = of_group(!ok) != 0;
-    const int other = __popc(of_group(!like(min(lane + 1, group + 15))));
-    const unsigned first = of_group(like(group)), last = of_group(like(group + 15));
-    // how long the group's first line is up to its last point here, and its last line from its first one
-    const int lead = __ffs((int)~first) - 1, trail = __clz((int)~(last << 16));
-    const int64_t far = q == 0 ? i0 + line_point(lead - 1) - kLineLong : i0 + line_point(kLineLanes - trail) + kLineLong;
+    p.ok = line_bits(!ok) == 0;
+    p.other = __popc(line_bits(!like(min(lane + 1, group + 15))));
+    p.lead = __ffs((int)~line_bits(like(group))) - 1;
+    p.trail = __clz((int)~(line_bits(like(group + 15)) << 16));
+    return p;
+}
+
+// Both line kernels take no group with more than some 70 rays in short runs (kLineOther stretches), which they would
+// scatter or gather one by one: a line of 340 rays and 22 of 8 in turn took 57 ms where k_back_runs takes 15 ms, one of 400
+// and 7 of 16 forward 2.9 ms where gathers take 1.7 ms.
+constexpr int kLineOther = 2;
+
+// The rule of k_fwd_lines: the first or the last nine points (nine sixteenths of the group) on one line.  (Much shorter
+// runs would be walked one after the other by a few of the waves.)
+__device__ inline bool line_group(const RaySrc& src, int64_t i0, int64_t n) {
+    const LineProbe p = line_probe(src, i0, n);
+    return p.ok && p.other <= kLineOther && (p.lead >= 9 || p.trail >= 9);
+}
+
+// The rule of k_back_lines besides:
+// - the line of those nine points is longer than kLineLong rays (shorter ones change sheets too often: TOF lines of 480
+//   rays 1.9 ms by k_back_runs, 2.2 by lines; of 600 rays 2.5 and 1.8 ms);
+// - regular: the rays' mid points move by the same step from ray to ray, as in a sinogram, whose neighbours meet in few
+//   entries of the sheet.  Without TOF those meetings bound the kernel (40 M presorted events 11.8 ms by k_back_runs, 18.8
+//   by lines; lines of 1200 rays of random slices 1.25 and 1.63 ms); with TOF the lines are the faster all the same
+//   (lines of 1200 presorted rays 1.9 and 0.7 ms).
+constexpr int kLineRegular = 11, kLineLong = 545;
+
+__device__ inline bool back_lines_group(const RaySrc& src, int64_t i0, int64_t n, bool regular) {
+    const LineProbe p = line_probe(src, i0, n);
+    const int lane = (int)threadIdx.x & 63, q = lane & (kLineLanes - 1);
+    // a ray kLineLong before the last point of the first line, and after the first point of the last one
+    const int64_t far = q == 0 ? i0 + line_point(p.lead - 1) - kLineLong : i0 + line_point(kLineLanes - p.trail) + kLineLong;
+    const float *s, *e;
     bool on = false;
-    if ((q == 0 || q == 15) && far >= 0 && far < n && src.ends(far, s, e)) on = s[0] == ax && s[1] == ay && e[0] == bx && e[1] == by;
-    const unsigned out = of_group(on);
-    const bool head = lead >= 9 && out & 1, tail = trail >= 9 && out >> 15;
-    bool take = !bad && other <= kLineOther && (head || tail);
+    if ((q == 0 || q == 15) && far >= 0 && far < n && src.ends(far, s, e))
+        on = s[0] == p.ax && s[1] == p.ay && e[0] == p.bx && e[1] == p.by;
+    const unsigned out = line_bits(on);
+    bool take = p.ok && p.other <= kLineOther && ((p.lead >= 9 && out & 1) || (p.trail >= 9 && out >> 15));
     if (regular) {
-        // from this ray to the next, or the list's last one's from the one before it
-        const int64_t by1 = i + 1 < n ? 1 : -1;
-        if (src.ends(max(i + by1, (int64_t)0), s, e)) {
+        // from this point's ray to the next, or the list's last one's from the one before it
+        const int64_t i = min(i0 + line_point(q), n - 1), by = i + 1 < n ? 1 : -1;
+        float step = 0.0f;
+        if (src.ends(max(i + by, (int64_t)0), s, e)) {
             const float z = s[2] + e[2];
-            if (src.ends(i, s, e)) step = (z - (s[2] + e[2])) * (float)by1;
+            if (src.ends(i, s, e)) step = (z - (s[2] + e[2])) * (float)by;
         }
-        auto steps = [&](int from) {  // how many of the steps are lane `from`'s
-            const float d = __shfl(step, group + from, 64);
-            const int like_it = __popc(of_group(fabsf(step - d) <= 0.02f * fabsf(d)));
-            return d != 0.0f ? like_it : 0;
+        auto steps = [&](int from) {  // how many of the steps are point `from`'s
+            const float d = __shfl(step, lane - q + from, 64);
+            const int alike = __popc(line_bits(fabsf(step - d) <= 0.02f * fabsf(d)));
+            return d != 0.0f ? alike : 0;
         };
         const int a = steps(2), b = steps(9);
         take = take && max(a, b) >= kLineRegular;

@@ -37,7 +37,7 @@ __device__ __forceinline__ float sum_parts(float v) {
     return v;
 }
 
-template <int Parts>
+template <int Parts, int Walk>
 __global__ void __launch_bounds__(kBlock) k_fwd(RaySrc src,
                                                 int64_t n, GeomK g, const float* __restrict__ img,
                                                 float* __restrict__ p, const int32_t* __restrict__ order) {
@@ -46,7 +46,7 @@ __global__ void __launch_bounds__(kBlock) k_fwd(RaySrc src,
     const __amdgpu_buffer_rsrc_t ib = img_buffer(img, g);
     RayK r;
     float acc = 0.0f;
-    if (l >= 0 && ray_setup(src, l, g, r)) ray_walk<Parts>(ib, r, [&](double, float v) { acc += v; }, part);
+    if (l >= 0 && ray_setup(src, l, g, r)) ray_walk<Parts, Walk, true>(ib, r, [&](double, float v) { acc += v; }, part);
     else r.ell = 0.0f;
     acc = sum_parts<Parts>(acc) * r.ell;
     if (l >= 0 && part == 0) p[l] = acc;
@@ -54,25 +54,29 @@ __global__ void __launch_bounds__(kBlock) k_fwd(RaySrc src,
 
 // The groups of kLineBlock rays that k_fwd_lines leaves (line_group), half a group at a time; a workgroup looks at
 // `batch` halves.
+constexpr int kLeftBatch = 32;
+
+template <int Walk>
 __global__ void __launch_bounds__(kBlock) k_fwd_left(RaySrc src, int64_t n, GeomK g, const float* __restrict__ img,
                                                      float* __restrict__ p, int batch) {
     static_assert(kLineBlock == 2 * kBlock, "halves of a group");
-    __shared__ bool left[kBlock];
-    const int64_t h0 = (int64_t)blockIdx.x * batch;
-    if ((int)threadIdx.x < batch) {
-        const int64_t i = (h0 + threadIdx.x) / 2 * kLineBlock;
-        left[threadIdx.x] = i < n && !line_group(src, i, n, kLineBlock);
-    }
+    static_assert(kLeftBatch / 2 * kLineLanes == kBlock, "lanes for every group");
+    __shared__ bool left[kLeftBatch / 2];
+    const int64_t h0 = (int64_t)blockIdx.x * batch;  // (batch is even: whole groups)
+    const int at = (int)threadIdx.x / kLineLanes;
+    const int64_t i = (h0 / 2 + at) * kLineBlock;
+    const bool take = line_group(src, i < n ? i : 0, n);
+    if (threadIdx.x % kLineLanes == 0) left[at] = i < n && !take;
     __syncthreads();
     const __amdgpu_buffer_rsrc_t ib = img_buffer(img, g);
     for (int q = 0; q < batch; ++q) {
-        if (!left[q]) continue;  // block-uniform
+        if (!left[q / 2]) continue;  // block-uniform
         const int64_t l = (h0 + q) * kBlock + threadIdx.x;
         if (l >= n) continue;
         RayK r;
         float acc = 0.0f;
         if (ray_setup(src, l, g, r)) {
-            ray_walk(ib, r, [&](double, float v) { acc += v; });
+            ray_walk<1, Walk, true>(ib, r, [&](double, float v) { acc += v; });
             acc *= r.ell;
         }
         p[l] = acc;
@@ -91,10 +95,10 @@ __global__ void __launch_bounds__(kLineBlock) k_fwd_lines(RaySrc src, int64_t n,
     if (threadIdx.x == 0) left = 0;
     __syncthreads();
     const int64_t first = (int64_t)blockIdx.x * groups * blockDim.x;
-    if ((int)threadIdx.x < groups) {
-        const int64_t i0 = first + (int64_t)threadIdx.x * blockDim.x;
-        if (i0 < n && !line_group(src, i0, n, blockDim.x)) atomicOr(&left, 1u << threadIdx.x);
-    }
+    const int at = (int)threadIdx.x / kLineLanes;  // groups <= kLineBlock / kLineLanes
+    const int64_t ia = first + (int64_t)at * blockDim.x;
+    const bool some = at < groups && ia < n, take = line_group(src, some ? ia : 0, n);
+    if (some && !take && threadIdx.x % kLineLanes == 0) atomicOr(&left, 1u << at);
     __syncthreads();
     const int64_t here = (n - first + blockDim.x - 1) / blockDim.x;  // groups with rays
     if (__popc(left) >= (here < groups ? here : groups)) return;
@@ -111,7 +115,7 @@ __global__ void __launch_bounds__(kLineBlock) k_fwd_lines(RaySrc src, int64_t n,
                 line_walk<true>(sheet, zs, r, [&](float v, int) { acc += v; },
                                 [&](const float (&v)[4]) { acc += (v[0] + v[1]) + (v[2] + v[3]); });
             } else {
-                ray_walk(ib, r, [&](double, float v) { acc += v; });
+                ray_walk<1, 1, true>(ib, r, [&](double, float v) { acc += v; });
             }
             acc *= r.ell;
         },
@@ -692,6 +696,10 @@ static bool split_rays(int64_t n) { return n <= (int64_t)device_cus() * (kBlock 
 
 hipError_t launch_fwd(const RaySrc& src, int64_t n, const GeomK& g, const float* img, float* p,
                       const int32_t* order, hipStream_t s) {
+    // Planes read at a time: while the image fits an XCD's L2 four (128 x 128 x 64, 5 M presorted rays 655 -> 599 us),
+    // in a larger one, whose lines more samples in flight only drive out, one (215 x 215 x 71, 1 M unsorted rays: 2.86 ms
+    // with four, 2.2 with one)
+    const bool walk4 = (int64_t)g.n[0] * g.n[1] * g.n[2] * 4 <= (4 << 20);
     if (!order && n >= kLineRays && lines_fit(g)) {
         constexpr int T = kLineBlock;
         const size_t lds = (size_t)line_lds_bytes(g);
@@ -699,17 +707,19 @@ hipError_t launch_fwd(const RaySrc& src, int64_t n, const GeomK& g, const float*
                                                  (int)lds);
         if (e != hipSuccess) return e;
         const int groups = line_groups_of(n, T, 16384);
-        const int64_t per = n / ((int64_t)kBlock * 64 * device_cus());
-        const int batch = (int)(per < 1 ? 1 : per > 64 ? 64 : per);
-        hipLaunchKernelGGL(k_fwd_left, dim3(grid_for(n, kBlock * batch)), dim3(kBlock), 0, s, src, n, g, img, p, batch);
+        const int64_t per = n / ((int64_t)kBlock * 32 * device_cus()) / 2 * 2;
+        const int batch = (int)(per < 2 ? 2 : per > kLeftBatch ? kLeftBatch : per);
+        hipLaunchKernelGGL(walk4 ? k_fwd_left<kWalk> : k_fwd_left<1>, dim3(grid_for(n, kBlock * batch)), dim3(kBlock), 0, s, src,
+                           n, g, img, p, batch);
         hipLaunchKernelGGL(k_fwd_lines, dim3(grid_for(n, T * groups)), dim3(T), lds, s, src, n, g, img, p, kLineMinRun,
                            groups);
         return hipGetLastError();
     }
     if (split_rays(n))
-        hipLaunchKernelGGL(k_fwd<kParts>, dim3(grid_for(n * kParts, kBlock)), dim3(kBlock), 0, s, src, n, g, img, p, order);
+        hipLaunchKernelGGL((k_fwd<kParts, 1>), dim3(grid_for(n * kParts, kBlock)), dim3(kBlock), 0, s, src, n, g, img, p, order);
     else
-        hipLaunchKernelGGL(k_fwd<1>, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, src, n, g, img, p, order);
+        hipLaunchKernelGGL((walk4 ? k_fwd<1, kWalk> : k_fwd<1, 1>), dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, src, n, g,
+                           img, p, order);
     return hipGetLastError();
 }
 
