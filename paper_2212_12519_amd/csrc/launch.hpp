@@ -52,6 +52,11 @@ hipError_t launch_back_tof_lm_batch(const RaySrc& src, const int16_t* bins, int6
 // nullptr: non-TOF (one image)
 size_t tile_bytes(int64_t n, const GeomK& g, const TofK* t, int n_img = 1);
 size_t tile_workspace_bytes(int64_t n, const GeomK& g, const TofK* t, bool listmode, int n_img);
+// the run/sheet back projection of a listmode call, for a device-side choice between it and the tiles: its launch does
+// nothing where *changes >= need
+hipError_t launch_back_runs_or_tiles(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK* t,
+                                     float* imgs, int n_img, const float* p, const int32_t* order, const int* changes,
+                                     int need, hipStream_t s);
 hipError_t launch_back_tiles(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK* t,
                              float* imgs, int n_img, const float* p, const int32_t* order, void* ws, int cus,
                              hipStream_t s);

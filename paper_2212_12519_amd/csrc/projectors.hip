@@ -728,7 +728,7 @@ hipError_t launch_fwd(const RaySrc& src, int64_t n, const GeomK& g, const float*
 template <bool Left = false, class Mode>
 static hipError_t launch_runs(const Mode& m, const RaySrc& src, int64_t n, const GeomK& g, float* img,
                               const int32_t* order, hipStream_t s, int n_img = 1, int64_t img_stride = 0,
-                              bool regular = false) {
+                              bool regular = false, RunsOrTiles choice = {nullptr, 0}) {
     const int nw = (g.n[2] <= kSheetMaxW) ? g.n[2] : 0;
     const size_t lds = SheetLayout::bytes(nw, g);
     const void* k;
@@ -748,7 +748,7 @@ static hipError_t launch_runs(const Mode& m, const RaySrc& src, int64_t n, const
                            regular);
     else
         hipLaunchKernelGGL(k_back_runs<Mode>, grid, dim3(kSheetBlock), lds, s, m, src, n, g, img, order, nw, (int)groups,
-                           n_img, img_stride);
+                           n_img, img_stride, choice);
     return hipGetLastError();
 }
 
@@ -863,25 +863,32 @@ hipError_t launch_fwd_tof_lm_batch(const RaySrc& src, const int16_t* bins, int64
     return hipSuccess;
 }
 
+static hipError_t back_tof_lm_runs(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK& t,
+                                   float* img, const float* p, const int32_t* order, hipStream_t s,
+                                   RunsOrTiles choice = {nullptr, 0}) {
+    const int form = tof_form(t);
+    auto runs = [&](const auto& m) { return launch_runs(m, src, n, g, img, order, s, 1, 0, false, choice); };
+    if (t.sig_ray || t.off_ray) {
+        if (form == kFormLut) return runs(ModeTofLm<kFormLut, true>{p, bins, t});
+        if (form == kFormPoly) return runs(ModeTofLm<kFormPoly, true>{p, bins, t});
+        return runs(ModeTofLm<kFormErf, true>{p, bins, t});
+    }
+    if (form == kFormLut) return runs(ModeTofLm<kFormLut>{p, bins, t});
+    if (form == kFormPoly) return runs(ModeTofLm<kFormPoly>{p, bins, t});
+    return runs(ModeTofLm<kFormErf>{p, bins, t});
+}
+
 hipError_t launch_back_tof_lm(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g,
                               const TofK& t, float* img, const float* p, const int32_t* order, hipStream_t s) {
-    const int form = tof_form(t);
-    if (t.sig_ray || t.off_ray) {
-        if (form == kFormLut) return launch_runs(ModeTofLm<kFormLut, true>{p, bins, t}, src, n, g, img, order, s);
-        if (form == kFormPoly) return launch_runs(ModeTofLm<kFormPoly, true>{p, bins, t}, src, n, g, img, order, s);
-        return launch_runs(ModeTofLm<kFormErf, true>{p, bins, t}, src, n, g, img, order, s);
-    }
-    if (form == kFormLut) return launch_runs(ModeTofLm<kFormLut>{p, bins, t}, src, n, g, img, order, s);
-    if (form == kFormPoly) return launch_runs(ModeTofLm<kFormPoly>{p, bins, t}, src, n, g, img, order, s);
-    return launch_runs(ModeTofLm<kFormErf>{p, bins, t}, src, n, g, img, order, s);
+    return back_tof_lm_runs(src, bins, n, g, t, img, p, order, s);
 }
 
 // Images per launch of the batched listmode back projection (each launch walks the events once)
 constexpr int kBackBatch = 16;
 
-hipError_t launch_back_tof_lm_batch(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g,
-                                    const TofK& t, float* imgs, int n_img, const float* p, const int32_t* order,
-                                    hipStream_t s) {
+static hipError_t back_tof_lm_batch_runs(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK& t,
+                                         float* imgs, int n_img, const float* p, const int32_t* order, hipStream_t s,
+                                         RunsOrTiles choice = {nullptr, 0}) {
     const int64_t nv = (int64_t)g.n[0] * g.n[1] * g.n[2];
     const int form = tof_form(t);
     const bool per = t.sig_ray || t.off_ray;
@@ -889,19 +896,35 @@ hipError_t launch_back_tof_lm_batch(const RaySrc& src, const int16_t* bins, int6
         const int cnt = (n_img - b0 < kBackBatch) ? (n_img - b0) : kBackBatch;
         float* im = imgs + (int64_t)b0 * nv;
         const float* pb = p + (int64_t)b0 * n;
+        auto runs = [&](const auto& m) { return launch_runs(m, src, n, g, im, order, s, cnt, nv, false, choice); };
         hipError_t e;
         if (per) {
-            if (form == kFormLut) e = launch_runs(ModeTofLm<kFormLut, true, true>{pb, bins, t}, src, n, g, im, order, s, cnt, nv);
-            else if (form == kFormPoly) e = launch_runs(ModeTofLm<kFormPoly, true, true>{pb, bins, t}, src, n, g, im, order, s, cnt, nv);
-            else e = launch_runs(ModeTofLm<kFormErf, true, true>{pb, bins, t}, src, n, g, im, order, s, cnt, nv);
+            if (form == kFormLut) e = runs(ModeTofLm<kFormLut, true, true>{pb, bins, t});
+            else if (form == kFormPoly) e = runs(ModeTofLm<kFormPoly, true, true>{pb, bins, t});
+            else e = runs(ModeTofLm<kFormErf, true, true>{pb, bins, t});
         } else {
-            if (form == kFormLut) e = launch_runs(ModeTofLm<kFormLut, false, true>{pb, bins, t}, src, n, g, im, order, s, cnt, nv);
-            else if (form == kFormPoly) e = launch_runs(ModeTofLm<kFormPoly, false, true>{pb, bins, t}, src, n, g, im, order, s, cnt, nv);
-            else e = launch_runs(ModeTofLm<kFormErf, false, true>{pb, bins, t}, src, n, g, im, order, s, cnt, nv);
+            if (form == kFormLut) e = runs(ModeTofLm<kFormLut, false, true>{pb, bins, t});
+            else if (form == kFormPoly) e = runs(ModeTofLm<kFormPoly, false, true>{pb, bins, t});
+            else e = runs(ModeTofLm<kFormErf, false, true>{pb, bins, t});
         }
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+hipError_t launch_back_tof_lm_batch(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g,
+                                    const TofK& t, float* imgs, int n_img, const float* p, const int32_t* order,
+                                    hipStream_t s) {
+    return back_tof_lm_batch_runs(src, bins, n, g, t, imgs, n_img, p, order, s);
+}
+
+hipError_t launch_back_runs_or_tiles(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK* t,
+                                     float* imgs, int n_img, const float* p, const int32_t* order, const int* changes,
+                                     int need, hipStream_t s) {
+    const RunsOrTiles choice{changes, need};
+    if (!bins) return launch_runs(ModeNonTof{p}, src, n, g, imgs, order, s, 1, 0, false, choice);
+    if (n_img == 1) return back_tof_lm_runs(src, bins, n, g, *t, imgs, p, order, s, choice);
+    return back_tof_lm_batch_runs(src, bins, n, g, *t, imgs, n_img, p, order, s, choice);
 }
 
 static int sino_block(int nb) { return nb <= 64 ? 256 : 64; }  // LDS tile <= 64 KiB

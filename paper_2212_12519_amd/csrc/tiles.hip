@@ -11,13 +11,31 @@ namespace ppmi {
 __global__ void k_tile_zero(TileWork w, int nt) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < nt) w.count[i] = 0;
-    if (i <= kTileImages) w.head[4 + i] = 0;
+    if (i <= kTileImages + 1) w.head[4 + i] = 0;
+}
+
+// Events of kProbes places of the processing order that lie on another transaxial line than the next one (in either
+// direction)
+constexpr int kProbes = 16384;
+
+__global__ void __launch_bounds__(256) k_tile_probe(RaySrc src, int64_t n, const int32_t* __restrict__ order, TileWork w) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    const int64_t q = min((int64_t)i * n / kProbes, n - 2);
+    const int64_t a = order ? order[q] : q, b = order ? order[q + 1] : q + 1;
+    bool same = false;
+    const float *s0, *e0, *s1, *e1;
+    if (a >= 0 && a < n && b >= 0 && b < n && src.ends(a, s0, e0) && src.ends(b, s1, e1))
+        same = (s0[0] == s1[0] && s0[1] == s1[1] && e0[0] == e1[0] && e0[1] == e1[1]) ||
+               (s0[0] == e1[0] && s0[1] == e1[1] && e0[0] == s1[0] && e0[1] == s1[1]);
+    const unsigned long long other = __ballot(!same);
+    if (__lane_id() == 0) atomicAdd(&w.head[5 + kTileImages], __popcll(other));
 }
 
 // Exclusive prefix sums over the tiles: every tile's first piece, and its first unit where a unit has at
 // most `per` pieces, per chosen so that about `units` units hold them all.
 __global__ void __launch_bounds__(1024) k_tile_scan(int nt, int units, TileWork w) {
     __shared__ int part[2][1024];
+    if (!w.on()) return;
     const int tid = threadIdx.x;
     const int each = (nt + 1023) / 1024, t_lo = min(nt, tid * each), t_hi = min(nt, t_lo + each);
     auto scan = [&](int v, int* buf) {  // inclusive prefix sum over the workgroup
@@ -59,6 +77,7 @@ __global__ void __launch_bounds__(1024) k_tile_scan(int nt, int units, TileWork 
 // stretch of each tile's range and writes them there.
 __global__ void __launch_bounds__(kBinBlock) k_tile_fill(TileGeom tg, int cnt, int rays, TileWork w) {
     extern __shared__ int hist[];
+    if (!w.on()) return;
     const int nt = tg.count();
     for (int t = threadIdx.x; t < nt; t += kBinBlock) hist[t] = 0;
     __syncthreads();
@@ -132,6 +151,25 @@ constexpr int64_t kTileEventsNonTof = 7'000'000;
 constexpr int64_t kTileEventsBatch = 20'000'000;
 constexpr int64_t kTileRaysList = 5'700'000;
 
+// Below those limits the sheets are still the better way where many events share a line.  Their time is about
+// kSheetsMs + line changes * flush + n e, the tiles' n t, and t - e (ns) hardly depends on the scanner: 0.28 with a TOF window of
+// 107 planes, 0.2 with 63, 0.62 without TOF in 215 planes, 0.13 an image of a batch; a flush of 215 x 71 entries takes 46
+// ns (66 without TOF).  So few events go to the tiles unasked, for more the changes are counted.  Presorted events of a
+// ring of 128 crystals (128 x 128 x 64, 6.9 M): tiles 2.25 ms (4.4 without TOF), sheets 1.66 (2.1); of 360 crystals (215 x
+// 215 x 71, 6.9 M) 3.0 (5.4) and 2.3 (2.5) ms, of 760 crystals 2.9 and 4.6 ms, 1 M of 360 crystals 0.47 and 1.5 ms.
+constexpr double kSheetsMs = 0.9;
+
+// TileWork::need for n events
+static int tile_need(int64_t n, const GeomK& g, const TofK* t, int n_img) {
+    if (g.n[2] > kSheetMaxW || n < 2) return 0;  // no sheets
+    double planes = g.n[0] > g.n[1] ? g.n[0] : g.n[1];
+    const double flush = (t ? 46.0 : 66.0) * planes * g.n[2] / (215.0 * 71.0);
+    if (t && !t->sig_ray) planes = std::fmin(planes, (t->hi - t->lo) / std::fmin(g.h[0], g.h[1]));
+    const double more = n_img > 1 ? 0.13 : t ? 0.12 + 0.0015 * planes : 0.3 + 0.0015 * planes;  // t - e, ns
+    const double share = (more - kSheetsMs * 1e6 / (double)n) / flush;  // line changes an event
+    return share <= 0.0 ? 0 : (int)std::fmin(std::ceil(share * kProbes), kProbes + 1.0);
+}
+
 static size_t up256(size_t b) { return (b + 255) & ~size_t(255); }
 
 static size_t tile_layout(int64_t events, int tiles, int bound, int n_img, char* base, TileWork& w) {
@@ -141,7 +179,8 @@ static size_t tile_layout(int64_t events, int tiles, int bound, int n_img, char*
         at += up256(bytes);
         return p;
     };
-    w.head = reinterpret_cast<int*>(take((5 + kTileImages) * 4));
+    w.need = 0;
+    w.head = reinterpret_cast<int*>(take((6 + kTileImages) * 4));
     w.count = reinterpret_cast<int*>(take((size_t)tiles * 4));
     w.first = reinterpret_cast<int*>(take((size_t)tiles * 4));
     w.cursor = reinterpret_cast<int*>(take((size_t)tiles * 4));
@@ -176,12 +215,13 @@ size_t tile_workspace_bytes(int64_t n, const GeomK& g, const TofK* t, bool listm
 
 template <class Mode>
 static hipError_t launch_tiles(const Mode& m, const RaySrc& src, int64_t n, const GeomK& g, const TofK* t, float* img,
-                               int n_img, const int32_t* order, void* ws, int cus, hipStream_t s) {
+                               int n_img, const int32_t* order, void* ws, int cus, hipStream_t s, int need,
+                               TileWork& w) {
     TileGeom tg;
     if (!tile_geom(g, tg)) return hipErrorInvalidValue;
-    TileWork w;
     const int nt = tg.count(), cnt = (int)n;
     tile_layout(n, nt, pieces_bound(g, tg, t), Mode::kBatch ? (n_img > 1 ? n_img : 2) : 1, static_cast<char*>(ws), w);
+    w.need = need;
     const size_t lds = tg.lds_bytes(), hist = (size_t)nt * 4;
     hipError_t e = hipFuncSetAttribute((const void*)k_tile_add<Mode>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds);
@@ -192,6 +232,7 @@ static hipError_t launch_tiles(const Mode& m, const RaySrc& src, int64_t n, cons
     const int rays = each < kBinRays ? each : kBinRays;
     const dim3 bins((unsigned)((cnt + kBinBlock * rays - 1) / (kBinBlock * rays)));
     hipLaunchKernelGGL(k_tile_zero, dim3((nt + 255) / 256), dim3(256), 0, s, w, nt);
+    if (need) hipLaunchKernelGGL(k_tile_probe, dim3(kProbes / 256), dim3(256), 0, s, src, n, order, w);
     hipLaunchKernelGGL(k_tile_bin<Mode>, bins, dim3(kBinBlock), hist, s, m, src, n, g, tg, img, order, rays, w, n_img,
                        stride);
     // about three units per CU: a unit's flush writes its whole tile (some 15 us at 320 G values/s for the
@@ -202,17 +243,29 @@ static hipError_t launch_tiles(const Mode& m, const RaySrc& src, int64_t n, cons
     return hipGetLastError();
 }
 
+// The tiles, and where it is open whether they pay the run/sheet kernel too, one of which then does nothing
+template <class Mode>
+static hipError_t launch_either(const Mode& m, const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g,
+                                const TofK* t, float* imgs, int n_img, const float* p, const int32_t* order, void* ws,
+                                int cus, hipStream_t s) {
+    TileWork w;
+    const int need = tile_need(n, g, t, n_img);
+    const hipError_t e = launch_tiles(m, src, n, g, t, imgs, n_img, order, ws, cus, s, need, w);
+    if (e != hipSuccess || !need) return e;
+    return launch_back_runs_or_tiles(src, bins, n, g, t, imgs, n_img, p, order, w.head + 5 + kTileImages, need, s);
+}
+
 template <int Form, bool PerRay>
 static hipError_t launch_tiles_lm(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK& t,
                                   float* imgs, int n_img, const float* p, const int32_t* order, void* ws, int cus,
                                   hipStream_t s) {
     if (n_img == 1)
-        return launch_tiles(ModeTofLm<Form, PerRay>{p, bins, t}, src, n, g, &t, imgs, 1, order, ws, cus, s);
+        return launch_either(ModeTofLm<Form, PerRay>{p, bins, t}, src, bins, n, g, &t, imgs, 1, p, order, ws, cus, s);
     const int64_t nv = (int64_t)g.n[0] * g.n[1] * g.n[2];
     for (int b = 0; b < n_img; b += kTileImages) {
-        const hipError_t e = launch_tiles(ModeTofLm<Form, PerRay, true>{p + (int64_t)b * n, bins, t}, src, n, g, &t,
-                                          imgs + b * nv, n_img - b < kTileImages ? n_img - b : kTileImages, order, ws,
-                                          cus, s);
+        const float* pb = p + (int64_t)b * n;
+        const hipError_t e = launch_either(ModeTofLm<Form, PerRay, true>{pb, bins, t}, src, bins, n, g, &t, imgs + b * nv,
+                                           n_img - b < kTileImages ? n_img - b : kTileImages, pb, order, ws, cus, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -221,7 +274,7 @@ static hipError_t launch_tiles_lm(const RaySrc& src, const int16_t* bins, int64_
 hipError_t launch_back_tiles(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK* t,
                              float* imgs, int n_img, const float* p, const int32_t* order, void* ws, int cus,
                              hipStream_t s) {
-    if (!bins) return launch_tiles(ModeNonTof{p}, src, n, g, nullptr, imgs, 1, order, ws, cus, s);
+    if (!bins) return launch_either(ModeNonTof{p}, src, nullptr, n, g, nullptr, imgs, 1, p, order, ws, cus, s);
     const int form = tof_form(*t);
     if (t->sig_ray || t->off_ray) {
         if (form == kFormLut) return launch_tiles_lm<kFormLut, true>(src, bins, n, g, *t, imgs, n_img, p, order, ws, cus, s);
@@ -236,11 +289,11 @@ hipError_t launch_back_tiles(const RaySrc& src, const int16_t* bins, int64_t n, 
 hipError_t launch_osem_tiles(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK& t,
                              const float* x, float bg, float* acc, void* ws, int cus, hipStream_t s) {
     const int form = tof_form(t);
-    if (form == kFormLut)
-        return launch_tiles(ModeOsem<kFormLut>{x, bins, bg, t}, src, n, g, &t, acc, 1, nullptr, ws, cus, s);
-    if (form == kFormPoly)
-        return launch_tiles(ModeOsem<kFormPoly>{x, bins, bg, t}, src, n, g, &t, acc, 1, nullptr, ws, cus, s);
-    return launch_tiles(ModeOsem<kFormErf>{x, bins, bg, t}, src, n, g, &t, acc, 1, nullptr, ws, cus, s);
+    TileWork w;
+    auto tiles = [&](const auto& m) { return launch_tiles(m, src, n, g, &t, acc, 1, nullptr, ws, cus, s, 0, w); };
+    if (form == kFormLut) return tiles(ModeOsem<kFormLut>{x, bins, bg, t});
+    if (form == kFormPoly) return tiles(ModeOsem<kFormPoly>{x, bins, bg, t});
+    return tiles(ModeOsem<kFormErf>{x, bins, bg, t});
 }
 
 }  // namespace ppmi

@@ -15,6 +15,7 @@
 // finite, is added to the image directly.
 //
 //   k_tile_zero    clears the per-tile counters
+//   k_tile_probe   (where it is open whether the tiles pay) counts the line changes from event to event
 //   k_tile_bin     one event per thread: ray setup, the event's record (64 B), its pieces counted per tile
 //                  (an LDS histogram per workgroup); rays along axis 2 are scattered directly
 //   k_tile_scan    one workgroup: first piece of every tile, and the work units (a tile's pieces split so
@@ -72,15 +73,17 @@ constexpr uint32_t kNoPlanes = 0xffffffffu;
 // The workspace's parts (device pointers)
 struct TileWork {
     int* head;    // [0] pieces, [1] units, [2] pieces per unit, [3] the weights' bound (float bits), [4 + b] largest |value| of image b (float
-                  // bits), then the next unit to take
+                  // bits), then the next unit to take, then the line changes that k_tile_probe found
     int* count;   // [tiles] pieces of a tile
     int* first;   // [tiles] its first piece
     int* cursor;  // [tiles] next free piece of the tile's range
-    int* unit0;   // [tiles + 1] its first unit
+    int* unit0;   // [tiles] its first unit
     TileRec* rec; // [events]
     uint2* piece; // [capacity] (record, k0 | (k1 - k0) << 16 | axis << 31)
     float* value; // [images][n] batch modes: cv times the event's value, in processing order
     int64_t capacity;
+    int need;     // fewest line changes among the probed events for which the tiles are the better way (0: not asked)
+    __device__ bool on() const { return need == 0 || head[5 + kTileImages] >= need; }
 };
 
 // The first plane after k (whose coordinate lies in `tile`) where the coordinate A0 + k dA has left the tile, at
@@ -139,6 +142,7 @@ __global__ void __launch_bounds__(kBinBlock) k_tile_bin(Mode m, RaySrc src, int6
     extern __shared__ int hist[];
     __shared__ float red[4];
     __shared__ unsigned top[kTileImages];
+    if (!w.on()) return;
     const int nt = tg.count();
     for (int t = threadIdx.x; t < nt; t += kBinBlock) hist[t] = 0;
     if (threadIdx.x < kTileImages) top[threadIdx.x] = 0;
@@ -253,6 +257,7 @@ template <class Mode>
 __global__ void __launch_bounds__(kAddBlock) k_tile_add(Mode m, int64_t n, GeomK g, TileGeom tg, TileWork w,
                                                         float* __restrict__ img, int n_img, int64_t img_stride) {
     extern __shared__ unsigned long long tile[];
+    if (!w.on()) return;
     typedef __attribute__((address_space(3))) unsigned long long lds_u64;
     const int T1 = tg.edge + 1, zs = tg.zs, nt = tg.count();
     const int total = T1 * T1 * zs;
