@@ -725,7 +725,10 @@ int pp_lm_osem_subset_batched(const pp_frame_desc_t* d_slots, int32_t n_slots, c
 
 size_t pp_lm_osem_frame_workspace_bytes(int64_t n_events, int32_t n_sub, const pp_image_t* geom, const pp_tof_t* tof) {
     if (n_events <= 0 || n_sub < 1) return 0;
-    return pp_back_lm_workspace_bytes((n_events + n_sub - 1) / n_sub, geom, tof, 1, 1);
+    // the subsets' two sizes: the fewer events can need the more, in one pass where the others take two
+    const int64_t most = (n_events + n_sub - 1) / n_sub, least = n_events / n_sub;
+    const size_t a = pp_back_lm_workspace_bytes(most, geom, tof, 1, 1);
+    return a == 0 ? 0 : std::max(a, pp_back_lm_workspace_bytes(least, geom, tof, 1, 1));
 }
 
 int pp_lm_osem_frame_ws(const pp_frame_desc_t* frame, const pp_image_t* geom, const pp_tof_t* tof, void* workspace,

@@ -8,10 +8,10 @@
 
 namespace ppmi {
 
-__global__ void k_tile_zero(TileWork w, int nt) {
+__global__ void k_tile_zero(TileWork w, int nt, bool first) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < nt) w.count[i] = 0;
-    if (i <= kTileImages + 1) w.head[4 + i] = 0;
+    if (i <= kTileImages + (first ? 1 : 0)) w.head[4 + i] = 0;  // (what k_tile_probe found holds for every pass)
 }
 
 // Events of kProbes places of the processing order that lie on another transaxial line than the next one (in either
@@ -195,13 +195,26 @@ static size_t tile_layout(int64_t events, int tiles, int bound, int n_img, char*
 
 constexpr int64_t kTileEventsMost = 40'000'000;
 
-// 0: a grid the tiles do not suit, or more events than their counts (32 bits) or 16 GB of workspace hold
+// Events of one pass over the tiles: as many as kTilePassBytes of workspace hold, in passes of equal size.  A pass costs
+// its launches and a flush of every tile, some 60 us beside the 5 ms and more that so many events take.
+constexpr size_t kTilePassBytes = size_t(4) << 30;
+
+static int64_t tile_pass(int64_t n, const TileGeom& tg, int bound, int n_img) {
+    TileWork w;
+    const size_t bytes = tile_layout(n, tg.count(), bound, n_img, nullptr, w);
+    const int64_t passes = (int64_t)((bytes + kTilePassBytes - 1) / kTilePassBytes);
+    return (n + passes - 1) / passes;
+}
+
+// 0: a grid the tiles do not suit, or more events than their counts (32 bits) or 16 GB of records and pieces hold
 size_t tile_bytes(int64_t n, const GeomK& g, const TofK* t, int n_img) {
     TileGeom tg;
     if (n <= 0 || n > kTileEventsMost || !tile_geom(g, tg)) return 0;
     TileWork w;
-    const size_t bytes = tile_layout(n, tg.count(), pieces_bound(g, tg, t), n_img, nullptr, w);
-    return w.capacity <= INT32_MAX && bytes <= (size_t(16) << 30) ? bytes : 0;
+    const int bound = pieces_bound(g, tg, t);
+    const size_t bytes = tile_layout(n, tg.count(), bound, n_img, nullptr, w);
+    if (w.capacity > INT32_MAX || bytes > (size_t(16) << 30)) return 0;
+    return tile_layout(tile_pass(n, tg, bound, n_img), tg.count(), bound, n_img, nullptr, w);
 }
 
 // Grids of more slices than a sheet holds have no other way than float atomics (12 M presorted TOF events, 160
@@ -213,44 +226,50 @@ size_t tile_workspace_bytes(int64_t n, const GeomK& g, const TofK* t, bool listm
     return n <= most ? tile_bytes(n, g, t, n_img) : 0;
 }
 
+// all_img: the images of the whole call, for which the workspace was laid out
 template <class Mode>
 static hipError_t launch_tiles(const Mode& m, const RaySrc& src, int64_t n, const GeomK& g, const TofK* t, float* img,
-                               int n_img, const int32_t* order, void* ws, int cus, hipStream_t s, int need,
+                               int n_img, int all_img, const int32_t* order, void* ws, int cus, hipStream_t s, int need,
                                TileWork& w) {
     TileGeom tg;
     if (!tile_geom(g, tg)) return hipErrorInvalidValue;
-    const int nt = tg.count(), cnt = (int)n;
-    tile_layout(n, nt, pieces_bound(g, tg, t), Mode::kBatch ? (n_img > 1 ? n_img : 2) : 1, static_cast<char*>(ws), w);
+    const int nt = tg.count(), bound = pieces_bound(g, tg, t);
+    const int64_t pass = tile_pass(n, tg, bound, all_img);
+    tile_layout(pass, nt, bound, all_img, static_cast<char*>(ws), w);
     w.need = need;
     const size_t lds = tg.lds_bytes(), hist = (size_t)nt * 4;
     hipError_t e = hipFuncSetAttribute((const void*)k_tile_add<Mode>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds);
     if (e != hipSuccess) return e;
     const int64_t stride = (int64_t)g.n[0] * g.n[1] * g.n[2];
-    // four workgroups per CU where there are events for them, up to kBinRays events per thread
-    const int each = (cnt + 4 * cus * kBinBlock - 1) / (4 * cus * kBinBlock);
-    const int rays = each < kBinRays ? each : kBinRays;
-    const dim3 bins((unsigned)((cnt + kBinBlock * rays - 1) / (kBinBlock * rays)));
-    hipLaunchKernelGGL(k_tile_zero, dim3((nt + 255) / 256), dim3(256), 0, s, w, nt);
-    if (need) hipLaunchKernelGGL(k_tile_probe, dim3(kProbes / 256), dim3(256), 0, s, src, n, order, w);
-    hipLaunchKernelGGL(k_tile_bin<Mode>, bins, dim3(kBinBlock), hist, s, m, src, n, g, tg, img, order, rays, w, n_img,
-                       stride);
-    // about three units per CU: a unit's flush writes its whole tile (some 15 us at 320 G values/s for the
-    // chip), more units balance better (400 k events: 158 us of adding with 2 or 3 per CU, 206 with 6)
-    hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(1024), 0, s, nt, 3 * cus, w);
-    hipLaunchKernelGGL(k_tile_fill, bins, dim3(kBinBlock), hist, s, tg, cnt, rays, w);
-    hipLaunchKernelGGL(k_tile_add<Mode>, dim3(cus), dim3(kAddBlock), lds, s, m, n, g, tg, w, img, n_img, stride);
+    for (int64_t first = 0; first < n; first += pass) {
+        const int cnt = (int)(n - first < pass ? n - first : pass);
+        // four workgroups per CU where there are events for them, up to kBinRays events per thread
+        const int each = (cnt + 4 * cus * kBinBlock - 1) / (4 * cus * kBinBlock);
+        const int rays = each < kBinRays ? each : kBinRays;
+        const dim3 bins((unsigned)((cnt + kBinBlock * rays - 1) / (kBinBlock * rays)));
+        hipLaunchKernelGGL(k_tile_zero, dim3((nt + 255) / 256), dim3(256), 0, s, w, nt, first == 0);
+        if (need && first == 0) hipLaunchKernelGGL(k_tile_probe, dim3(kProbes / 256), dim3(256), 0, s, src, n, order, w);
+        hipLaunchKernelGGL(k_tile_bin<Mode>, bins, dim3(kBinBlock), hist, s, m, src, n, g, tg, img, order, first, cnt, rays,
+                           w, n_img, stride);
+        // about three units per CU: a unit's flush writes its whole tile (some 15 us at 320 G values/s for the
+        // chip), more units balance better (400 k events: 158 us of adding with 2 or 3 per CU, 206 with 6)
+        hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(1024), 0, s, nt, 3 * cus, w);
+        hipLaunchKernelGGL(k_tile_fill, bins, dim3(kBinBlock), hist, s, tg, cnt, rays, w);
+        hipLaunchKernelGGL(k_tile_add<Mode>, dim3(cus), dim3(kAddBlock), lds, s, m, (int64_t)cnt, g, tg, w, img, n_img,
+                           stride);
+    }
     return hipGetLastError();
 }
 
 // The tiles, and where it is open whether they pay the run/sheet kernel too, one of which then does nothing
 template <class Mode>
 static hipError_t launch_either(const Mode& m, const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g,
-                                const TofK* t, float* imgs, int n_img, const float* p, const int32_t* order, void* ws,
-                                int cus, hipStream_t s) {
+                                const TofK* t, float* imgs, int n_img, int all_img, const float* p,
+                                const int32_t* order, void* ws, int cus, hipStream_t s) {
     TileWork w;
-    const int need = tile_need(n, g, t, n_img);
-    const hipError_t e = launch_tiles(m, src, n, g, t, imgs, n_img, order, ws, cus, s, need, w);
+    const int need = tile_need(n, g, t, all_img);
+    const hipError_t e = launch_tiles(m, src, n, g, t, imgs, n_img, all_img, order, ws, cus, s, need, w);
     if (e != hipSuccess || !need) return e;
     return launch_back_runs_or_tiles(src, bins, n, g, t, imgs, n_img, p, order, w.head + 5 + kTileImages, need, s);
 }
@@ -260,12 +279,13 @@ static hipError_t launch_tiles_lm(const RaySrc& src, const int16_t* bins, int64_
                                   float* imgs, int n_img, const float* p, const int32_t* order, void* ws, int cus,
                                   hipStream_t s) {
     if (n_img == 1)
-        return launch_either(ModeTofLm<Form, PerRay>{p, bins, t}, src, bins, n, g, &t, imgs, 1, p, order, ws, cus, s);
+        return launch_either(ModeTofLm<Form, PerRay>{p, bins, t}, src, bins, n, g, &t, imgs, 1, 1, p, order, ws, cus, s);
     const int64_t nv = (int64_t)g.n[0] * g.n[1] * g.n[2];
     for (int b = 0; b < n_img; b += kTileImages) {
         const float* pb = p + (int64_t)b * n;
         const hipError_t e = launch_either(ModeTofLm<Form, PerRay, true>{pb, bins, t}, src, bins, n, g, &t, imgs + b * nv,
-                                           n_img - b < kTileImages ? n_img - b : kTileImages, pb, order, ws, cus, s);
+                                           n_img - b < kTileImages ? n_img - b : kTileImages, n_img, pb, order, ws, cus,
+                                           s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -274,7 +294,7 @@ static hipError_t launch_tiles_lm(const RaySrc& src, const int16_t* bins, int64_
 hipError_t launch_back_tiles(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK* t,
                              float* imgs, int n_img, const float* p, const int32_t* order, void* ws, int cus,
                              hipStream_t s) {
-    if (!bins) return launch_either(ModeNonTof{p}, src, nullptr, n, g, nullptr, imgs, 1, p, order, ws, cus, s);
+    if (!bins) return launch_either(ModeNonTof{p}, src, nullptr, n, g, nullptr, imgs, 1, 1, p, order, ws, cus, s);
     const int form = tof_form(*t);
     if (t->sig_ray || t->off_ray) {
         if (form == kFormLut) return launch_tiles_lm<kFormLut, true>(src, bins, n, g, *t, imgs, n_img, p, order, ws, cus, s);
@@ -290,7 +310,7 @@ hipError_t launch_osem_tiles(const RaySrc& src, const int16_t* bins, int64_t n, 
                              const float* x, float bg, float* acc, void* ws, int cus, hipStream_t s) {
     const int form = tof_form(t);
     TileWork w;
-    auto tiles = [&](const auto& m) { return launch_tiles(m, src, n, g, &t, acc, 1, nullptr, ws, cus, s, 0, w); };
+    auto tiles = [&](const auto& m) { return launch_tiles(m, src, n, g, &t, acc, 1, 1, nullptr, ws, cus, s, 0, w); };
     if (form == kFormLut) return tiles(ModeOsem<kFormLut>{x, bins, bg, t});
     if (form == kFormPoly) return tiles(ModeOsem<kFormPoly>{x, bins, bg, t});
     return tiles(ModeOsem<kFormErf>{x, bins, bg, t});

@@ -80,7 +80,7 @@ struct TileWork {
     int* unit0;   // [tiles] its first unit
     TileRec* rec; // [events]
     uint2* piece; // [capacity] (record, k0 | (k1 - k0) << 16 | axis << 31)
-    float* value; // [images][n] batch modes: cv times the event's value, in processing order
+    float* value; // [images][events of the pass] batch modes: cv times the event's value, in processing order
     int64_t capacity;
     int need;     // fewest line changes among the probed events for which the tiles are the better way (0: not asked)
     __device__ bool on() const { return need == 0 || head[5 + kTileImages] >= need; }
@@ -133,12 +133,13 @@ __device__ __forceinline__ void tile_walk(const TileGeom& tg, double U0, double 
     }
 }
 
-// The events in processing order -> records and per-tile counts.  Batch modes: the
+// The cnt events from place `first` of the processing order on -> records and per-tile counts.  Batch modes: the
 // record's cv is for a value of 1; n_img images (img_stride apart) receive the rays along axis 2.
 template <class Mode>
 __global__ void __launch_bounds__(kBinBlock) k_tile_bin(Mode m, RaySrc src, int64_t n, GeomK g, TileGeom tg,
                                                         float* __restrict__ img, const int32_t* __restrict__ order,
-                                                        int rays, TileWork w, int n_img, int64_t img_stride) {
+                                                        int64_t first, int cnt, int rays, TileWork w, int n_img,
+                                                        int64_t img_stride) {
     extern __shared__ int hist[];
     __shared__ float red[4];
     __shared__ unsigned top[kTileImages];
@@ -154,10 +155,10 @@ __global__ void __launch_bounds__(kBinBlock) k_tile_bin(Mode m, RaySrc src, int6
     const unsigned block = Mode::kReads ? xcd_block() : blockIdx.x;
     for (int e = 0; e < rays; ++e) {
         const int q = (block * rays + e) * kBinBlock + threadIdx.x;
-        if ((block * rays + e) * kBinBlock >= n) break;  // block-uniform
+        if ((int64_t)(block * rays + e) * kBinBlock >= cnt) break;  // block-uniform
         int64_t l = -1;
-        if (q < n) {
-            l = order ? (int64_t)order[q] : q;
+        if (q < cnt) {
+            l = order ? (int64_t)order[first + q] : first + q;
             if (l < 0 || l >= n) l = -1;
         }
         RayK r;
@@ -188,7 +189,7 @@ __global__ void __launch_bounds__(kBinBlock) k_tile_bin(Mode m, RaySrc src, int6
             float c = ok ? cv : 0.0f;
             if constexpr (Mode::kBatch) {
                 c = ok ? cv * m.value(l, b, n) : 0.0f;
-                if (q < n) w.value[b * n + q] = c;
+                if (q < cnt) w.value[(int64_t)b * cnt + q] = c;
             }
             float a = m.mag(c, ax) * wb;
             if (!(a <= FLT_MAX)) a = 0.0f;
@@ -196,7 +197,7 @@ __global__ void __launch_bounds__(kBinBlock) k_tile_bin(Mode m, RaySrc src, int6
             for (int off = 32; off > 0; off >>= 1) a = fmaxf(a, __shfl_xor(a, off, 64));
             if (__lane_id() == 0) atomicMax(&top[b], __float_as_uint(a));
         }
-        if (q < n) {
+        if (q < cnt) {
             TileRec rec{};
             rec.kk = kNoPlanes;
             if (ok && !direct) {
@@ -254,7 +255,7 @@ __device__ inline void tile_direct(float* __restrict__ img, const GeomK& g, bool
 // The lanes of a wave take pieces of one length that lie far apart in the unit (neighbouring events,
 // which a presort puts on nearly the same line, would meet in the same LDS entries).
 template <class Mode>
-__global__ void __launch_bounds__(kAddBlock) k_tile_add(Mode m, int64_t n, GeomK g, TileGeom tg, TileWork w,
+__global__ void __launch_bounds__(kAddBlock) k_tile_add(Mode m, int64_t cnt_events, GeomK g, TileGeom tg, TileWork w,
                                                         float* __restrict__ img, int n_img, int64_t img_stride) {
     extern __shared__ unsigned long long tile[];
     if (!w.on()) return;
@@ -342,7 +343,7 @@ __global__ void __launch_bounds__(kAddBlock) k_tile_add(Mode m, int64_t n, GeomK
             float value[kEach];
             if constexpr (Mode::kBatch)
 #pragma unroll
-                for (int j = 0; j < kEach; ++j) value[j] = w.value[b * n + pcs[j].x];
+                for (int j = 0; j < kEach; ++j) value[j] = w.value[b * cnt_events + pcs[j].x];
             TileRec next = w.rec[pcs[0].x];
 #pragma unroll
             for (int j = 0; j < kEach; ++j) {

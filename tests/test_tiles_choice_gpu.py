@@ -70,3 +70,65 @@ def test_choice(gpu, mode, grouped):
     want = oracle.back(xs, xe, o, h, DIM, want_p) if tof is None else oracle.back_tof_lm(xs, xe, o, h, DIM, tofd(*tof), bins, want_p)
     for b in range(nb):
         assert rel_l2(img[b].cpu().numpy(), want * (b + 1)) <= BACK_TOL, b
+
+
+@pytest.mark.parametrize("n_img", [1, 2, 18])
+def test_passes_over_the_events(gpu, n_img):
+    """More events than one pass's workspace (4 GiB) holds: several passes, the last one shorter, in one workspace.  Most
+    events miss the grid of more than 128 slices, so that only their records take time."""
+    lib = gpu.load()
+    dim, vox = (40, 36, 140), (6.0, 6.0, 1.5)
+    G, T = gpu.ImageGeom(dim, vox), gpu.TofParams(28.0, 24.8, 3.0, 9)
+    size = lambda k: lib.pp_back_lm_workspace_bytes(k, G.c(), T.c(), 1, n_img)  # noqa: E731
+    one = next(k for k in range(1_000_000, 40_000_000, 500_000) if size(k + 500_000) < size(k))  # the most of one pass
+    n = one + 700_001
+    assert 0 < size(n) < size(one) <= (4 << 30) + (1 << 20)
+    rng = np.random.default_rng(72)
+    o, h = [f32(-(d - 1) / 2 * v) for d, v in zip(dim, vox)], [f32(v) for v in vox]
+    k = 20_000
+    half = 0.5 * np.asarray(dim) * np.asarray(vox)
+    xs = rng.uniform(-1.0, 1.0, (k, 3)) * half * [0.4, 0.4, 0.9]
+    u = rng.normal(size=(k, 3)) * [1.0, 1.0, 0.2]
+    u /= np.linalg.norm(u, axis=1, keepdims=True)
+    xs, xe = (xs - 400.0 * u).astype(np.float32), (xs + 400.0 * u).astype(np.float32)
+    at = np.sort(rng.choice(n, k, replace=False))
+    at[0], at[-1] = 0, n - 1
+    bins, p = rng.integers(0, 9, k).astype(np.int16), rng.uniform(0.5, 1.5, k).astype(np.float32)
+    dev = torch.device("cuda")
+    t = lambda a: torch.from_numpy(a).to(dev)  # noqa: E731
+    dxs, dxe = (torch.full((n, 3), v, device=dev) for v in (1e4, 1.1e4))
+    dp, db, w = torch.ones((n_img, n), device=dev), torch.zeros(n, dtype=torch.int16, device=dev), t(at)
+    dxs[w], dxe[w], db[w] = t(xs), t(xe), t(bins)
+    for b in range(n_img):
+        dp[b, w] = t(p) * (b + 1)
+    img = torch.zeros((n_img, *dim), device=dev)
+    from paper_2212_12519_amd._lib import check, ptr, stream_of
+    ws = torch.empty(size(n), dtype=torch.uint8, device=dev)
+    check(lib.pp_back_lm_ws(ptr(dxs), ptr(dxe), 0, None, ptr(db), n, G.c(), T.c(n), ptr(img), n_img, ptr(dp), None, ptr(ws),
+                            ws.numel(), stream_of(img)))
+    want = oracle.back_tof_lm(xs, xe, o, h, dim, tofd(28.0, 24.8, 3.0, 9), bins, p)
+    for b in range(n_img):
+        assert rel_l2(img[b].cpu().numpy(), want * (b + 1)) <= 1e-5, b
+
+
+def test_without_memory_for_a_workspace(gpu):
+    """Where the workspace cannot be had the calls take their way without one, with the same result."""
+    xs, xe, rng = _events(400, 300_000, 73)
+    n, dev = xs.shape[0], torch.device("cuda")
+    o, h = [f32(-(d - 1) / 2 * v) for d, v in zip(DIM, VOX)], [f32(v) for v in VOX]
+    p = rng.uniform(0.5, 1.5, n).astype(np.float32)
+    t = lambda a: torch.from_numpy(a).to(dev)  # noqa: E731
+    G, dxs, dxe, dp = gpu.ImageGeom(DIM, VOX), t(xs), t(xe), t(p)
+    order, img = t(rng.permutation(n).astype(np.int32)), torch.zeros(DIM, device=dev)
+    need = gpu.load().pp_back_lm_workspace_bytes(n, G.c(), None, 1, 1)
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    assert need > 8 << 20
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (4 << 20)) / total)
+    try:
+        gpu.pp_back(dxs, dxe, G, img, dp, order)
+        peak = torch.cuda.memory_reserved()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert peak < need
+    assert rel_l2(img.cpu().numpy(), oracle.back(xs, xe, o, h, DIM, p)) <= BACK_TOL
