@@ -725,16 +725,24 @@ hipError_t launch_fwd(const RaySrc& src, int64_t n, const GeomK& g, const float*
     return hipGetLastError();
 }
 
-// Back projections of ray lists go through the run/sheet kernel (sheet.hpp); Left: only what k_back_lines leaves of a
-// list without an order.
-template <bool Left = false, class Mode>
+// Back projections of ray lists go through the run/sheet kernel (sheet.hpp): kLeftRuns: only what k_back_lines leaves of a
+// list without an order; kRunsOrTiles: where the device has not chosen the tiles.
+enum Runs : int { kAllRuns, kLeftRuns, kRunsOrTiles };
+
+struct RunsOrTiles {
+    const int* changes;  // the tiles where *changes >= need
+    int need;
+};
+
+template <Runs Kind = kAllRuns, class Mode>
 static hipError_t launch_runs(const Mode& m, const RaySrc& src, int64_t n, const GeomK& g, float* img,
                               const int32_t* order, hipStream_t s, int n_img = 1, int64_t img_stride = 0,
                               bool regular = false, RunsOrTiles choice = {nullptr, 0}) {
     const int nw = (g.n[2] <= kSheetMaxW) ? g.n[2] : 0;
     const size_t lds = SheetLayout::bytes(nw, g);
     const void* k;
-    if constexpr (Left) k = (const void*)k_back_runs_left<Mode>;
+    if constexpr (Kind == kLeftRuns) k = (const void*)k_back_runs_left<Mode>;
+    else if constexpr (Kind == kRunsOrTiles) k = (const void*)k_back_runs_else<Mode>;
     else k = (const void*)k_back_runs<Mode>;
     hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
@@ -742,15 +750,18 @@ static hipError_t launch_runs(const Mode& m, const RaySrc& src, int64_t n, const
     const int cus = device_cus();
     int64_t groups = (n + (int64_t)kSheetBlock * 4 * cus - 1) / ((int64_t)kSheetBlock * 4 * cus);
     groups = groups < 1 ? 1 : (groups > kSheetGroups ? kSheetGroups : groups);
-    if (Left && n > (int64_t)kSheetGroups * kSheetBlock * 16 * cus)
+    if (Kind == kLeftRuns && n > (int64_t)kSheetGroups * kSheetBlock * 16 * cus)
         groups = n > (int64_t)kLeftGroups * kSheetBlock * 16 * cus ? kLeftGroups : kLeftGroups / 2;
     const dim3 grid(grid_for(n, kSheetBlock * groups));
-    if constexpr (Left)
+    if constexpr (Kind == kLeftRuns)
         hipLaunchKernelGGL(k_back_runs_left<Mode>, grid, dim3(kSheetBlock), lds, s, m, src, n, g, img, nw, (int)groups,
                            regular);
+    else if constexpr (Kind == kRunsOrTiles)
+        hipLaunchKernelGGL(k_back_runs_else<Mode>, grid, dim3(kSheetBlock), lds, s, m, src, n, g, img, order, nw, (int)groups,
+                           n_img, img_stride, choice.changes, choice.need);
     else
         hipLaunchKernelGGL(k_back_runs<Mode>, grid, dim3(kSheetBlock), lds, s, m, src, n, g, img, order, nw, (int)groups,
-                           n_img, img_stride, choice);
+                           n_img, img_stride);
     return hipGetLastError();
 }
 
@@ -763,7 +774,7 @@ static hipError_t launch_back_lines(const LineMode& lm, const Mode& m, const Ray
     hipError_t e = hipFuncSetAttribute((const void*)k_back_lines<LineMode>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds);
     if (e != hipSuccess) return e;
-    e = launch_runs<true>(m, src, n, g, img, nullptr, s, 1, 0, LineMode::kRegular);
+    e = launch_runs<kLeftRuns>(m, src, n, g, img, nullptr, s, 1, 0, LineMode::kRegular);
     if (e != hipSuccess) return e;
     const int groups = line_groups_of(n, kLineBlock, 16384);
     hipLaunchKernelGGL(k_back_lines<LineMode>, dim3(grid_for(n, kLineBlock * groups)), dim3(kLineBlock), lds, s, lm, src, n,
@@ -865,11 +876,12 @@ hipError_t launch_fwd_tof_lm_batch(const RaySrc& src, const int16_t* bins, int64
     return hipSuccess;
 }
 
+template <Runs Kind = kAllRuns>
 static hipError_t back_tof_lm_runs(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK& t,
                                    float* img, const float* p, const int32_t* order, hipStream_t s,
                                    RunsOrTiles choice = {nullptr, 0}) {
     const int form = tof_form(t);
-    auto runs = [&](const auto& m) { return launch_runs(m, src, n, g, img, order, s, 1, 0, false, choice); };
+    auto runs = [&](const auto& m) { return launch_runs<Kind>(m, src, n, g, img, order, s, 1, 0, false, choice); };
     if (t.sig_ray || t.off_ray) {
         if (form == kFormLut) return runs(ModeTofLm<kFormLut, true>{p, bins, t});
         if (form == kFormPoly) return runs(ModeTofLm<kFormPoly, true>{p, bins, t});
@@ -888,6 +900,7 @@ hipError_t launch_back_tof_lm(const RaySrc& src, const int16_t* bins, int64_t n,
 // Images per launch of the batched listmode back projection (each launch walks the events once)
 constexpr int kBackBatch = 16;
 
+template <Runs Kind = kAllRuns>
 static hipError_t back_tof_lm_batch_runs(const RaySrc& src, const int16_t* bins, int64_t n, const GeomK& g, const TofK& t,
                                          float* imgs, int n_img, const float* p, const int32_t* order, hipStream_t s,
                                          RunsOrTiles choice = {nullptr, 0}) {
@@ -898,7 +911,7 @@ static hipError_t back_tof_lm_batch_runs(const RaySrc& src, const int16_t* bins,
         const int cnt = (n_img - b0 < kBackBatch) ? (n_img - b0) : kBackBatch;
         float* im = imgs + (int64_t)b0 * nv;
         const float* pb = p + (int64_t)b0 * n;
-        auto runs = [&](const auto& m) { return launch_runs(m, src, n, g, im, order, s, cnt, nv, false, choice); };
+        auto runs = [&](const auto& m) { return launch_runs<Kind>(m, src, n, g, im, order, s, cnt, nv, false, choice); };
         hipError_t e;
         if (per) {
             if (form == kFormLut) e = runs(ModeTofLm<kFormLut, true, true>{pb, bins, t});
@@ -924,9 +937,9 @@ hipError_t launch_back_runs_or_tiles(const RaySrc& src, const int16_t* bins, int
                                      float* imgs, int n_img, const float* p, const int32_t* order, const int* changes,
                                      int need, hipStream_t s) {
     const RunsOrTiles choice{changes, need};
-    if (!bins) return launch_runs(ModeNonTof{p}, src, n, g, imgs, order, s, 1, 0, false, choice);
-    if (n_img == 1) return back_tof_lm_runs(src, bins, n, g, *t, imgs, p, order, s, choice);
-    return back_tof_lm_batch_runs(src, bins, n, g, *t, imgs, n_img, p, order, s, choice);
+    if (!bins) return launch_runs<kRunsOrTiles>(ModeNonTof{p}, src, n, g, imgs, order, s, 1, 0, false, choice);
+    if (n_img == 1) return back_tof_lm_runs<kRunsOrTiles>(src, bins, n, g, *t, imgs, p, order, s, choice);
+    return back_tof_lm_batch_runs<kRunsOrTiles>(src, bins, n, g, *t, imgs, n_img, p, order, s, choice);
 }
 
 static int sino_block(int nb) { return nb <= 64 ? 256 : 64; }  // LDS tile <= 64 KiB

@@ -729,22 +729,25 @@ __device__ void back_runs_chunk(const Mode& m, RaySrc src, int64_t n,
     __syncthreads();  // the LDS may be reused by the caller
 }
 
-// A launch of two of which one is to work, by what a kernel before them counted (*changes >= need: the tiles, tiles.hpp;
-// changes nullptr: no choice)
-struct RunsOrTiles {
-    const int* changes;
-    int need;
-    __device__ bool tiles() const { return changes && *changes >= need; }
-};
-
 // (batch modes: n_img images at img + b * img_stride, values p[b][l])
 template <class Mode>
 __global__ void __launch_bounds__(kSheetBlock) k_back_runs(Mode m, RaySrc src, int64_t n, GeomK g,
                                                           float* __restrict__ img, const int32_t* __restrict__ order,
-                                                          int nw_lds, int groups, int n_img, int64_t img_stride,
-                                                          RunsOrTiles choice) {
+                                                          int nw_lds, int groups, int n_img, int64_t img_stride) {
     extern __shared__ double smem[];
-    if (choice.tiles()) return;
+    const int64_t chunk0 = (int64_t)blockIdx.x * groups * kSheetBlock;
+    back_runs_chunk(m, src, n, g, img, order, nw_lds, groups, chunk0, smem, n_img, img_stride);
+}
+
+// The same where a kernel before it has not given the work to the tiles (tiles.hpp): *changes < need.  (A kernel of its own:
+// the look at its arguments is 2 of the 41 us of 64,000 rays.)
+template <class Mode>
+__global__ void __launch_bounds__(kSheetBlock) k_back_runs_else(Mode m, RaySrc src, int64_t n, GeomK g,
+                                                               float* __restrict__ img, const int32_t* __restrict__ order,
+                                                               int nw_lds, int groups, int n_img, int64_t img_stride,
+                                                               const int* __restrict__ changes, int need) {
+    extern __shared__ double smem[];
+    if (*changes >= need) return;
     const int64_t chunk0 = (int64_t)blockIdx.x * groups * kSheetBlock;
     back_runs_chunk(m, src, n, g, img, order, nw_lds, groups, chunk0, smem, n_img, img_stride);
 }
