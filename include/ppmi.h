@@ -37,8 +37,10 @@
  *     or a tabulated kernel (pp_tof_t.lut).
  *   Pointers: every array argument is a DEVICE pointer owned by the caller;
  *     the geometry / TOF structs are HOST pointers read during the call.
- *     The library allocates nothing and keeps no state between calls (one
- *     exception: the per-GPU workspace of pp_lm_presort_noalloc).
+ *     The library allocates no device memory and keeps no results between calls.
+ *     It holds the per-GPU workspace of pp_lm_presort_noalloc, and on each host
+ *     thread the polynomials fitted to the last four TOF kernels (some 4 KB, by
+ *     their bin width, sigma and truncation).
  *   Streams: `stream` is a hipStream_t (NULL = the default stream).  Calls
  *     are asynchronous: they enqueue kernels and return.  Calls on different
  *     streams are independent.  Every call may be captured into a HIP graph.
@@ -221,19 +223,22 @@ int pp_back_tof_lm_batch(const float* xstart, const float* xend, const int16_t* 
                          const int32_t* order, void* stream);
 
 /* Bytes of device memory pp_back_lm_ws needs for n events and n_img images of this grid (tof NULL: non-TOF), 0 where
- * the call is better served by pp_back, pp_back_tof_lm or their variants (many events per transaxial
- * line, or a grid the tiles do not suit; invalid arguments also give 0).  listmode 0: the rays are a
- * sinogram's or another list of whole lines.  Host only. */
+ * the call is better served by pp_back, pp_back_tof_lm or their variants (too many events, or a grid the
+ * tiles do not suit; invalid arguments also give 0).  At most about 4 GiB: more events share a workspace in several
+ * passes, so that fewer events may need more.  listmode 0: the rays are a sinogram's or another list of whole
+ * lines.  Host only. */
 size_t pp_back_lm_workspace_bytes(int64_t n_events, const pp_image_t* geom, const pp_tof_t* tof, int32_t listmode,
                                    int32_t n_img);
 
 /* The listmode back projections (Sec. 2.2) with a caller workspace (16-byte aligned, at least
  * pp_back_lm_workspace_bytes(n_events, geom, tof, ...) bytes, else PP_EINVAL_N): the events' planes are
  * collected per image tile and added up in LDS, so that the events need no order and sparse lines
- * cost no more than dense ones.  Same results as pp_back (tof_bin NULL, tof unused),
+ * cost no more than dense ones.  From some millions of events on, lists that hold hundreds of events per line (counted on
+ * the device) go through the kernel of pp_back instead.  Same results as pp_back (tof_bin NULL, tof unused),
  * pp_back_tof_lm, pp_back_tof_lm_batch (n_img images and value arrays; n_img <= 1 without TOF) or, with
  * pair != NULL, their crystal-index forms (xstart the crystal table, xend unused), up to the order and
- * rounding of the sums (float64 inside a tile).  The workspace is free for other use in stream order. */
+ * rounding of the sums: inside a tile 64-bit fixed point, in which a piece of an event's line keeps at least 20 bits
+ * of its largest value (smaller pieces are added to the image as floats).  The workspace is free for other use in stream order. */
 int pp_back_lm_ws(const float* xstart, const float* xend, int32_t n_crystals, const int32_t* pair,
                   const int16_t* tof_bin, int64_t n_events, const pp_image_t* geom, const pp_tof_t* tof, float* imgs,
                   int32_t n_img, const float* p, const int32_t* order, void* workspace, size_t workspace_bytes,

@@ -4,9 +4,9 @@
 // The rays of a line add their samples to an LDS sheet (planes x slices, 32-bit fixed point, as in sheet.hpp: a
 // power-of-two scale from the run's bound, rounding remainders carried along the ray), which is then added
 // to the line's two image columns per plane.  With a ray per lane a sample takes its two LDS adds and some 15
-// instructions (a line's rays differ in their slices, so the lanes of a plane mostly meet different entries);
-// the run/sheet kernel's half-wave per ray needs as many again to read, bound and place every ray, which
-// pays for short runs only.
+// instructions (in a sinogram neighbouring rays differ in their slices, so the lanes of a plane mostly meet different
+// entries); the run/sheet kernel's half-wave per ray needs as many again to read, bound and place every ray, which
+// pays for short runs and for rays of nearly the same slices (back_lines_group).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -21,7 +21,7 @@ namespace ppmi {
 // not is preceded by a flush.  Values are left to the direct scatter below kSheetBits + what coarsening may still take:
 // the bits that sheet.hpp keeps at least.  The beginning of a line that goes on in the next group is scaled with room
 // for that group.  (A first run scaled to 28 bits, without coarsening, gave TOF sinograms with values over three decades
-// 2.9e-7 against float64 where k_back_runs gives 1.7e-7; now 1.2 to 1.6e-7.  335 M LORs: 22.9 -> 23.2 ms.)
+// 2.9e-7 against float64 where k_back_runs gives 1.7e-7; now 1.2 to 1.6e-7.  335 M LORs: 22.9 -> 23.5 ms.)
 constexpr int kLineCoarse = 3;
 
 // Every word of the sheet divided by 2^sft and rounded, the remainder carried into the thread's next word (every thread
@@ -328,7 +328,7 @@ __global__ void __launch_bounds__(kLineBlock, 4) k_back_lines(Mode m, RaySrc src
         }
         // Rays left out of their run's sheet (values of 1e-6 of the run's sum, as at a body's rim): the lanes of the
         // wave take a ray's planes.  With the wave's combined scatter for one such ray the clinical sinogram of a
-        // phantom (335 M LORs) took 38.3 ms, with lanes on its planes 19.7 ms (with TOF 82 and 59.8 ms).
+        // phantom (335 M LORs) took 38.3 ms, with lanes on its planes 19.7 ms, now 21.0 (with TOF 82 and 59.8, now 61.1).
         while (const unsigned long long some = __ballot(todo)) {
             if (__popcll(some) > kLineApart) break;
             const int j = __builtin_amdgcn_readfirstlane(__ffsll((long long)some) - 1);

@@ -21,7 +21,7 @@ constexpr int kLineBlock = 512;  // rays of a group of k_fwd_lines and k_back_li
 // rays a line: 0.58 ms with a sheet for every run, 0.28 ms by gathers); where the groups have long runs but at
 // their ends (line_group): what the sheet's entries cost
 constexpr int kLineMinRun = 96, kLineMinRunTof = 224;
-constexpr int kLineHeads = 32;  // a group with more runs than its rays / kLineHeads gathers them all
+constexpr int kLineHeads = 32;  // forward: a group with more runs than its rays / kLineHeads gathers them all
 
 // What a group of kLineBlock rays looks like at its sixteen points, by their transaxial end points: how many of the fifteen
 // stretches between them begin and end on different lines, and how many points lie on the line of the first and of

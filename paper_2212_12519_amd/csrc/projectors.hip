@@ -691,8 +691,8 @@ constexpr int64_t kLineRays = 11 << 19;
 constexpr int64_t kLineRaysTof = 1 << 20;  // TOF back projection
 
 // Lanes that share a ray in the ray-per-thread forwards: kParts of them while that leaves lanes of the chip idle.
-// A small call's time is one ray's, a wait for memory per kWalk planes: 25 of them on a grid of 100 planes (64,000
-// rays: 22.2 -> 18.6 us).  Only where rays are sinograms' or sorted: 100,001 unsorted TOF events stay at 61 us,
+// A small call's time is one ray's, a wait for memory per plane, of which each lane has a quarter (64,512 rays: 22.2 -> 15.9
+// us; four planes read at a time 17.2).  Only where rays are sinograms' or sorted: 100,001 unsorted TOF events stay at 61 us,
 // bound by their 20 M requests for cache lines.
 static bool split_rays(int64_t n) { return n <= (int64_t)device_cus() * (kBlock * 8 / kParts); }
 

@@ -140,8 +140,8 @@ static int pieces_bound(const GeomK& g, const TileGeom& tg, const TofK* t) {
     return (int)std::ceil(planes / tg.edge + 1.0) + (int)std::ceil(u / tg.edge + 1.0) + (int)std::ceil(z) + 1;
 }
 
-// Most events the tiles take.  The sheets' cost hardly grows with the events while a line has few of them
-// (clinical grid, 58.5 mm TOF, presorted: 3.9 ms at 1.5 M events, 5.6 ms at 15 M), the tiles' is
+// Most events the tiles take, on a scanner of 760 crystals a ring (tile_need: on others).  The sheets' cost hardly grows
+// with the events while a line has few of them (clinical grid, 58.5 mm TOF, presorted: 3.9 ms at 1.5 M events, 5.6 ms at 15 M), the tiles' is
 // proportional to the plane samples (0.71 and 6.3 ms; non-TOF 1.15 and 11 ms against 5.2 and 6.4 ms); both
 // limits lie a little below the crossings (serving grid 128 x 128 x 64: 13 M and 8 M).
 constexpr int64_t kTileEventsTof = 10'000'000;

@@ -132,3 +132,24 @@ def test_without_memory_for_a_workspace(gpu):
         torch.cuda.set_per_process_memory_fraction(1.0)
     assert peak < need
     assert rel_l2(img.cpu().numpy(), oracle.back(xs, xe, o, h, DIM, p)) <= BACK_TOL
+
+
+@pytest.mark.parametrize("mode", ["nontof", "tof", "missing"])
+def test_single_event(gpu, mode):
+    """One event, one record, nearly all tiles empty; and one that misses the grid, with no piece at all."""
+    from paper_2212_12519_amd import projectors as P
+
+    o, h = [f32(-(d - 1) / 2 * v) for d, v in zip(DIM, VOX)], [f32(v) for v in VOX]
+    xs, xe = np.array([[-200.0, 13.0, -7.0]], np.float32), np.array([[210.0, -31.0, 9.0]], np.float32)
+    if mode == "missing":
+        xs, xe = xs + np.float32(1e4), xe + np.float32(1e4)
+    p, bins = np.array([1.7], np.float32), np.array([5], np.int16)
+    dev = torch.device("cuda")
+    t = lambda a: torch.from_numpy(a).to(dev)  # noqa: E731
+    G, img = gpu.ImageGeom(DIM, VOX), torch.zeros((1, *DIM), device=dev)
+    T = gpu.TofParams(28.0, 24.8, 3.0, 9)
+    assert P._back_lm_tiles(t(xs), t(xe), 0, None, t(bins) if mode == "tof" else None, 1, G.c(),
+                            T.c(1) if mode == "tof" else None, img, 1, t(p), None)
+    want = oracle.back_tof_lm(xs, xe, o, h, DIM, tofd(28.0, 24.8, 3.0, 9), bins, p) if mode == "tof" else oracle.back(xs, xe, o, h, DIM, p)
+    got = img[0].cpu().numpy()
+    assert rel_l2(got, want) <= 1e-5 and want.any() == (mode != "missing") and got.any() == want.any()
