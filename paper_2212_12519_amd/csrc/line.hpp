@@ -82,7 +82,7 @@ __device__ inline bool line_group(const RaySrc& src, int64_t i0, int64_t n) {
 //   entries of the sheet.  Without TOF those meetings bound the kernel (40 M presorted events 11.8 ms by k_back_runs, 18.8
 //   by lines; lines of 1200 rays of random slices 1.25 and 1.63 ms); with TOF the lines are the faster all the same
 //   (lines of 1200 presorted rays 1.9 and 0.7 ms).
-constexpr int kLineRegular = 11, kLineLong = 545;
+constexpr int kLineRegular = 11, kLineLong = 500;
 
 __device__ inline bool back_lines_group(const RaySrc& src, int64_t i0, int64_t n, bool regular) {
     const LineProbe p = line_probe(src, i0, n);
