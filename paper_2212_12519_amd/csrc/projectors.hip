@@ -590,14 +590,12 @@ __global__ void __launch_bounds__(kSinoBlock, 4) k_fwd_tof_sino_lines(RaySrc src
                     else advance();
                 }
                 tof_edge_weights<R>((float)(B - fb), t, w);
-                if (__ballot(!(fabsf(v) <= FLT_MAX))) {  // only into the bins that the sample reaches: no 0 * inf
+                // only into the bins that the sample reaches, which are all but an outer one (R - 1 < reach <= R bins):
+                // v may be infinite
+                if (w[0] != 0.0f) acc[0] = fmaf(w[0], v, acc[0]);
+                if (w[2 * R] != 0.0f) acc[2 * R] = fmaf(w[2 * R], v, acc[2 * R]);
 #pragma unroll
-                    for (int i = 0; i <= 2 * R; ++i)
-                        if (w[i] != 0.0f) acc[i] = fmaf(w[i], v, acc[i]);
-                    return;
-                }
-#pragma unroll
-                for (int i = 0; i <= 2 * R; ++i) acc[i] = fmaf(w[i], v, acc[i]);
+                for (int i = 1; i < 2 * R; ++i) acc[i] = fmaf(w[i], v, acc[i]);
             };
             if (sheet) {
                 line_walk<false>(sheet, zs, r, sample, [](const float (&)[4]) {});
